@@ -89,8 +89,8 @@ typedef struct {
                                 span < 2 GiB); 0 = chosen from the grid size */
   int32_t graph_steps;       /* >0: replay steps from a captured HIP graph of this many steps */
   int32_t tune;              /* 1 (the default) with variant = 0 and zchunk = 0: wave_create
-                                times candidate configurations for a few steps on the fresh
-                                (zero) fields: the 2.5D shapes and z-chunks, both cache policies
+                                times candidate configurations for a few steps on fields of
+                                noise (zeroed afterwards): the 2.5D shapes and z-chunks, both cache policies
                                 (without CPML or adjoint), and for float32 forward runs without
                                 CPML or adjoint also the 3D-blocked gmem and smem shapes.  It
                                 keeps the fastest (the fixed rule's choice unless another is more
@@ -166,8 +166,7 @@ int wave_workspace_bytes(const wave_params *p, size_t *bytes);
  * the caller and borrowed until wave_destroy.  hip_stream: the hipStream_t all
  * work is queued on (NULL = default stream).  Synchronises that stream to read
  * back the velocity range and, with tune = 1 (a grid shape not yet tuned in
- * this process), to time a few steps of each candidate configuration on the
- * zeroed fields.  Errors: WAVE_EINVAL (bad params, pointer,
+ * this process), to time a few steps of each candidate configuration.  Errors: WAVE_EINVAL (bad params, pointer,
  * alignment, non-finite or non-positive velocity), WAVE_ENOSPC (workspace too
  * small), WAVE_EUNSTABLE (max(v) dt above the leapfrog stability limit
  * 2 / sqrt(2048/315 * sum_a h_a^-2)), WAVE_EHIP.  The state is reset:
@@ -289,7 +288,9 @@ int wave_variant_count(void);
 /* Shape of kernel variant `variant` (0 .. wave_variant_count()-1), written to
  * info[0..4] (caller-owned host array of 5): family, by, ry, pd, vec.
  * Family 0 is the 2.5D blocking of paper Sec. IV-A (tile x and y, stream
- * along z): tiles of 64*vec x by*ry nodes, pd planes of loads in flight.
+ * along z): by wavefronts of 64 lanes, ry rows and vec nodes along x per lane,
+ * pd planes of loads in flight; tiles of 64*vec x by*ry nodes (variants up to
+ * 19) or of the same number of nodes in another width (from 20 on).
  * Variant 0 means "automatic"; its info is the shape that choice falls back
  * to (also available explicitly as another variant).
  * Families 1 and 2 are the paper's 3D-blocking designs of the same section

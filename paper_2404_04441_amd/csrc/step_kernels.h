@@ -8,10 +8,11 @@
 // source and receivers in the same pass.  Blocking follows the 2.5D idea of
 // paper Sec. IV-A (tile x and y, stream along z) redesigned for CDNA4:
 //
-//  * a workgroup owns a (64*VEC) x (BY*RY) column of the grid over a z-chunk;
-//    each 64-lane wavefront owns RY consecutive rows and each lane VEC
-//    consecutive x nodes, so every global access of the interior is one
-//    coalesced row of 256*VEC bytes;
+//  * a workgroup of BY wavefronts owns an (LX*VEC) x (64*BY/LX*RY) column of
+//    the grid over a z-chunk; LX consecutive lanes own RY consecutive rows and
+//    each lane VEC consecutive x nodes, so every global access of the interior
+//    is made of coalesced row pieces of 4*LX*VEC bytes (LX = 64: one row per
+//    wavefront);
 //  * each field has one buffer resource per workgroup; the plane is the
 //    scalar offset, the row and column one lane register.  Lanes outside the
 //    grid use an offset past the resource's end (loads read zero, stores are
@@ -58,6 +59,15 @@ __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+// The same until an f returns false; whether all returned true.
+template <typename F, int... Is>
+__device__ __forceinline__ bool static_while_impl(F &&f, std::integer_sequence<int, Is...>) {
+  return (f(std::integral_constant<int, Is>{}) && ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ bool static_while(F &&f) {
+  return static_while_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 __device__ __forceinline__ float exp2i(int e) {  // 2^e, e in [-126, 127]
@@ -271,8 +281,9 @@ constexpr int kQ = 2 * R + 1;  // z-queue length (planes z-4 .. z+4)
 constexpr uint32_t kOOB = 0x80000000u;
 static_assert(kPadZ >= (kQ - 1) + kMaxPD + R, "z padding must cover the last trip's loads");
 
-// BY wavefronts per workgroup, RY consecutive rows per wavefront, VEC
-// consecutive x nodes per lane (tile 64*VEC x BY*RY), PD planes of loads in
+// BY wavefronts per workgroup, whose lanes form rows of LX lanes; RY
+// consecutive grid rows per row of lanes, VEC consecutive x nodes per lane
+// (tile LX*VEC x 64*BY/LX*RY), PD planes of loads in
 // flight ahead of the plane being computed (PD divides 9: the z loop is
 // unrolled 9 times so the queue rotates by register renaming instead of
 // copies).  VEC > 1 requires nx % VEC == 0 (whole rows stay aligned).
@@ -295,18 +306,20 @@ static_assert(kPadZ >= (kQ - 1) + kMaxPD + R, "z padding must cover the last tri
 // there from step to step (forward; chosen by create-time tuning or the
 // caller).
 // M16: m is read as 16-bit codes (m = m_lo + u m_step; 16-bit storage only).
-template <int S, int BY, int RY, int PD, int VEC, bool SEMI, bool ADJ, bool CP, bool KEEP, bool M16 = false>
+template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, bool ADJ, bool CP, bool KEEP, bool M16 = false>
 __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
-  using StageT = Stage<S, RY, VEC, (2 * R + BY - 1) / BY, ADJ, CP, M16>;
+  constexpr int ROWS = 64 * BY / LX;  // row groups of LX lanes
+  static_assert(64 * BY % LX == 0, "whole rows of lanes");
+  using StageT = Stage<S, RY, VEC, (2 * R + ROWS - 1) / ROWS, ADJ, CP, M16>;
   static_assert(!M16 || (S != kF32 && !ADJ && !CP && !SEMI), "16-bit model codes: 16-bit storage forward");
   constexpr int NA = StageT::NA, NF = StageT::NF;
-  constexpr int TX = kTileX * VEC;
-  constexpr int TY = BY * RY;
+  constexpr int TX = LX * VEC;
+  constexpr int TY = ROWS * RY;
   constexpr int LW = TX + 2 * R;
   constexpr int LH = TY + 2 * R;
-  constexpr int NYH = (2 * R + BY - 1) / BY;
+  constexpr int NYH = (2 * R + ROWS - 1) / ROWS;
   constexpr uint32_t ES = S == kF32 ? 4u : 2u;
-  static_assert(8 * RY <= 64, "x-halo of a wavefront's rows must fit in one load");
+  static_assert(8 * RY <= LX, "x-halo of a row group's rows must fit in one load");
   static_assert(kQ % PD == 0, "pipeline depth must divide the queue length");
   static_assert(PD <= kMaxPD, "z padding assumes at most kMaxPD planes in flight");
   static_assert(VEC == 1 || VEC == 2 || VEC == 4, "lane width");
@@ -365,8 +378,11 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const int zb = chunk * a.zchunk;
   const int zend = min(zb + a.zchunk, a.nz);
   const int ze = zb + (zend - zb + kQ - 1) / kQ * kQ;
-  const int lane = static_cast<int>(threadIdx.x) & 63;
-  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  // lane: position in its row of LX lanes; w: row group (with LX = 64 one
+  // wavefront, and w the same for all its lanes)
+  const int lane = LX == 64 ? static_cast<int>(threadIdx.x) & 63 : static_cast<int>(threadIdx.x) % LX;
+  const int w = LX == 64 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6)
+                         : static_cast<int>(threadIdx.x) / LX;
   const int nx = a.nx, ny = a.ny;
   const size_t plane = static_cast<size_t>(nx) * static_cast<size_t>(ny);
   const uint32_t pbytes = static_cast<uint32_t>(plane) * ES;
@@ -418,12 +434,12 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const char *U = static_cast<const char *>(a.cur);
   const char *P = static_cast<const char *>(a.prev);
   char *O = static_cast<char *>(a.out);
-  const rsrc_t rU = make_rsrc(U + base_b, span);
-  const rsrc_t rP = make_rsrc(P + base_b, span);
+  const rsrc_t rU_ = make_rsrc(U + base_b, span);
+  const rsrc_t rP_ = make_rsrc(P + base_b, span);
   const rsrc_t rO = make_rsrc(O + base_b, span);
   const rsrc_t rVo = make_rsrc((S != kF32 ? static_cast<char *>(a.vout) : O) + base_b, span);
-  const rsrc_t rM = M16 ? make_rsrc(reinterpret_cast<const char *>(a.m) + base * 2, span)
-                        : make_rsrc(a.m + base, span_f);
+  const rsrc_t rM_ = M16 ? make_rsrc(reinterpret_cast<const char *>(a.m) + base * 2, span)
+                         : make_rsrc(a.m + base, span_f);
   const rsrc_t rnull = make_rsrc(a.gz, 0u);
   const rsrc_t rF = make_rsrc((ADJ ? a.fwd : a.m) + base, span_f);
   const rsrc_t rI = make_rsrc((ADJ ? a.img : a.m) + base, ADJ ? span_f : 0u);
@@ -445,6 +461,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   }
   // the source node: qrow[j] = 1 in its lane and row, its column index srci
   const int srci = (!ADJ && a.sx >= 0) ? (a.sx - x0) % VEC : 0;
+  const bool src_tile = a.sx >= x0 && a.sx < x0 + TX && a.sy >= y0 && a.sy < y0 + TY;
 #pragma unroll
   for (int j = 0; j < RY; ++j) {
     const int yj = yb + j;
@@ -465,7 +482,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   uint32_t vyh[NYH], vyh_f[NYH];
 #pragma unroll
   for (int i = 0; i < NYH; ++i) {
-    const int r = w + BY * i;
+    const int r = w + ROWS * i;
     const bool yhin = r < 2 * R;
     const int lr = r < R ? r : TY + r;
     const int gyy = y0 - R + lr;
@@ -540,7 +557,11 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
                                           static_cast<uint32_t>(a.nrec) * 4u)
                               : rnull;
 
+  // loads of planes past the chunk's outputs (the last PD iterations issue
+  // them) go through a resource without records: no memory traffic
   auto load_stage = [&](StageT &st, int z) {
+    const bool live = !kSkipTail || z < zend;
+    const rsrc_t rU = live ? rU_ : rnull, rP = live ? rP_ : rnull, rM = live ? rM_ : rnull;
     const uint32_t sl = so(z + R), slf = so_f(z + R);
     const uint32_t sc = so(z), scf = so_f(z);
     st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
@@ -599,7 +620,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   for (int k = 0; k < 2 * R; ++k) {
     const int zz = zb - R + k;
     const bool zok = zz >= 0;
-    const rsrc_t r = zok ? rU : rnull;
+    const rsrc_t r = zok ? rU_ : rnull;
     const rsrc_t rf = zok ? rF : rnull;
     const uint32_t s0 = zok ? so(zz) : 0u, s0f = zok ? so_f(zz) : 0u;
 #pragma unroll
@@ -623,13 +644,13 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       for (int j = 0; j < RY; ++j) lds_put<VEC>(Lk + (R + w * RY + j) * LW + R + VEC * lane, q[R + k][j]);
 #pragma unroll
       for (int i = 0; i < NYH; ++i) {
-        const Words<NA> t = ld_words<NA, 0>(rU, vyh[i], s0);
+        const Words<NA> t = ld_words<NA, 0>(rU_, vyh[i], s0);
         float v[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = row_get<S>(t, e) * inv_cur;
         lds_put<VEC>(Lk + yhlds[i], v);
       }
-      Lk[xhlds] = row_get<S>(ld_words<S == kF32 ? 4 : 2, 0>(rU, vxh, s0), 0) * inv_cur;
+      Lk[xhlds] = row_get<S>(ld_words<S == kF32 ? 4 : 2, 0>(rU_, vxh, s0), 0) * inv_cur;
     }
   }
   // semi-stencil partials: slot (p - zb + R) mod 9 holds sum_m kz_m A(p-m) of plane p
@@ -647,6 +668,30 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           for (int m = R - 1; m >= 1; --m) t = fmaf(a.c.kz[m - 1], q[k - m][j][i] - c, t);
           X[k][j][i] = t;
         }
+  }
+  // Differences that two nodes share are subtracted once: u(k + m) - u(k) is
+  // node k's forward and, with the sign changed, node k + m's backward
+  // difference (a - b and b - a round to the same magnitude).  Along x and
+  // y between the nodes of one lane (kDiff).  Along z (kDz) they are kept
+  // from plane to plane: dz[m-1], slot of plane p, holds A(p + m) - A(p).
+  // With all three 42.5 instead of 48 operations per node at VEC = 4.  The
+  // z part costs 6 registers per node: the 16-bit forms, bound by
+  // instruction issue, gain 2-3% from it (f16 512^3 283 -> 277 us on zero
+  // fields); float32, bound by memory, gained nothing at 512^3 and lost
+  // where the registers cost a wavefront or spilled (384^3, 192x12 tiles:
+  // 133 -> 144 us).
+  constexpr bool kDiff = !SEMI && !CP && !kSumForm;
+  constexpr bool kDz = kDiff && S != kF32 && BY <= 8 && RY * VEC <= 4;  // the others would spill
+  float dz[kDz ? R : 1][kQ][RY][VEC];
+  if constexpr (kDz) {
+#pragma unroll
+    for (int m = 1; m <= R; ++m)
+#pragma unroll
+      for (int k = R - m; k < R; ++k)
+#pragma unroll
+        for (int j = 0; j < RY; ++j)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) dz[m - 1][k][j][i] = q[k + m][j][i] - q[k][j][i];
   }
   StageT stg[PD];
 #pragma unroll
@@ -668,16 +713,18 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // lap = (lax[0] + lax[1]) + lax[2].  sum_form (a compile-time flag): k0 u +
   // sum k_m (u(+m) + u(-m)) instead of the centred differences.
   auto laplacian = [&](const float (&Q)[kQ][RY][VEC], const float *Lp, int cs, int s0, int j, float *lap,
-                       const float (&Xp)[SEMI ? kQ : 1][RY][VEC], float (&lax)[3][VEC], auto sum_form)
-                       __attribute__((always_inline)) {
+                       const float (&Xp)[SEMI ? kQ : 1][RY][VEC], float (&lax)[3][VEC],
+                       float (&dy)[R][RY][VEC], auto sum_form) __attribute__((always_inline)) {
     constexpr bool kSum = decltype(sum_form)::value;
+    constexpr bool kPairs = kDiff && !kSum;
     const float *row = Lp + (R + w * RY + j) * LW + VEC * lane;  // window start: column x - R
     float win[VEC + 2 * R];
 #pragma unroll
     for (int k = 0; k < (VEC + 2 * R) / VEC; ++k)
-      if (VEC > 1 || k != R) lds_get<VEC>(row + VEC * k, win + VEC * k);
+      if (k != R / VEC) lds_get<VEC>(row + VEC * k, win + VEC * k);  // the lane's own nodes: from the queue
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
+      win[R + i] = Q[cs][j][i];
       lap[i] = kSum ? a.c.k0 * Q[cs][j][i] : 0.f;
       if constexpr (CP) {  // per axis, from the centre term (the sum form; see below)
 #pragma unroll
@@ -699,13 +746,35 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       } else {
         lds_get<VEC>(row - m * LW + R, ym);
       }
+      // along x, u(k + m) - u(k) of the window's nodes (see dz): nodes closer
+      // than VEC share them
+      float dx[VEC + R];
+      if constexpr (kPairs) {
+#pragma unroll
+        for (int k = 0; k < VEC + m; ++k) dx[k] = win[R + k] - win[R - m + k];
+      }
 #pragma unroll
       for (int i = 0; i < VEC; ++i) {
         // second differences from the centre: (u(+m) - u) + (u(-m) - u)
         const float c = Q[cs][j][i];
-        const float sx = (win[R + i + m] - c) + (win[R + i - m] - c);
-        const float sy = (yp[i] - c) + (ym[i] - c);
-        const float sz = (Q[(s0 + R + m) % kQ][j][i] - c) + (Q[(s0 + R - m + kQ) % kQ][j][i] - c);
+        float sx, sy, sz;
+        if constexpr (kPairs) {
+          sx = dx[i + m] - dx[i];
+          const float up = yp[i] - c;
+          sy = j - m >= 0 ? up - dy[m - 1][(j - m + RY) % RY][i] : up + (ym[i] - c);
+          dy[m - 1][j][i] = up;
+          const float fz = Q[(s0 + R + m) % kQ][j][i] - c;
+          if constexpr (kDz) {
+            sz = fz - dz[m - 1][(s0 + R - m + kQ) % kQ][j][i];
+            dz[m - 1][cs][j][i] = fz;
+          } else {
+            sz = fz + (Q[(s0 + R - m + kQ) % kQ][j][i] - c);
+          }
+        } else {
+          sx = (win[R + i + m] - c) + (win[R + i - m] - c);
+          sy = (yp[i] - c) + (ym[i] - c);
+          sz = (Q[(s0 + R + m) % kQ][j][i] - c) + (Q[(s0 + R - m + kQ) % kQ][j][i] - c);
+        }
         if constexpr (CP) {
           // The fused CPML kernel sums c_0 u + sum_m c_m (u(+m) + u(-m)) per
           // axis: it is issue-bound (its x boundary terms on top of the
@@ -744,11 +813,12 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   for (int zs = zb; zs < ze; zs += kQ) {
     // nine planes per trip with compile-time queue slots and stage indices, so
     // the queue rotates by register renaming (a runtime index would move the
-    // queue into scratch memory)
-    static_for<kQ>([&](auto sc) __attribute__((always_inline)) {
+    // queue into scratch memory).  The chunk's end leaves the loop at once, so
+    // that no value of an earlier trip stays live beside the rotated ones.
+    const bool more = static_while<kQ>([&](auto sc) __attribute__((always_inline)) {
       constexpr int s = decltype(sc)::value;
       const int z = zs + s;
-      if (kSkipTail && z >= zend) return;  // past the chunk: the same for the whole workgroup
+      if (kSkipTail && z >= zend) return false;  // past the chunk: the same for the whole workgroup
       constexpr int cslot = (s + R) % kQ;  // plane z
       StageT &cs = stg[s % PD];
       const int par = (z - zb) & 1;
@@ -792,16 +862,16 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       }
       Lw[xhlds] = row_get<S>(cs.xh, 0) * inv_cur;
       if constexpr (ADJ) LF[xhlds] = cs.xhF;
-      float *LX = ldsX[CP ? par : 0];
+      float *Lpsi = ldsX[CP ? par : 0];
       float zex[CP ? RY : 1][CP ? VEC : 1];
       if constexpr (CP) {
 #pragma unroll
         for (int j = 0; j < RY; ++j) {
-          lds_put<VEC>(LX + (w * RY + j) * LW + R + VEC * lane, cs.psx[j]);
+          lds_put<VEC>(Lpsi + (w * RY + j) * LW + R + VEC * lane, cs.psx[j]);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) zex[j][i] = cs.zex[j][i];
         }
-        LX[xhx] = cs.psxh;
+        Lpsi[xhx] = cs.psxh;
       }
       float pc[RY][VEC], mc[RY][VEC], ic[RY][VEC], rc[RY][VEC];
 #pragma unroll
@@ -825,16 +895,14 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 
       const uint32_t sz0 = so(z), sz0f = so_f(z);
       const bool zin = z < a.nz;
-      // source term of this plane, per column of the lane's VEC nodes
-      float wsp[VEC];
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) wsp[i] = (!ADJ && z == a.sz && i == srci) ? wsrc : 0.f;
+      const bool src_here = !ADJ && src_tile && z == a.sz;  // the same for the whole workgroup
+      float dy[R][RY][VEC];  // along y between this lane's own rows, as dz
       float outv[S == kF32 ? RY : 1][S == kF32 ? VEC : 1];  // float32: A^{n+1} of the plane's rows
       Words<NA> rkeep[S != kF32 ? RY : 1];                  // 16-bit: the stored rows (receivers)
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
         float lap[VEC], lax[3][VEC];
-        laplacian(q, L, cslot, s, j, lap, X, lax, std::integral_constant<bool, kSumForm>{});
+        laplacian(q, L, cslot, s, j, lap, X, lax, dy, std::integral_constant<bool, kSumForm>{});
         if constexpr (CP) {  // x part of the CPML terms: D1_x psi_x + zeta_x, zeta_x updated
           const int yj = yb + j;
           float ext[VEC], zn[VEC];
@@ -842,7 +910,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           // psi_x and zeta_x are zero off the layers
           {
             float px[VEC + 2 * R];
-            const float *xrow = LX + (w * RY + j) * LW + VEC * lane;
+            const float *xrow = Lpsi + (w * RY + j) * LW + VEC * lane;
 #pragma unroll
             for (int k = 0; k < (VEC + 2 * R) / VEC; ++k) lds_get<VEC>(xrow + VEC * k, px + VEC * k);
 #pragma unroll
@@ -864,22 +932,27 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           for (int i = 0; i < VEC; ++i) lap[i] += ext[i];
         }
         const float gyz = gyv[j] * gzv;
-        float v[VEC], vv[VEC];
+        float t[VEC], v[VEC], vv[VEC];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-          const float c = q[cslot][j][i];
           if (ADJ) lap[i] += rc[j][i];  // zero off the receivers
+          // float32: A^{n+1} = g (2 A^n - g A^{n-1} + m L A^n + q)
+          // 16-bit: V^{n+1} = g (V^n + m L A^n + q),  A^{n+1} = g A^n + V^{n+1}
           const float g = gxv[i] * gyz;
-          if (S == kF32) {  // A^{n+1} = g (2 A^n - g A^{n-1} + m L A^n + q)
-            float t = fmaf(-g, pc[j][i], 2.f * c);
-            t = fmaf(mc[j][i], lap[i], t);
-            if (!ADJ) t = fmaf(qrow[j], wsp[i], t);
-            v[i] = t * g;
-          } else {  // V^{n+1} = g (V^n + m L A^n + q),  A^{n+1} = g A^n + V^{n+1}
-            float t = fmaf(mc[j][i], lap[i], pc[j][i]);
-            t = fmaf(qrow[j], wsp[i], t);
-            vv[i] = t * g;
-            v[i] = fmaf(g, c, vv[i]);
+          t[i] = fmaf(mc[j][i], lap[i], S == kF32 ? fmaf(-g, pc[j][i], 2.f * q[cslot][j][i]) : pc[j][i]);
+        }
+        if (src_here) {
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) t[i] = fmaf(qrow[j], i == srci ? wsrc : 0.f, t[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const float g = gxv[i] * gyz;
+          if (S == kF32) {
+            v[i] = t[i] * g;
+          } else {
+            vv[i] = t[i] * g;
+            v[i] = fmaf(g, q[cslot][j][i], vv[i]);
           }
         }
         if constexpr (S == kF32) {
@@ -907,8 +980,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           // the imaging term L(A^k), only accumulated (no recurrence runs
           // through it): summed from the centre weight, 25 instead of 48
           // operations per node
-          float lapF[VEC], im[VEC], laxF[3][VEC];
-          laplacian(qF, LF, cslot, s, j, lapF, X, laxF, std::integral_constant<bool, true>{});
+          float lapF[VEC], im[VEC], laxF[3][VEC], dyF[R][RY][VEC];
+          laplacian(qF, LF, cslot, s, j, lapF, X, laxF, dyF, std::integral_constant<bool, true>{});
 #pragma unroll
           for (int i = 0; i < VEC; ++i) im[i] = fmaf(q[cslot][j][i], lapF[i], ic[j][i]);
           st_words<NF, kNT>(row_put<kF32, VEC>(im), rI, vrow_f[j], sz0f);
@@ -929,7 +1002,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
               a.traces[static_cast<size_t>(n) * a.nrec + (rzi * a.box.cny + ryi[j]) * a.box.cnx + rxi[i]] = val;
             }
       }
+      return true;
     });
+    if (!more) break;
   }
 
   if (S != kF32) {  // one order-independent atomic per workgroup and field
@@ -940,9 +1015,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       amax_loc = fmaxf(amax_loc, __shfl_xor(amax_loc, off, 64));
       amaxv_loc = fmaxf(amaxv_loc, __shfl_xor(amaxv_loc, off, 64));
     }
-    if (lane == 0) {
-      red[w] = amax_loc;
-      redv[w] = amaxv_loc;
+    if ((threadIdx.x & 63) == 0) {
+      red[threadIdx.x >> 6] = amax_loc;
+      redv[threadIdx.x >> 6] = amaxv_loc;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1372,36 +1447,56 @@ __global__ void __launch_bounds__(64 * kTbBY) step2_kernel(StepArgs a) {
   }
 }
 
-// Kernel variants (FAMILY, BY, RY, PD, VEC).  Family 0 is the 2.5D streaming
-// step_kernel (tile 64*VEC x BY*RY, PD planes in flight).  Variant 0 asks the
+// Kernel variants (FAMILY, BY, RY, PD, VEC, LX).  Family 0 is the 2.5D streaming
+// step_kernel (tile LX*VEC x 64*BY/LX*RY, PD planes in flight).  Variant 0 asks the
 // runtime for its automatic choice; its row is the shape that choice falls
 // back to, which variant 18 requests explicitly.  Families 1 (gmem)
 // and 2 (smem) are the 3D-blocked kernels with blocks of 64 x BY x RY nodes;
 // family 3 is the 2.5D kernel with the semi-stencil z sum; family 4 the
 // two-steps-per-pass kernel (step2_kernel; its shape is fixed).
-#define WAVE_VARIANTS(X)  \
-  X(0, 0, 8, 4, 3, 1)     \
-  X(1, 0, 4, 8, 1, 1)     \
-  X(2, 0, 4, 4, 3, 1)     \
-  X(3, 0, 8, 2, 3, 1)     \
-  X(4, 0, 4, 4, 1, 1)     \
-  X(5, 0, 8, 4, 1, 1)     \
-  X(6, 0, 2, 8, 1, 1)     \
-  X(7, 0, 4, 2, 3, 1)     \
-  X(8, 0, 8, 2, 3, 2)     \
-  X(9, 0, 8, 2, 1, 4)     \
-  X(10, 0, 4, 4, 1, 2)    \
-  X(11, 0, 8, 4, 1, 2)    \
-  X(12, 0, 8, 1, 3, 4)    \
-  X(13, 0, 4, 2, 3, 2)    \
-  X(14, 1, 4, 4, 1, 1)    \
-  X(15, 2, 4, 4, 1, 1)    \
-  X(16, 3, 8, 4, 3, 1)    \
-  X(17, 3, 8, 1, 3, 4)    \
-  X(18, 0, 8, 4, 3, 1)     \
-  X(19, 4, 8, 4, 1, 1)
+// Variants 20-28 hold one plane in flight and 4 nodes per lane, which leaves
+// registers for more wavefronts per SIMD, and lay tiles of other widths and
+// heights than 64 lanes give, so that a grid's tiles cover it with little
+// overhang and their number comes out near a multiple of the 256 CUs.
+// Measured on data-filled fields, float32, best of the tuned variants 0-19
+// -> with these: 128^3 12.3 -> 8.9 us a step (128x16 tiles, chunks of 4
+// planes), 256x192x128 23 -> 19.5 us (128x16), 320^3 99 -> 85 us (64x16),
+// 384^3 148 -> 139.5 us (192x12: 256 tiles in 4 chunks), 768^3 1427 ->
+// 1343 us (256x12: 768 workgroups, three full rounds); f16 256x192x128
+// 25.8 -> 21.7 us (128x16).  At 512^3 256x8 tiles with 1 or 3 planes in
+// flight are within 1% (343 and 344 us).
+#define WAVE_VARIANTS(X)    \
+  X(0, 0, 8, 4, 3, 1, 64)   \
+  X(1, 0, 4, 8, 1, 1, 64)   \
+  X(2, 0, 4, 4, 3, 1, 64)   \
+  X(3, 0, 8, 2, 3, 1, 64)   \
+  X(4, 0, 4, 4, 1, 1, 64)   \
+  X(5, 0, 8, 4, 1, 1, 64)   \
+  X(6, 0, 2, 8, 1, 1, 64)   \
+  X(7, 0, 4, 2, 3, 1, 64)   \
+  X(8, 0, 8, 2, 3, 2, 64)   \
+  X(9, 0, 8, 2, 1, 4, 64)   \
+  X(10, 0, 4, 4, 1, 2, 64)  \
+  X(11, 0, 8, 4, 1, 2, 64)  \
+  X(12, 0, 8, 1, 3, 4, 64)  \
+  X(13, 0, 4, 2, 3, 2, 64)  \
+  X(14, 1, 4, 4, 1, 1, 64)  \
+  X(15, 2, 4, 4, 1, 1, 64)  \
+  X(16, 3, 8, 4, 3, 1, 64)  \
+  X(17, 3, 8, 1, 3, 4, 64)  \
+  X(18, 0, 8, 4, 3, 1, 64)  \
+  X(19, 4, 8, 4, 1, 1, 64)  \
+  X(20, 0, 8, 1, 1, 4, 32)  \
+  X(21, 0, 4, 1, 1, 4, 32)  \
+  X(22, 0, 2, 1, 1, 4, 16)  \
+  X(23, 0, 4, 1, 1, 4, 16)  \
+  X(24, 0, 8, 1, 1, 4, 16)  \
+  X(25, 0, 8, 1, 1, 4, 64)  \
+  X(26, 0, 12, 1, 1, 4, 64) \
+  X(27, 0, 9, 1, 1, 4, 48)  \
+  X(28, 0, 10, 1, 1, 4, 80)
 
-#define WAVE_VARIANT_INFO(id, fam, by, ry, pd, vec) {by, ry, pd, vec, fam},
+#define WAVE_VARIANT_INFO(id, fam, by, ry, pd, vec, lx) {by, ry, pd, vec, fam, lx},
 constexpr Variant kVariants[] = {WAVE_VARIANTS(WAVE_VARIANT_INFO)};
 #undef WAVE_VARIANT_INFO
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
@@ -1414,37 +1509,37 @@ constexpr bool fuses_cpml() {
   return RY <= 2 && RY * VEC <= 4;
 }
 
-template <int S, int BY, int RY, int PD, int VEC, bool SEMI, bool ADJ, bool CP = false>
+template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, bool ADJ, bool CP = false>
 int blocks_per_cu() {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(step_kernel<S, BY, RY, PD, VEC, SEMI, ADJ, CP, false>), 64 * BY, 0) !=
+          &nb, reinterpret_cast<const void *>(step_kernel<S, BY, RY, PD, VEC, LX, SEMI, ADJ, CP, false>), 64 * BY, 0) !=
       hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 
-template <int FAM, int S, int BY, int RY, int PD, int VEC, bool ADJ>
+template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, bool ADJ>
 int blocks_fam(bool cpml) {
   if constexpr (FAM == 0 && S == kF32 && !ADJ && fuses_cpml<RY, VEC>())
-    if (cpml) return blocks_per_cu<S, BY, RY, PD, VEC, false, false, true>();
-  if constexpr (FAM == 0) return blocks_per_cu<S, BY, RY, PD, VEC, false, ADJ>();
-  if constexpr (FAM == 3 && S == kF32 && !ADJ) return blocks_per_cu<S, BY, RY, PD, VEC, true, false, false>();
+    if (cpml) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false, false, true>();
+  if constexpr (FAM == 0) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false, ADJ>();
+  if constexpr (FAM == 3 && S == kF32 && !ADJ) return blocks_per_cu<S, BY, RY, PD, VEC, LX, true, false, false>();
   return 1;  // the 3D-blocked kernels size their grids from the block shape alone
 }
 
 template <int S, bool ADJ>
 int blocks_variant(int v, bool cpml) {
   switch (v) {
-#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec) \
-  case id: return blocks_fam<fam, S, by, ry, pd, vec, ADJ>(cpml);
+#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec, lx) \
+  case id: return blocks_fam<fam, S, by, ry, pd, vec, lx, ADJ>(cpml);
     WAVE_VARIANTS(WAVE_VARIANT_CASE)
 #undef WAVE_VARIANT_CASE
     default: return 1;
   }
 }
 
-template <int FAM, int S, int BY, int RY, int PD, int VEC, bool ADJ, bool M16 = false>
+template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, bool ADJ, bool M16 = false>
 hipError_t launch_one(const StepArgs &a, hipStream_t s) {
   const unsigned grid = static_cast<unsigned>((a.total_tiles + 7) / 8 * 8);
   if constexpr (M16) {  // 16-bit storage forward with 16-bit model codes
@@ -1452,10 +1547,10 @@ hipError_t launch_one(const StepArgs &a, hipStream_t s) {
       return hipErrorInvalidValue;
     } else {
       if (a.keep)
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, false, false, false, true, true>), dim3(grid),
+        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, true, true>), dim3(grid),
                            dim3(64 * BY), 0, s, a);
       else
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, false, false, false, false, true>), dim3(grid),
+        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, false, true>), dim3(grid),
                            dim3(64 * BY), 0, s, a);
       return hipGetLastError();
     }
@@ -1463,26 +1558,26 @@ hipError_t launch_one(const StepArgs &a, hipStream_t s) {
     if constexpr (S == kF32 && !ADJ && fuses_cpml<RY, VEC>()) {
       if (a.cpml) {
         if (a.zchunk % kQ) return hipErrorInvalidValue;  // whole trips only (no skip branch)
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, false, false, true, false>), dim3(grid), dim3(64 * BY),
+        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, true, false>), dim3(grid), dim3(64 * BY),
                            0, s, a);
         return hipGetLastError();
       }
     }
     if constexpr (!ADJ) {
       if (a.keep) {
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, false, false, false, true>), dim3(grid), dim3(64 * BY),
+        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, true>), dim3(grid), dim3(64 * BY),
                            0, s, a);
         return hipGetLastError();
       }
     }
-    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, false, ADJ, false, false>), dim3(grid), dim3(64 * BY), 0, s,
+    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, ADJ, false, false>), dim3(grid), dim3(64 * BY), 0, s,
                        a);
   } else if constexpr (S != kF32 || ADJ) {
     return hipErrorInvalidValue;  // the study families are float32 forward only
   } else if constexpr (FAM == 4) {
     hipLaunchKernelGGL(step2_kernel, dim3(grid), dim3(64 * kTbBY), 0, s, a);
   } else if constexpr (FAM == 3) {
-    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, true, false, false, false>), dim3(grid), dim3(64 * BY), 0, s,
+    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, true, false, false, false>), dim3(grid), dim3(64 * BY), 0, s,
                        a);
   } else if constexpr (FAM == 1) {
     hipLaunchKernelGGL((gmem_kernel<BY, RY>), dim3(grid), dim3(64 * BY * RY), 0, s, a);
@@ -1495,8 +1590,8 @@ hipError_t launch_one(const StepArgs &a, hipStream_t s) {
 template <int S, bool ADJ, bool M16 = false>
 hipError_t launch_variant(int v, const StepArgs &a, hipStream_t s) {
   switch (v) {
-#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec) \
-  case id: return launch_one<fam, S, by, ry, pd, vec, ADJ, M16>(a, s);
+#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec, lx) \
+  case id: return launch_one<fam, S, by, ry, pd, vec, lx, ADJ, M16>(a, s);
     WAVE_VARIANTS(WAVE_VARIANT_CASE)
 #undef WAVE_VARIANT_CASE
     default: return hipErrorInvalidValue;

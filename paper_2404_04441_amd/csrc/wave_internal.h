@@ -127,6 +127,7 @@ struct Variant {
                // 3: 2.5D streaming with a semi-stencil z sum; 4: two time steps per
                // pass (families 1 and 2: blocks of 64 x by x ry nodes; families 1-4:
                // float32 forward only)
+  int lx;   // 2.5D: lanes per tile row (tile lx * vec x 64 * by / lx * ry nodes)
 };
 
 int variant_count();
@@ -167,6 +168,8 @@ hipError_t launch_check_finite(int storage, const void *field, size_t n, StepSta
 hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, size_t n,
                              hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+// n field values (storage type) to time candidate configurations on
+hipError_t launch_noise(int storage, void *field, size_t n, uint32_t seed, hipStream_t s);
 // psi_a^n = b psi_a^{n-1} + a D1_a cur, on the W-node layers
 hipError_t launch_cpml_psi(const CpmlArgs &c, const float *cur, hipStream_t s);
 // out += m * sum_a (D1_a psi_a + zeta_a), zeta_a = b zeta_a + a (D2_a cur + D1_a psi_a),

@@ -513,6 +513,20 @@ __global__ void grad_kernel(const float *__restrict__ img, const float *__restri
     grad[i] = 2.f * img[i] * dt / sqrtf(m[i]);
 }
 
+// Field values to time candidate configurations on (hash of the node index):
+// float32 in [-1, 1), 16-bit codes of magnitude below 2^10.
+template <int S>
+__global__ void noise_kernel(typename Codec<S>::raw *__restrict__ f, size_t n, uint32_t seed) {
+  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
+       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
+    uint32_t h = static_cast<uint32_t>(i) * 2654435761u + seed;
+    h = (h ^ (h >> 15)) * 2246822519u;
+    h ^= h >> 13;
+    const float v = static_cast<float>(static_cast<int32_t>(h)) * 0x1p-31f;
+    f[i] = Codec<S>::enc(S == kF32 ? v : v * 1024.f);
+  }
+}
+
 __global__ void zero_kernel(uint4 *p, size_t n16, uint8_t *tail, size_t ntail) {
   for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n16;
        i += static_cast<size_t>(gridDim.x) * blockDim.x)
@@ -543,7 +557,7 @@ Variant variant_info(int v) { return kVariants[v]; }
 
 bool variant_fuses_cpml(int v) {
   switch (v) {
-#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec) \
+#define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec, lx) \
   case id: return fam == 0 && fuses_cpml<ry, vec>();
     WAVE_VARIANTS(WAVE_VARIANT_CASE)
 #undef WAVE_VARIANT_CASE
@@ -600,6 +614,17 @@ hipError_t launch_bump(StepState *st, int count, hipStream_t s) {
 
 hipError_t launch_set_n(StepState *st, int n, hipStream_t s) {
   hipLaunchKernelGGL(set_n_kernel, dim3(1), dim3(64), 0, s, st, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_noise(int storage, void *field, size_t n, uint32_t seed, hipStream_t s) {
+  const dim3 g(grid_for(n, 256)), b(256);
+  switch (storage) {
+    case kF32: hipLaunchKernelGGL(noise_kernel<kF32>, g, b, 0, s, static_cast<float *>(field), n, seed); break;
+    case kF16: hipLaunchKernelGGL(noise_kernel<kF16>, g, b, 0, s, static_cast<uint16_t *>(field), n, seed); break;
+    case kBF16: hipLaunchKernelGGL(noise_kernel<kBF16>, g, b, 0, s, static_cast<uint16_t *>(field), n, seed); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -209,6 +209,7 @@ bool detect_box(const std::vector<int32_t> &rec, int nrec, RecBox *b) {
 // One tile decomposition of the grid for a step-kernel variant.
 struct Tiling {
   int variant = 0, tiles_x = 0, tiles_y = 0, nchunks = 0, zchunk = 0, total_tiles = 0;
+  float overhang = 1.f;  // 2.5D: nodes of the tiles of a plane over the plane's nodes
   bool keep = false;  // forward: regular cache policy for the fields streamed once
 };
 
@@ -262,10 +263,11 @@ Tiling make_tiling(const wave_params *p, int variant) {
     t.total_tiles = t.tiles_x * t.tiles_y * t.nchunks;
     return t;
   }
-  const int TY = v.by * v.ry;
-  const int TX = kTileX * v.vec;
+  const int TY = 64 * v.by / v.lx * v.ry;
+  const int TX = v.lx * v.vec;
   t.tiles_x = (nx + TX - 1) / TX;
   t.tiles_y = (ny + TY - 1) / TY;
+  t.overhang = static_cast<float>(t.tiles_x) * TX * t.tiles_y * TY / (static_cast<float>(nx) * ny);
   // a workgroup's buffer resources span its z-chunk rounded up to whole
   // nine-plane trips, R halo planes below and kMaxPD + R prefetch and halo
   // planes above; every span (float32 fields) must stay below 2^31 bytes.
@@ -528,8 +530,10 @@ int do_reset(wave_ctx *w) {
 }
 
 // ---- shape tuning: time each candidate (2.5D shape, z-chunk) for a few
-// steps on the zeroed fields and keep the fastest.  All candidates compute
-// identical bits, so the choice only changes speed.
+// steps and keep the fastest.  All candidates compute identical bits, so the
+// choice only changes speed.  The fields hold noise meanwhile: on zeros the
+// vector units draw less power, the clock stays higher (256^3: 37.5 us a step
+// on zeros, 41.9 on data) and the order of the candidates is another one.
 struct TuneEntry {
   int nx, ny, nz, storage, cache_hint, model_bits;
   bool cpml, adjoint;
@@ -537,6 +541,52 @@ struct TuneEntry {
 };
 std::mutex g_tune_mu;
 std::vector<TuneEntry> g_tune_cache;
+
+// The z-chunk lengths worth timing for a 2.5D shape: those whose workgroups
+// fill the CUs in 1 .. 6 whole rounds (as many chunks as fit in r rounds), and
+// a short list by the grid's size.  Short chunks pay on small grids, where more
+// workgroups hide the latency of each one's chain of planes (128^3: chunks of
+// 4 planes 8.9 us a step, of 9 planes 11 us); large grids lose more to the
+// overlap planes.
+std::vector<int> chunk_list(const wave_params &p, const Tiling &t) {
+  std::vector<int> z;
+  const int64_t per_plane = static_cast<int64_t>(t.tiles_x) * t.tiles_y;
+  const int64_t cap = 256 * static_cast<int64_t>(step_blocks_per_cu(p.storage, t.variant, p.cpml_width > 0));
+  for (int r = 1; r <= 6; ++r) {
+    const int64_t k = r * cap / per_plane;
+    if (k >= 1 && k <= p.nz) z.push_back(static_cast<int>((p.nz + k - 1) / k));
+  }
+  const int64_t nodes = static_cast<int64_t>(p.nx) * p.ny * p.nz;
+  const std::vector<int> list = nodes <= (int64_t(1) << 22)   ? std::vector<int>{3, 4, 5, 6, 9, 13}
+                                : nodes <= (int64_t(1) << 25) ? std::vector<int>{9, 13, 18, 27, 45}
+                                                              : std::vector<int>{45, 72, 99, 135, 198, 270};
+  for (int zc : list)
+    if (zc < p.nz) z.push_back(zc);
+  std::sort(z.begin(), z.end());
+  z.erase(std::unique(z.begin(), z.end()), z.end());
+  z.erase(std::remove(z.begin(), z.end(), t.zchunk), z.end());
+  return z;
+}
+
+// Whether a 2.5D shape is worth timing on this grid: its tiles hang over the
+// grid's edges by at most 1.4 times as much as the best-fitting shape's (the
+// overhang is work done on nothing).
+bool fits(const wave_params &p, int variant, bool cpml, float *best) {
+  auto overhang = [&](int v) {
+    wave_params q = p;
+    q.variant = v;
+    q.zchunk = std::max(1, std::min(p.nz, 16));  // the overhang does not depend on the chunk
+    return make_tiling(&q, v).overhang;
+  };
+  if (*best <= 0.f)
+    for (int v = 1; v < variant_count(); ++v) {
+      const Variant info = variant_info(v);
+      if (info.family != 0 || p.nx % info.vec || (cpml && !variant_fuses_cpml(v))) continue;
+      const float o = overhang(v);
+      if (*best <= 0.f || o < *best) *best = o;
+    }
+  return overhang(variant) <= 1.4f * *best;
+}
 
 int tune_forward(wave_ctx *w) {
   const wave_params &p = w->p;
@@ -554,17 +604,24 @@ int tune_forward(wave_ctx *w) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int rc = hip_rc(hipEventCreate(&e0));
   if (!rc) rc = hip_rc(hipEventCreate(&e1));
-  // no source while timing (the wavelet is not known yet); the fields stay zero
+  if (!rc) rc = hip_rc(launch_noise(p.storage, w->fa, w->N, 1u, w->stream));
+  if (!rc) rc = hip_rc(launch_noise(p.storage, p.storage == WAVE_F32 ? w->fb : w->fv, w->N, 2u, w->stream));
+  // no source while timing (the wavelet is not known yet)
   const int src_x = w->p.src[0];
   w->p.src[0] = -1;
   const Tiling fixed = w->fwd;
-  // milliseconds of 3 steps after 1 warm-up step, or a negative value on error
+  // steps per timing: 3, more where a step takes only microseconds (the
+  // event pair's own granularity would decide between candidates)
+  const int64_t nodes = static_cast<int64_t>(p.nx) * p.ny * p.nz;
+  const int nstep = nodes > (int64_t(1) << 24) ? 3 : (nodes > (int64_t(1) << 22) ? 5 : 8);
+  float best_overhang = 0.f;
+  // milliseconds of nstep steps after 1 warm-up step, or a negative value on error
   auto time_one = [&](const Tiling &t) {
     w->fwd = t;
     w->cpml_fused = w->cpml && variant_fuses_cpml(t.variant);
     int r = enqueue_steps(w, 1, nullptr, nullptr, false);
     if (!r) r = hip_rc(hipEventRecord(e0, w->stream));
-    if (!r) r = enqueue_steps(w, 3, nullptr, nullptr, false);
+    if (!r) r = enqueue_steps(w, nstep, nullptr, nullptr, false);
     if (!r) r = hip_rc(hipEventRecord(e1, w->stream));
     if (!r) r = hip_rc(hipEventSynchronize(e1));
     float ms = 0.f;
@@ -588,6 +645,7 @@ int tune_forward(wave_ctx *w) {
     }
     if (info.family != 0 || p.nx % info.vec) continue;
     if (w->cpml && !variant_fuses_cpml(v)) continue;
+    if (!fits(p, v, w->cpml, &best_overhang)) continue;
     wave_params q = p;
     q.variant = v;
     q.zchunk = 0;
@@ -601,7 +659,7 @@ int tune_forward(wave_ctx *w) {
   }
   std::vector<std::pair<float, Tiling>> timed;
   for (size_t i = 0; i < cands.size() && !rc; ++i) timed.emplace_back(time_one(cands[i]), cands[i]);
-  // stage 2: the z-chunk list for the four fastest 2.5D candidates of stage 1
+  // stage 2: the z-chunk lists of the four fastest 2.5D candidates of stage 1
   std::vector<std::pair<float, Tiling>> top;
   for (const auto &c : timed)
     if (variant_info(c.second.variant).family == 0) top.push_back(c);
@@ -610,8 +668,8 @@ int tune_forward(wave_ctx *w) {
   for (const auto &c : top) {
     wave_params q = p;
     q.variant = c.second.variant;
-    for (int zc : {9, 18, 27, 45, 72, 99, 135, 198, 270}) {
-      if (rc || zc >= p.nz) break;
+    for (int zc : chunk_list(p, c.second)) {
+      if (rc) break;
       q.zchunk = zc;
       Tiling t = make_tiling(&q, q.variant);
       t.keep = c.second.keep;
@@ -636,9 +694,9 @@ int tune_forward(wave_ctx *w) {
   w->cpml_fused = w->cpml && variant_fuses_cpml(w->fwd.variant);
   // Adjoint contexts: the adjoint step (two z queues, the forward field and
   // the imaging accumulator on top of the forward step's streams) is timed on
-  // its own, on the zero fields with no residual (wave_adjoint clears every
-  // buffer it reads before use): every 2.5D shape at its automatic z-chunk,
-  // then the z-chunk list for the two fastest, the default kept unless
+  // its own, with no residual, on whatever its buffers hold (wave_adjoint
+  // clears every buffer it reads before use): every 2.5D shape at its automatic z-chunk,
+  // then the z-chunk list (a shorter one) for the two fastest, the default kept unless
   // another is more than 3% faster.  All compute the same bits.
   if (!rc && p.adjoint) {
     const Layout &L = w->L;
@@ -672,6 +730,7 @@ int tune_forward(wave_ctx *w) {
     for (int v = 0; v < variant_count() && !rc; ++v) {
       const Variant info = variant_info(v);
       if (info.family != 0 || p.nx % info.vec || v == dflt.variant) continue;
+      if (!fits(p, v, false, &best_overhang)) continue;
       wave_params q = p;
       q.variant = v;
       q.zchunk = 0;
@@ -948,7 +1007,7 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
     w->cpml_fused = w->cpml && variant_fuses_cpml(w->fwd.variant);
   }
   if (!rc && p->tune && p->variant == 0 && p->zchunk == 0 && p->time_block == 0) {
-    rc = do_reset(w);  // zero fields (and CPML memory) for the timing runs
+    rc = do_reset(w);  // zero padding planes and CPML memory for the timing runs
     if (!rc) rc = tune_forward(w);
   }
   if (!rc) rc = do_reset(w);
