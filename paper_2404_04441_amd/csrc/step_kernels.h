@@ -99,7 +99,12 @@ typedef float f32x2v __attribute__((ext_vector_type(2)));
 template <> struct Codec<kF16> {
   using raw = uint16_t;
   __device__ static float dec(raw r) { return static_cast<float>(__builtin_bit_cast(_Float16, r)); }
-  __device__ static raw enc(float x) {  // round to nearest even (v_cvt_f16_f32)
+  // Round to nearest even (v_cvt_f16_f32) from the float32 value: made opaque,
+  // or the compiler would merge the conversion into the fma that forms it
+  // (v_fma_mixlo_f16, one rounding instead of two) where a lane holds one
+  // value, and other lane widths would give other bits.
+  __device__ static raw enc(float x) {
+    asm("" : "+v"(x));
     return __builtin_bit_cast(uint16_t, static_cast<_Float16>(x));
   }
   // two values, low half first: one v_cvt_pk_f16_f32 (round to nearest even)
@@ -133,7 +138,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 constexpr int kRsrcWord3 = 0x00020000;  // raw (untyped) buffer, gfx9 family
 constexpr int kNT = 2;                  // nontemporal cache policy bit
 
@@ -267,13 +271,85 @@ struct Stage {
   Words<NF> img[ADJ ? RY : 1];    // adjoint: imaging accumulator at plane z
   Words<NF> yhF[ADJ ? NYH : 1];
   float xhF;
-  float res[ADJ ? RY : 1][ADJ ? VEC : 1];  // adjoint: residual injected at receivers of plane z
   float psx[CP ? RY : 1][CP ? VEC : 1];  // CPML: psi_x at the lane's columns (0 off the x layers)
   float zex[CP ? RY : 1][CP ? VEC : 1];  // CPML: zeta_x at the lane's columns
   float psxh;                            // CPML: psi_x at this lane's x-halo node (lanes < 8*RY)
 };
 
 constexpr int kQ = 2 * R + 1;  // z-queue length (planes z-4 .. z+4)
+
+// 16-bit storage: the maxima of level k's stored magnitudes are the largest
+// over the state's record and kMaxSlots slots of that level, two words (A, V)
+// in a 128-byte line each: a workgroup raises one slot, so that a launch's
+// atomics spread over the slots instead of queueing on one line (11 ns each).
+__device__ __forceinline__ int max_slot(int level, int slot) {
+  return ((level & 3) * kMaxSlots + slot) * kMaxSlotStride;
+}
+// ma, mv := max with every slot of the level.  Lanes 0 .. 2 kMaxSlots - 1
+// load one word each (A in the first row of 16 lanes, V in the second), the
+// rows reduce by rotations; the values are ordered as unsigned bits.
+__device__ __forceinline__ void max_slots(const uint32_t *slots, int level, uint32_t &ma, uint32_t &mv) {
+  static_assert(kMaxSlots == 16, "one row of 16 lanes per field");
+  const int lane = static_cast<int>(threadIdx.x) & 31;
+  uint32_t v = slots[max_slot(level, lane & 15) + (lane >> 4)];
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x128, 0xf, 0xf, false)));
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x124, 0xf, 0xf, false)));
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x122, 0xf, 0xf, false)));
+  v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x121, 0xf, 0xf, false)));
+  ma = max(ma, static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 0)));
+  mv = max(mv, static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 16)));
+}
+
+constexpr int kFarScales = 40;  // factors up to 2^40 keep every product of the step in range
+
+// 16-bit storage with exponents far apart: the step on the nodes of one
+// workgroup's column, in true units, every stencil value loaded on its own.
+// The operations and their order are the main loop's, so the bits are the
+// ones it would give if its factors did not overflow.
+template <int S, bool M16, bool SUM>
+__device__ __forceinline__ void step_far(const StepArgs &a, int n, int x0, int y0, int tx, int ty, int zb, int zend,
+                                         int ea, int ev, int ea_next, int ev_next, float &amax, float &amaxv) {
+  using raw = typename Codec<S>::raw;
+  const raw *cur = static_cast<const raw *>(a.cur);
+  const float ia = exp2i(-ea), iv = exp2i(-ev), sa = exp2i(ea_next), sv = exp2i(ev_next);
+  const float wsrc = a.sx >= 0 ? a.wavelet[n] * a.src_scale : 0.f;
+  const int count = tx * ty * (zend - zb);
+  for (int k = static_cast<int>(threadIdx.x); k < count; k += static_cast<int>(blockDim.x)) {
+    const int x = x0 + k % tx, y = y0 + k / tx % ty, z = zb + k / (tx * ty);
+    if (x >= a.nx || y >= a.ny) continue;
+    auto at = [&](int i, int j, int l) {
+      const bool in = i >= 0 && i < a.nx && j >= 0 && j < a.ny && l >= 0 && l < a.nz;
+      return in ? Codec<S>::dec(cur[(static_cast<size_t>(l) * a.ny + j) * a.nx + i]) * ia : 0.f;
+    };
+    const size_t o = (static_cast<size_t>(z) * a.ny + y) * a.nx + x;
+    const float c = at(x, y, z);
+    float lap = SUM ? a.c.k0 * c : 0.f;
+    for (int m = 1; m <= R; ++m) {
+      const float xp = at(x + m, y, z), xm = at(x - m, y, z), yp = at(x, y + m, z), ym = at(x, y - m, z),
+                  zp = at(x, y, z + m), zm = at(x, y, z - m);
+      lap = fmaf(a.c.kx[m - 1], SUM ? xp + xm : (xp - c) + (xm - c), lap);
+      lap = fmaf(a.c.ky[m - 1], SUM ? yp + ym : (yp - c) + (ym - c), lap);
+      lap = fmaf(a.c.kz[m - 1], SUM ? zp + zm : (zp - c) + (zm - c), lap);
+    }
+    const float mc = M16 ? fmaf(static_cast<float>(reinterpret_cast<const uint16_t *>(a.m)[o]), a.m_step, a.m_lo) : a.m[o];
+    const float g = a.gx[x] * (a.gy[y] * a.gz[z]);
+    raw *vf = static_cast<raw *>(a.vout);
+    float t = fmaf(mc, lap, Codec<S>::dec(vf[o]) * iv);
+    if (x == a.sx && y == a.sy && z == a.sz) t = fmaf(1.f, wsrc, t);
+    const float vn = t * g, vs = vn * sv, as = fmaf(g, c, vn) * sa;
+    static_cast<raw *>(a.out)[o] = Codec<S>::enc(as);
+    vf[o] = Codec<S>::enc(vs);
+    amax = fmaxf(amax, fabsf(as));
+    amaxv = fmaxf(amaxv, fabsf(vs));
+    if (a.box.cnx > 0 && a.rz[z] >= 0) {
+      const int dx = x - a.box.x0, dy = y - a.box.y0;
+      if (dx >= 0 && dx % a.box.sx == 0 && dx / a.box.sx < a.box.cnx && dy >= 0 && dy % a.box.sy == 0 &&
+          dy / a.box.sy < a.box.cny)
+        a.traces[static_cast<size_t>(n) * a.nrec + (a.rz[z] * a.box.cny + dy / a.box.sy) * a.box.cnx + dx / a.box.sx] =
+            Codec<S>::dec(Codec<S>::enc(as)) * exp2i(-ea_next);
+    }
+  }
+}
 
 // Lane byte offset past the end of every buffer resource the step kernel
 // builds (each spans less than 2^31 bytes, and resource offset plus this
@@ -391,32 +467,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const bool xin = x < nx;        // all VEC columns (nx % VEC == 0)
   const int yb = y0 + w * RY;     // first row of this wavefront
 
-  // ---- step index and 16-bit field scales.  16-bit storage: the exponents of
-  // A^{n+1} and V^{n+1} come from bounds valid at every node,
-  //   |V^{n+1}| <= max|V^n| + gamma max|A^n| + |q^n| = bV,  |A^{n+1}| <= max|A^n| + bV,
-  // so each is fixed before anything is written.
-  const int n = ADJ ? 0 : a.st->n + a.k;
-  float inv_cur = 1.f, inv_prev = 1.f, s_next = 1.f, inv_next = 1.f, sv_next = 1.f;
-  if (S != kF32) {
-    const int ea = a.st->exps[n & 3], ev = a.st->exps_v[n & 3];
-    inv_cur = exp2i(-ea);
-    inv_prev = exp2i(-ev);
-    const float a_a = __uint_as_float(a.st->amax[n & 3]) * inv_cur;
-    const float a_v = __uint_as_float(a.st->amax_v[n & 3]) * inv_prev;
-    const float qmag = a.sx >= 0 ? fabsf(a.wavelet[n]) * a.src_scale : 0.f;
-    const float bv = a_v + a.gamma * a_a + qmag;
-    const int ea_next = scale_exponent(a_a + bv), ev_next = scale_exponent(bv);
-    s_next = exp2i(ea_next);
-    inv_next = exp2i(-ea_next);
-    sv_next = exp2i(ev_next);
-    if (logical == 0 && threadIdx.x == 0) {
-      a.st->exps[(n + 1) & 3] = ea_next;
-      a.st->exps_v[(n + 1) & 3] = ev_next;
-      a.st->amax[(n + 2) & 3] = 0u;
-      a.st->amax_v[(n + 2) & 3] = 0u;
-    }
-  }
-
   // ---- buffer resources: one per field for the whole workgroup, based at
   // the first plane it touches (zlo) and spanning the planes [zlo, zhi) its
   // trips, prefetches and halo cover (the host keeps every span below 2^31
@@ -446,22 +496,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   auto so = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes; };     // plane offset, A fields
   auto so_f = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes_f; };  // plane offset, float fields
 
-  // ---- per-row data (wavefront-uniform) and per-lane offsets
-  float gxv[VEC], gyv[RY], qrow[RY];
-  int ryi[RY], rxi[VEC];
-  uint32_t vrow[RY], vrow_f[RY];  // lane byte offset of (x, row j) in a plane, or kOOB
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) {
-    gxv[i] = xin ? a.gx[x + i] : 0.f;
-    rxi[i] = -1;
-    if (a.box.cnx > 0 && xin) {
-      const int d = x + i - a.box.x0;
-      if (d >= 0 && d % a.box.sx == 0 && d / a.box.sx < a.box.cnx) rxi[i] = d / a.box.sx;
-    }
-  }
-  // the source node: qrow[j] = 1 in its lane and row, its column index srci
-  const int srci = (!ADJ && a.sx >= 0) ? (a.sx - x0) % VEC : 0;
-  const bool src_tile = a.sx >= x0 && a.sx < x0 + TX && a.sy >= y0 && a.sy < y0 + TY;
+  // ---- lane byte offsets of (x, row j) in a plane, or kOOB
+  uint32_t vrow[RY], vrow_f[RY];
 #pragma unroll
   for (int j = 0; j < RY; ++j) {
     const int yj = yb + j;
@@ -469,13 +505,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const uint32_t e = static_cast<uint32_t>(yj) * static_cast<uint32_t>(nx) + static_cast<uint32_t>(x);
     vrow[j] = ok ? e * ES : kOOB;
     vrow_f[j] = ok ? e * 4u : kOOB;
-    gyv[j] = yj < ny ? a.gy[yj] : 0.f;
-    ryi[j] = -1;
-    if (a.box.cnx > 0 && yj < ny) {
-      const int d = yj - a.box.y0;
-      if (d >= 0 && d % a.box.sy == 0 && d / a.box.sy < a.box.cny) ryi[j] = d / a.box.sy;
-    }
-    qrow[j] = (!ADJ && a.sx >= 0 && a.sx >= x && a.sx < x + VEC && yj == a.sy) ? 1.f : 0.f;
   }
   // y-halo rows of this wavefront: halo row r = w + BY*i (r < R above the tile, else below)
   int yhlds[NYH];
@@ -548,8 +577,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   };
   // per-plane tables, nz + kPadZ entries: the padding planes read sponge
   // factor 0 and receiver index -1
-  const rsrc_t rgz = make_rsrc(a.gz, static_cast<uint32_t>(a.nz + kPadZ) * 4u);
-  const rsrc_t rrz = make_rsrc(a.rz, static_cast<uint32_t>(a.nz + kPadZ) * 4u);
+  // (one resource over both: rz lies behind gz in the workspace)
+  const uint32_t rz_off = static_cast<uint32_t>(reinterpret_cast<const char *>(a.rz) - reinterpret_cast<const char *>(a.gz));
+  const rsrc_t rgz = make_rsrc(a.gz, rz_off + static_cast<uint32_t>(a.nz + kPadZ) * 4u);
   // residual row of this launch (adjoint); the resource covers exactly that
   // row.  Without receivers it has no records (its loads return zero).
   const bool has_res = ADJ && a.resid != nullptr && a.nrec > 0;
@@ -565,7 +595,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const uint32_t sl = so(z + R), slf = so_f(z + R);
     const uint32_t sc = so(z), scf = so_f(z);
     st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
-    st.rz = static_cast<int>(ld_words<4, 0>(rrz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
+    st.rz = static_cast<int>(ld_words<4, 0>(rgz, 0u, rz_off + static_cast<uint32_t>(z) * 4u).w[0]);
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
       st.lead[j] = ld_words<NA, 0>(rU, vrow[j], sl);
@@ -584,16 +614,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
       for (int i = 0; i < NYH; ++i) st.yhF[i] = ld_words<NF, 0>(rF, vyh_f[i], scf);
       st.xhF = __uint_as_float(ld_words<4, 0>(rF, vxh_f, scf).w[0]);
-      const int rzi = rec_plane(z);
-#pragma unroll
-      for (int j = 0; j < RY; ++j)
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          const bool at = rzi >= 0 && ryi[j] >= 0 && rxi[i] >= 0;
-          const uint32_t ridx =
-              at ? static_cast<uint32_t>((rzi * a.box.cny + ryi[j]) * a.box.cnx + rxi[i]) * 4u : kOOB;
-          st.res[j][i] = __uint_as_float(ld_words<4, 0>(rres, ridx, 0u).w[0]);
-        }
     }
     if constexpr (CP) {  // x slab plane z (none past nz); zero off the x layers
       const bool zin = z < a.nz;
@@ -613,9 +633,15 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     }
   };
 
-  // ---- prologue: queue slot (p - zb + R) mod 9 holds plane p; stages hold planes zb .. zb+PD-1
-  float q[kQ][RY][VEC];
-  float qF[ADJ ? kQ : 1][RY][VEC];
+  // ---- prologue.  Every load of it is issued first, the planes' own and
+  // those of the first PD stages, so that the tables, the receiver indices
+  // and the 16-bit scales (a chain of small loads) are worked out while they
+  // are in flight.  Queue slot (p - zb + R) mod 9 holds plane p; stages hold
+  // planes zb .. zb+PD-1.
+  Words<NA> pq[2 * R][RY];
+  Words<NF> pqF[ADJ ? 2 * R : 1][RY];
+  Words<NA> pyh[LEADH ? R : 1][NYH];
+  Words<S == kF32 ? 4 : 2> pxh[LEADH ? R : 1];
 #pragma unroll
   for (int k = 0; k < 2 * R; ++k) {
     const int zz = zb - R + k;
@@ -625,32 +651,126 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const uint32_t s0 = zok ? so(zz) : 0u, s0f = zok ? so_f(zz) : 0u;
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
-      const Words<NA> t = ld_words<NA, 0>(r, vrow[j], s0);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) q[k][j][i] = row_get<S>(t, i) * inv_cur;
-      if constexpr (ADJ) {
-        const Words<NF> tf = ld_words<NF, 0>(rf, vrow_f[j], s0f);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) qF[k][j][i] = __uint_as_float(tf.w[i]);
-      }
+      pq[k][j] = ld_words<NA, 0>(r, vrow[j], s0);
+      if constexpr (ADJ) pqF[k][j] = ld_words<NF, 0>(rf, vrow_f[j], s0f);
     }
   }
+  if constexpr (LEADH) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const uint32_t s0 = so(zb + k);
+#pragma unroll
+      for (int i = 0; i < NYH; ++i) pyh[k][i] = ld_words<NA, 0>(rU_, vyh[i], s0);
+      pxh[k] = ld_words<S == kF32 ? 4 : 2, 0>(rU_, vxh, s0);
+    }
+  }
+  StageT stg[PD];
+#pragma unroll
+  for (int s = 0; s < PD; ++s) load_stage(stg[s], zb + s);
+
+  // ---- per-row data and the receiver indices of the lane's nodes
+  float gxv[VEC], gyv[RY], qrow[RY];
+  int ryi[RY], rxi[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    gxv[i] = xin ? a.gx[x + i] : 0.f;
+    rxi[i] = -1;
+    if (a.box.cnx > 0 && xin) {
+      const int d = x + i - a.box.x0;
+      if (d >= 0 && d % a.box.sx == 0 && d / a.box.sx < a.box.cnx) rxi[i] = d / a.box.sx;
+    }
+  }
+  // the source node: qrow[j] = 1 in its lane and row, its column index srci
+  const int srci = (!ADJ && a.sx >= 0) ? (a.sx - x0) % VEC : 0;
+  const bool src_tile = a.sx >= x0 && a.sx < x0 + TX && a.sy >= y0 && a.sy < y0 + TY;
+#pragma unroll
+  for (int j = 0; j < RY; ++j) {
+    const int yj = yb + j;
+    gyv[j] = yj < ny ? a.gy[yj] : 0.f;
+    ryi[j] = -1;
+    if (a.box.cnx > 0 && yj < ny) {
+      const int d = yj - a.box.y0;
+      if (d >= 0 && d % a.box.sy == 0 && d / a.box.sy < a.box.cny) ryi[j] = d / a.box.sy;
+    }
+    qrow[j] = (!ADJ && a.sx >= 0 && a.sx >= x && a.sx < x + VEC && yj == a.sy) ? 1.f : 0.f;
+  }
+
+  // ---- step index and 16-bit field scales.  16-bit storage: the exponents of
+  // A^{n+1} and V^{n+1} come from bounds valid at every node,
+  //   |V^{n+1}| <= max|V^n| + gamma max|A^n| + |q^n| = bV,  |A^{n+1}| <= max|A^n| + bV,
+  // so each is fixed before anything is written.
+  //
+  // The step runs in the stored units, a = 2^ea A and v = 2^ev V, so that
+  // decoding a value multiplies nothing and the scales enter once per node
+  // through m (2^(ev-ea)) and the factors of the stores.  Scaling by powers
+  // of two is exact, so the bits are those of the update in true units.
+  // Where the exponents lie so far apart that a factor could overflow (fields
+  // set to arbitrary scales by wave_write_field), the chunk is advanced in
+  // true units, node by node (step_far).
+  const int n = ADJ ? 0 : a.st->n + a.k;
+  bool far = false;
+  int ea = 0, ev = 0, ea_next = 0, ev_next = 0;
+  float m_unit = 1.f, v_unit = 1.f, inv_next = 1.f;
+  float out_a = 1.f, out_va = 1.f, out_v = 1.f;  // 2^(ea_next - ea), 2^(ea_next - ev), 2^(ev_next - ev)
+  if constexpr (S != kF32) {
+    ea = a.st->exps[n & 3];
+    ev = a.st->exps_v[n & 3];
+    uint32_t ma = a.st->amax[n & 3], mv = a.st->amax_v[n & 3];
+    max_slots(a.slots, n, ma, mv);
+    const float a_a = __uint_as_float(ma) * exp2i(-ea);
+    const float a_v = __uint_as_float(mv) * exp2i(-ev);
+    const float qmag = a.sx >= 0 ? fabsf(a.wavelet[n]) * a.src_scale : 0.f;
+    const float bv = a_v + a.gamma * a_a + qmag;
+    ea_next = scale_exponent(a_a + bv);
+    ev_next = scale_exponent(bv);
+    const int apart = max(max(abs(ev - ea), abs(ea_next - ea)), max(abs(ea_next - ev), abs(ev_next - ev)));
+    far = __builtin_amdgcn_readfirstlane(apart) > kFarScales;
+    if (!far) {
+      m_unit = exp2i(ev - ea);
+      v_unit = exp2i(ev);
+      out_a = exp2i(ea_next - ea);
+      out_va = exp2i(ea_next - ev);
+      out_v = exp2i(ev_next - ev);
+    }
+    inv_next = exp2i(-ea_next);
+    if (logical == 0) {
+      if (threadIdx.x == 0) {
+        a.st->exps[(n + 1) & 3] = ea_next;
+        a.st->exps_v[(n + 1) & 3] = ev_next;
+        a.st->amax[(n + 2) & 3] = 0u;
+        a.st->amax_v[(n + 2) & 3] = 0u;
+      }
+      if (threadIdx.x < 2 * kMaxSlots) a.slots[max_slot(n + 2, threadIdx.x >> 1) + (threadIdx.x & 1)] = 0u;
+    }
+  }
+
+
+  // ---- queue and ring from the prologue's loads
+  float q[kQ][RY][VEC];
+  float qF[ADJ ? kQ : 1][RY][VEC];
+#pragma unroll
+  for (int k = 0; k < 2 * R; ++k)
+#pragma unroll
+    for (int j = 0; j < RY; ++j)
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        q[k][j][i] = row_get<S>(pq[k][j], i);
+        if constexpr (ADJ) qF[k][j][i] = __uint_as_float(pqF[k][j].w[i]);
+      }
   if constexpr (LEADH) {  // ring slots 0 .. R-1: planes zb .. zb+R-1 with their halo
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       float *Lk = lds[k];
-      const uint32_t s0 = so(zb + k);
 #pragma unroll
       for (int j = 0; j < RY; ++j) lds_put<VEC>(Lk + (R + w * RY + j) * LW + R + VEC * lane, q[R + k][j]);
 #pragma unroll
       for (int i = 0; i < NYH; ++i) {
-        const Words<NA> t = ld_words<NA, 0>(rU_, vyh[i], s0);
         float v[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = row_get<S>(t, e) * inv_cur;
+        for (int e = 0; e < VEC; ++e) v[e] = row_get<S>(pyh[k][i], e);
         lds_put<VEC>(Lk + yhlds[i], v);
       }
-      Lk[xhlds] = row_get<S>(ld_words<S == kF32 ? 4 : 2, 0>(rU_, vxh, s0), 0) * inv_cur;
+      Lk[xhlds] = row_get<S>(pxh[k], 0);
     }
   }
   // semi-stencil partials: slot (p - zb + R) mod 9 holds sum_m kz_m A(p-m) of plane p
@@ -693,17 +813,15 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
           for (int i = 0; i < VEC; ++i) dz[m - 1][k][j][i] = q[k + m][j][i] - q[k][j][i];
   }
-  StageT stg[PD];
-#pragma unroll
-  for (int s = 0; s < PD; ++s) load_stage(stg[s], zb + s);
-
-  const float wsrc = (!ADJ && a.sx >= 0) ? a.wavelet[n] * a.src_scale : 0.f;
-  // 16-bit storage: running maxima of the stored magnitudes kept as 16-bit
-  // patterns with the sign cleared, both halves of a word per instruction;
-  // for f16 and bf16 the magnitude order of finite values is the unsigned
-  // order of those bits, so the maxima decode to max |stored| exactly
+  const float wsrc = (!ADJ && a.sx >= 0) ? a.wavelet[n] * a.src_scale * v_unit : 0.f;
+  // 16-bit storage: running maxima of the magnitudes before they are rounded,
+  // two values per instruction; rounding is monotonic, so the rounded maximum
+  // is the largest stored magnitude
   float amax_loc = 0.f, amaxv_loc = 0.f;
-  u16x2 amax_bits = {0, 0}, amaxv_bits = {0, 0};
+  const float m_step = a.m_step * m_unit, m_lo = a.m_lo * m_unit;
+  float gxa[VEC];  // the x sponge factor in units of the stored A^{n+1}
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) gxa[i] = gxv[i] * out_a;
 
   // Laplacian of Eq. 1 at the VEC nodes of row j of this lane: centre and z
   // neighbours from the queue Q, x neighbours from a window of the LDS row,
@@ -810,7 +928,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     }
   };
 
-  for (int zs = zb; zs < ze; zs += kQ) {
+  if (S != kF32 && far)
+    step_far<S, M16, kSumForm>(a, n, x0, y0, TX, TY, zb, zend, ea, ev, ea_next, ev_next, amax_loc, amaxv_loc);
+  for (int zs = far ? ze : zb; zs < ze; zs += kQ) {
     // nine planes per trip with compile-time queue slots and stage indices, so
     // the queue rotates by register renaming (a runtime index would move the
     // queue into scratch memory).  The chunk's end leaves the loop at once, so
@@ -830,7 +950,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) q[(s + 2 * R) % kQ][j][i] = row_get<S>(cs.lead[j], i) * inv_cur;
+        for (int i = 0; i < VEC; ++i) q[(s + 2 * R) % kQ][j][i] = row_get<S>(cs.lead[j], i);
         lds_put<VEC>(Lw + (R + w * RY + j) * LW + R + VEC * lane, q[LEADH ? (s + 2 * R) % kQ : cslot][j]);
         if constexpr (SEMI) {  // left half of plane z+R from planes z .. z+R-1
 #pragma unroll
@@ -852,7 +972,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       for (int k = 0; k < NYH; ++k) {
         float t[VEC];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) t[i] = row_get<S>(cs.yh[k], i) * inv_cur;
+        for (int i = 0; i < VEC; ++i) t[i] = row_get<S>(cs.yh[k], i);
         lds_put<VEC>(Lw + yhlds[k], t);
         if constexpr (ADJ) {
 #pragma unroll
@@ -860,7 +980,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           lds_put<VEC>(LF + yhlds[k], t);
         }
       }
-      Lw[xhlds] = row_get<S>(cs.xh, 0) * inv_cur;
+      Lw[xhlds] = row_get<S>(cs.xh, 0);
       if constexpr (ADJ) LF[xhlds] = cs.xhF;
       float *Lpsi = ldsX[CP ? par : 0];
       float zex[CP ? RY : 1][CP ? VEC : 1];
@@ -873,20 +993,20 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
         }
         Lpsi[xhx] = cs.psxh;
       }
-      float pc[RY][VEC], mc[RY][VEC], ic[RY][VEC], rc[RY][VEC];
+      float pc[RY][VEC], mc[RY][VEC], ic[RY][VEC];
 #pragma unroll
       for (int j = 0; j < RY; ++j)
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-          pc[j][i] = row_get<S>(cs.p[j], i) * inv_prev;
+          pc[j][i] = row_get<S>(cs.p[j], i);
           if constexpr (M16) {
             const uint32_t u = (cs.m[j].w[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-            mc[j][i] = fmaf(static_cast<float>(u), a.m_step, a.m_lo);
+            mc[j][i] = fmaf(static_cast<float>(u), m_step, m_lo);
           } else {
             mc[j][i] = __uint_as_float(cs.m[j].w[i]);
+            if constexpr (S != kF32) mc[j][i] *= m_unit;
           }
           ic[j][i] = ADJ ? __uint_as_float(cs.img[ADJ ? j : 0].w[i]) : 0.f;
-          rc[j][i] = ADJ ? cs.res[ADJ ? j : 0][ADJ ? i : 0] : 0.f;
         }
       const float gzv = cs.gz;
       const int rzi = ADJ ? rec_plane(z) : __builtin_amdgcn_readfirstlane(cs.rz);
@@ -899,9 +1019,11 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       float dy[R][RY][VEC];  // along y between this lane's own rows, as dz
       float outv[S == kF32 ? RY : 1][S == kF32 ? VEC : 1];  // float32: A^{n+1} of the plane's rows
       Words<NA> rkeep[S != kF32 ? RY : 1];                  // 16-bit: the stored rows (receivers)
+      float t[RY][VEC];  // the Laplacian, then 2 A^n - g A^{n-1} + m L A^n + q (16-bit: V^n + m L A^n + q)
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
-        float lap[VEC], lax[3][VEC];
+        float (&lap)[VEC] = t[j];
+        float lax[3][VEC];
         laplacian(q, L, cslot, s, j, lap, X, lax, dy, std::integral_constant<bool, kSumForm>{});
         if constexpr (CP) {  // x part of the CPML terms: D1_x psi_x + zeta_x, zeta_x updated
           const int yj = yb + j;
@@ -931,28 +1053,42 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
           for (int i = 0; i < VEC; ++i) lap[i] += ext[i];
         }
+        if (ADJ && rzi >= 0) {  // residuals of a receiver plane
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) {
+            const bool at = ryi[j] >= 0 && rxi[i] >= 0;
+            const uint32_t ridx =
+                at ? static_cast<uint32_t>((rzi * a.box.cny + ryi[j]) * a.box.cnx + rxi[i]) * 4u : kOOB;
+            lap[i] += __uint_as_float(ld_words<4, 0>(rres, ridx, 0u).w[0]);
+          }
+        }
         const float gyz = gyv[j] * gzv;
-        float t[VEC], v[VEC], vv[VEC];
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          if (ADJ) lap[i] += rc[j][i];  // zero off the receivers
-          // float32: A^{n+1} = g (2 A^n - g A^{n-1} + m L A^n + q)
-          // 16-bit: V^{n+1} = g (V^n + m L A^n + q),  A^{n+1} = g A^n + V^{n+1}
-          const float g = gxv[i] * gyz;
-          t[i] = fmaf(mc[j][i], lap[i], S == kF32 ? fmaf(-g, pc[j][i], 2.f * q[cslot][j][i]) : pc[j][i]);
-        }
-        if (src_here) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) t[i] = fmaf(qrow[j], i == srci ? wsrc : 0.f, t[i]);
-        }
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
           const float g = gxv[i] * gyz;
+          t[j][i] = fmaf(mc[j][i], lap[i], S == kF32 ? fmaf(-g, pc[j][i], 2.f * q[cslot][j][i]) : pc[j][i]);
+        }
+      }
+      if (src_here) {
+#pragma unroll
+        for (int j = 0; j < RY; ++j)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) t[j][i] = fmaf(qrow[j], i == srci ? wsrc : 0.f, t[j][i]);
+      }
+#pragma unroll
+      for (int j = 0; j < RY; ++j) {
+        // float32: A^{n+1} = g t.  16-bit: V^{n+1} = g t, A^{n+1} = g A^n +
+        // V^{n+1}, in units of what is stored
+        const float gyz = gyv[j] * gzv;
+        float v[VEC], vv[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const float vn = t[j][i] * (gxv[i] * gyz);
           if (S == kF32) {
-            v[i] = t[i] * g;
+            v[i] = vn;
           } else {
-            vv[i] = t[i] * g;
-            v[i] = fmaf(g, q[cslot][j][i], vv[i]);
+            vv[i] = vn * out_v;
+            v[i] = fmaf(gxa[i] * gyz, q[cslot][j][i], vn * out_va);
           }
         }
         if constexpr (S == kF32) {
@@ -960,19 +1096,13 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
           for (int i = 0; i < VEC; ++i) outv[j][i] = v[i];
         } else {
-          float sa[VEC], sv[VEC];
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) {
-            sa[i] = v[i] * s_next;
-            sv[i] = vv[i] * sv_next;
-          }
-          const Words<NA> ra = row_put<S, VEC>(sa), rv = row_put<S, VEC>(sv);
+          const Words<NA> ra = row_put<S, VEC>(v), rv = row_put<S, VEC>(vv);
           st_words<NA, NTP>(ra, rO, vrow[j], sz0);
           st_words<NA, NTP>(rv, rVo, vrow[j], sz0);
 #pragma unroll
-          for (int k = 0; k < Words<NA>::N; ++k) {
-            amax_bits = __builtin_elementwise_max(amax_bits, __builtin_bit_cast(u16x2, ra.w[k] & 0x7fff7fffu));
-            amaxv_bits = __builtin_elementwise_max(amaxv_bits, __builtin_bit_cast(u16x2, rv.w[k] & 0x7fff7fffu));
+          for (int i = 0; i < VEC; ++i) {
+            amax_loc = fmaxf(amax_loc, fabsf(v[i]));
+            amaxv_loc = fmaxf(amaxv_loc, fabsf(vv[i]));
           }
           rkeep[S != kF32 ? j : 0] = ra;
         }
@@ -1008,8 +1138,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   }
 
   if (S != kF32) {  // one order-independent atomic per workgroup and field
-    amax_loc = row_get<S>(Words<2>{{static_cast<uint32_t>(amax_bits.x > amax_bits.y ? amax_bits.x : amax_bits.y)}}, 0);
-    amaxv_loc = row_get<S>(Words<2>{{static_cast<uint32_t>(amaxv_bits.x > amaxv_bits.y ? amaxv_bits.x : amaxv_bits.y)}}, 0);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
       amax_loc = fmaxf(amax_loc, __shfl_xor(amax_loc, off, 64));
@@ -1027,8 +1155,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
         mx = fmaxf(mx, red[k]);
         mv = fmaxf(mv, redv[k]);
       }
-      atomicMax(&a.st->amax[(n + 1) & 3], __float_as_uint(mx));
-      atomicMax(&a.st->amax_v[(n + 1) & 3], __float_as_uint(mv));
+      uint32_t *slot = a.slots + max_slot(n + 1, logical & (kMaxSlots - 1));
+      atomicMax(slot, __float_as_uint(Codec<S>::dec(Codec<S>::enc(mx))));
+      atomicMax(slot + 1, __float_as_uint(Codec<S>::dec(Codec<S>::enc(mv))));
     }
   }
 }

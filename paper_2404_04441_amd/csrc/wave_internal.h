@@ -17,11 +17,19 @@ constexpr int kMaxPD = 3;    // most z-planes of loads a step kernel keeps in fl
 // and its z halo run into them instead of past the allocation.
 constexpr int kPadZ = 2 * kRadius + kMaxPD + kRadius;
 
+// 16-bit storage: a step's workgroups spread their maxima over this many
+// slots per level, each a 128-byte line holding A's and V's.  16 of them:
+// 1000 workgroups then queue 63 deep on a line (0.7 us) instead of 2000 deep,
+// and the next step still reads them with one load per wavefront.
+constexpr int kMaxSlots = 16, kMaxSlotStride = 32;
+constexpr size_t kMaxSlotBytes = size_t(4) * kMaxSlots * kMaxSlotStride * 4;  // four levels
+
 // Device-resident per-run state, at the head of the workspace.
 struct StepState {
   int32_t n;            // absolute index of the next step (advanced by bump kernels)
   int32_t pad0[3];
-  uint32_t amax[4];     // 16-bit storage, slot k%4: max |stored raw value| of A^k (float bits)
+  uint32_t amax[4];     // 16-bit storage, slot k%4: max |stored raw value| of A^k (float bits; of the
+                        // level after a run of steps, the others only in the per-level slots)
   int32_t exps[4];      // slot k%4: scale exponent of A^k (stored = A * 2^e)
   uint32_t flags;       // WAVE_FLAG_* bits
   uint32_t vmin_bits;   // velocity range from the create pass (float bits)
@@ -116,6 +124,7 @@ struct StepArgs {
   // 16-bit storage only: m holds 16-bit codes u, m = m_lo + u * m_step
   int m16;
   float m_lo, m_step;
+  uint32_t *slots;    // 16-bit storage: per-level maxima (max_slot in the step kernels)
 };
 
 struct Variant {
@@ -145,12 +154,13 @@ hipError_t launch_init_m(const float *vel, float *m, size_t n, float dt, StepSta
 // codes u = round(((v dt)^2 - m_lo) / m_step), clamped to [0, 65535] (0 when m_step == 0)
 hipError_t launch_encode_m16(const float *vel, uint16_t *codes, size_t n, float dt, float m_lo, float m_step,
                              hipStream_t s);
-hipError_t launch_bump(StepState *st, int count, hipStream_t s);
+// st->n += count; with slots (16-bit storage) also the new level's maxima from them into st
+hipError_t launch_bump(StepState *st, int count, const uint32_t *slots, hipStream_t s);
 // 16-bit storage: encode float32 x into a stored field of step n (dst; the
 // V field with v_field) at the exponent the bound rule gives for max |x|,
 // and set that field's exponent and stored-maximum records for step n
-hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, bool v_field,
-                              hipStream_t s);
+hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, uint32_t *slots,
+                              bool v_field, hipStream_t s);
 hipError_t launch_decode(int storage, const void *field, float *out, size_t n, const StepState *st,
                          int slot_from_n_offset, bool v_field, hipStream_t s);
 hipError_t launch_decode_prev(int storage, const void *a, const void *v, float *out, const float *gx,
@@ -162,7 +172,7 @@ hipError_t launch_gather(int storage, const void *field, const int64_t *rec_lin,
 // in receiver order): nodes u < nnode, their receivers ord[off[u] .. off[u+1])
 hipError_t launch_scatter(float *field, const int64_t *node, const int32_t *off, const int32_t *ord, int nnode,
                           int nrec, const float *m, const float *gnode, const float *resid, int row, hipStream_t s);
-hipError_t launch_reset_state(StepState *st, hipStream_t s);
+hipError_t launch_reset_state(StepState *st, uint32_t *slots, hipStream_t s);  // slots: null for float32
 hipError_t launch_set_n(StepState *st, int n, hipStream_t s);
 hipError_t launch_check_finite(int storage, const void *field, size_t n, StepState *st, hipStream_t s);
 hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, size_t n,

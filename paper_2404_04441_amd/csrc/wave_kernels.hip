@@ -376,8 +376,9 @@ __global__ void encode_m16_kernel(const float *__restrict__ vel, uint16_t *__res
 // values are non-negative, so unsigned order is float order), the encode
 // uses the exponent the step kernel's rule gives for that bound, and the
 // record then takes the largest stored magnitude, with the exponent beside it.
-__global__ void scale_record_clear_kernel(StepState *st, int v_field) {
+__global__ void scale_record_clear_kernel(StepState *st, uint32_t *slots, int v_field) {
   if (threadIdx.x == 0) (v_field ? st->amax_v : st->amax)[st->n & 3] = 0u;
+  if (threadIdx.x < kMaxSlots) slots[max_slot(st->n, threadIdx.x) + v_field] = 0u;
 }
 
 __global__ void __launch_bounds__(256) absmax_kernel(const float *__restrict__ x, size_t n, StepState *st,
@@ -417,16 +418,27 @@ __global__ void scale_record_kernel(StepState *st, int v_field) {
   (v_field ? st->exps_v : st->exps)[slot] = e;
 }
 
-__global__ void bump_kernel(StepState *st, int count) {
-  if (threadIdx.x == 0) st->n += count;
+__global__ void bump_kernel(StepState *st, int count, const uint32_t *slots) {  // one wavefront
+  const int n = st->n + count;
+  if (slots) {
+    uint32_t ma = st->amax[n & 3], mv = st->amax_v[n & 3];
+    max_slots(slots, n, ma, mv);
+    if (threadIdx.x == 0) {
+      st->amax[n & 3] = ma;
+      st->amax_v[n & 3] = mv;
+    }
+  }
+  if (threadIdx.x == 0) st->n = n;
 }
 
 __global__ void set_n_kernel(StepState *st, int n) {
   if (threadIdx.x == 0) st->n = n;
 }
 
-__global__ void reset_state_kernel(StepState *st) {
+__global__ void reset_state_kernel(StepState *st, uint32_t *slots) {
   const int t = threadIdx.x;
+  if (slots)
+    for (int k = t; k < 4 * kMaxSlots * 2; k += 64) slots[max_slot(k >> 5, (k >> 1) & 15) + (k & 1)] = 0u;
   if (t == 0) {
     st->n = 0;
     st->flags = 0u;
@@ -590,12 +602,12 @@ hipError_t launch_encode_m16(const float *vel, uint16_t *codes, size_t n, float 
   return hipGetLastError();
 }
 
-hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, bool v_field,
-                              hipStream_t s) {
+hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, uint32_t *slots,
+                              bool v_field, hipStream_t s) {
   if (storage != kF16 && storage != kBF16) return hipErrorInvalidValue;
   const int vf = v_field ? 1 : 0;
   const dim3 g(grid_for(n, 256)), b(256);
-  hipLaunchKernelGGL(scale_record_clear_kernel, dim3(1), dim3(64), 0, s, st, vf);
+  hipLaunchKernelGGL(scale_record_clear_kernel, dim3(1), dim3(64), 0, s, st, slots, vf);
   hipLaunchKernelGGL(absmax_kernel, g, b, 0, s, x, n, st, vf);
   if (storage == kF16) {
     hipLaunchKernelGGL(encode_field_kernel<kF16>, g, b, 0, s, x, static_cast<uint16_t *>(dst), n, st, vf);
@@ -607,8 +619,8 @@ hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n,
   return hipGetLastError();
 }
 
-hipError_t launch_bump(StepState *st, int count, hipStream_t s) {
-  hipLaunchKernelGGL(bump_kernel, dim3(1), dim3(64), 0, s, st, count);
+hipError_t launch_bump(StepState *st, int count, const uint32_t *slots, hipStream_t s) {
+  hipLaunchKernelGGL(bump_kernel, dim3(1), dim3(64), 0, s, st, count, slots);
   return hipGetLastError();
 }
 
@@ -628,8 +640,8 @@ hipError_t launch_noise(int storage, void *field, size_t n, uint32_t seed, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_reset_state(StepState *st, hipStream_t s) {
-  hipLaunchKernelGGL(reset_state_kernel, dim3(1), dim3(64), 0, s, st);
+hipError_t launch_reset_state(StepState *st, uint32_t *slots, hipStream_t s) {
+  hipLaunchKernelGGL(reset_state_kernel, dim3(1), dim3(64), 0, s, st, slots);
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ constexpr double kD1[4] = {4.0 / 5.0, -1.0 / 5.0, 4.0 / 105.0, -1.0 / 280.0};
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct Layout {
-  size_t st, gx, gy, gz, rz, rec_lin, rec_node, rec_off, rec_ord, grec, m, fa, fb, fc, fd, fv, ckpt, seg, mua, mub, img;
+  size_t st, slots, gx, gy, gz, rz, rec_lin, rec_node, rec_off, rec_ord, grec, m, fa, fb, fc, fd, fv, ckpt, seg, mua, mub, img;
   size_t cpml_ab, cpml_slab[3], total;  // CPML: a/b tables, psi+zeta slab pair per axis
   int K, nck;
 };
@@ -116,6 +116,7 @@ int plan(const wave_params *p, Layout *L) {
     return at;
   };
   L->st = take(sizeof(StepState));
+  L->slots = p->storage == WAVE_F32 ? off : take(kMaxSlotBytes);
   L->gx = take(4 * static_cast<size_t>(p->nx));
   L->gy = take(4 * static_cast<size_t>(p->ny));
   L->gz = take(4 * (static_cast<size_t>(p->nz) + kPadZ));
@@ -317,6 +318,7 @@ struct wave_ctx {
   char *ws = nullptr;
   Layout L{};
   StepState *st = nullptr;
+  uint32_t *slots = nullptr;  // 16-bit storage: the per-level maxima
   float *gx = nullptr, *gy = nullptr, *gz = nullptr, *m = nullptr, *grec = nullptr;  // grec: per receiver node
   int32_t *rz = nullptr;
   bool cpml = false;
@@ -393,6 +395,7 @@ StepArgs base_args(const wave_ctx *w, const Tiling &t) {
   a.m16 = w->m16 ? 1 : 0;
   a.m_lo = w->m_lo;
   a.m_step = w->m_step;
+  a.slots = w->slots;
   return a;
 }
 
@@ -449,7 +452,7 @@ int enqueue_steps(wave_ctx *w, int count, const float *wavelet, float *traces, b
       if (rc) return rc;
     }
   }
-  return hip_rc(launch_bump(w->st, count, w->stream));
+  return hip_rc(launch_bump(w->st, count, w->slots, w->stream));
 }
 
 // Replay `reps` times a captured graph of graph_steps steps (even count, so
@@ -524,7 +527,7 @@ int do_reset(wave_ctx *w) {
   if (!rc && w->fc) rc = hip_rc(launch_fill_zero(w->fc, es * w->Np, w->stream));
   if (!rc && w->fd) rc = hip_rc(launch_fill_zero(w->fd, es * w->Np, w->stream));
   if (!rc && w->fv) rc = hip_rc(launch_fill_zero(w->fv, es * w->Np, w->stream));
-  if (!rc) rc = hip_rc(launch_reset_state(w->st, w->stream));
+  if (!rc) rc = hip_rc(launch_reset_state(w->st, w->slots, w->stream));
   if (!rc) w->n = 0;
   return rc;
 }
@@ -882,6 +885,7 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   w->ws = static_cast<char *>(ws_dev);
   w->L = L;
   w->st = reinterpret_cast<StepState *>(w->ws + L.st);
+  if (p->storage != WAVE_F32) w->slots = reinterpret_cast<uint32_t *>(w->ws + L.slots);
   w->gx = reinterpret_cast<float *>(w->ws + L.gx);
   w->gy = reinterpret_cast<float *>(w->ws + L.gy);
   w->gz = reinterpret_cast<float *>(w->ws + L.gz);
@@ -1178,7 +1182,7 @@ int wave_write_field(wave_t w, int32_t which, const float *in_dev) {
   }
   if (which != 0 && which != 2) return WAVE_EINVAL;  // 16-bit storage keeps A^n and V^n
   return hip_rc(launch_encode_field(w->p.storage, in_dev, which == 0 ? w->field(w->n) : w->fv, w->N, w->st,
-                                    which == 2, w->stream));
+                                    w->slots, which == 2, w->stream));
 }
 
 // Snapshot layout: 256-B header | step state | A fields 0 and 1 | V (16-bit)
@@ -1262,6 +1266,8 @@ int wave_load_state(wave_t w, const void *src_dev) {
       h.pad[0] != w->p.time_block)
     return WAVE_EINVAL;
   rc = hip_rc(hipMemcpyAsync(w->st, src + 256, sizeof(StepState), hipMemcpyDeviceToDevice, w->stream));
+  // the snapshot's state holds the maxima of its level; the slots start empty
+  if (!rc && w->slots) rc = hip_rc(launch_fill_zero(w->slots, kMaxSlotBytes, w->stream));
   size_t off = 512;
   void *fields[3] = {w->fa, w->fb, w->fv};
   if (w->p.time_block == 2) {
