@@ -96,189 +96,285 @@ __device__ __forceinline__ float cur_k(const float *cur, unsigned o, const AxisA
   return (j < 0 || j >= A.n) ? 0.f : cur[static_cast<int>(o) + k * static_cast<int>(A.stride)];
 }
 
-// Row r of the shell's first two parts (the rows of its z-layer planes, then
-// its y-layer rows in the remaining planes) as (y, z).
-__device__ __forceinline__ void shell_row(const Shell &S, unsigned r, int &y, int &z) {
-  const unsigned r0 = S.cz * S.ny;
-  if (r < r0) {
-    const unsigned k = r / S.ny;
-    y = static_cast<int>(r - k * S.ny);
-    z = static_cast<int>(k < S.E ? k : S.nz - S.cz + k);
-    return;
+// A lane's kRowNodes nodes of a row: kRowNodes / VEC vectors of VEC nodes, 64
+// vectors apart (whole rows need nx % VEC == 0; narrower vectors, more of
+// them).
+constexpr int kRowNodes = 4;
+template <int VEC> struct Row {
+  Words<VEC * 4> v[kRowNodes / VEC];
+  __device__ float at(int e) const { return __uint_as_float(v[e / VEC].w[e % VEC]); }
+};
+template <int VEC> __device__ __forceinline__ Row<VEC> ld_row(rsrc_t r, uint32_t xo) {
+  Row<VEC> out;
+#pragma unroll
+  for (int k = 0; k < kRowNodes / VEC; ++k) out.v[k] = ld_words<VEC * 4, 0>(r, xo + k * (256u * VEC), 0u);
+  return out;
+}
+template <int VEC> __device__ __forceinline__ void st_row(const float *v, rsrc_t r, uint32_t xo) {
+#pragma unroll
+  for (int k = 0; k < kRowNodes / VEC; ++k)
+    st_words<VEC * 4, 0>(row_put<kF32, VEC>(v + k * VEC), r, xo + k * (256u * VEC), 0u);
+}
+
+// The row kernels' order of work.  A wavefront owns 256 consecutive nodes
+// of one row of the shell, so that the row, its layers and its neighbour rows
+// are scalars: one resource per neighbour row, without records where the row
+// lies outside (its loads return zero), and no address or mask arithmetic per
+// lane.  With a thread per vector of the whole shell these kernels were bound
+// by that arithmetic, five integer divisions per thread among it.  A row's
+// neighbours along z (z layers) or y (y layers) are other rows of the shell:
+// each XCD, with an L2 of its own, takes a contiguous run of rows (hardware
+// dispatches workgroups round-robin over the 8 XCDs), and the z-layer planes
+// are visited in bundles of kBundle rows, all planes of a bundle and then the
+// next bundle, so that the rows in flight on an XCD hold whole z lines.
+// Every XCD takes an eighth of each part (z-layer rows, y-layer rows, nodes of
+// the x slabs), so that they end together.  Measured at 512^3, W = 20: the psi
+// update (before: a row kernel of 95 us and a column kernel of 37 us) 83 us,
+// 0.44 GB; the correction reads 0.45 instead of 0.80 GB and takes the same
+// 150 us; at 401x333x301, where a lane held one node, a whole step went from
+// 398 to 362 us.  Bundles of 4, 32 and 64 rows differ by 1%.
+constexpr unsigned kBundle = 32;
+
+// n / d for n < 2^31: (n + mulhi(n, m)) >> s.
+struct FastDiv {
+  unsigned d, m, s;
+  explicit FastDiv(unsigned div = 1) : d(div), s(0) {
+    while ((1ull << s) < d) ++s;
+    m = static_cast<unsigned>((((1ull << s) - d) << 32) / d + 1);
   }
-  r -= r0;
-  const unsigned k = r / S.cy, j = r - k * S.cy;
-  z = static_cast<int>(S.E + k);
-  y = static_cast<int>(j < S.E ? j : S.ny - S.cy + j);
+  __device__ unsigned operator()(unsigned n) const { return (__umulhi(n, m) + n) >> s; }
+};
+
+struct ShellWork {
+  Shell S;
+  unsigned per0, per1, per2;  // workgroups (4 wavefronts) of each part per XCD
+  unsigned rows0, rows1;      // rows of the first two parts
+  unsigned nslab;             // vectors of the x slabs
+  FastDiv seg, bundle, last, cy, w2v;  // wavefronts per row; rows per bundle and in the last one; rows per y-layer plane; vectors per x-slab row
+  ShellWork(const CpmlArgs &c, int E, int vx) : S(E, c.nx, c.ny, c.nz) {
+    const unsigned nseg = (static_cast<unsigned>(c.nx) + 64 * kRowNodes - 1) / (64 * kRowNodes);
+    seg = FastDiv(nseg);
+    bundle = FastDiv(S.cz * kBundle);
+    const unsigned tail = S.ny % kBundle;
+    last = FastDiv(tail ? tail : kBundle);
+    cy = FastDiv(S.cy);
+    rows0 = S.cz * S.ny;
+    rows1 = S.mz * S.cy;
+    w2v = FastDiv(vx ? 2u * c.W / vx : 1u);
+    nslab = vx ? static_cast<unsigned>(c.nz) * c.ny * (2u * c.W / vx) : 0u;
+    auto share = [](size_t waves) { return static_cast<unsigned>((waves + 31) / 32); };  // 4 wavefronts, 8 XCDs
+    per0 = share(size_t(rows0) * nseg);
+    per1 = share(size_t(rows1) * nseg);
+    per2 = share((size_t(nslab) + 63) / 64);
+  }
+  unsigned grid() const { return 8 * (per0 + per1 + per2); }
+};
+
+// This wavefront's part, its index there and, in the row parts, its row: part
+// 0 (the rows of the z-layer planes, by bundles) or 1 (the y-layer rows of the
+// remaining planes), the segment of the row; part 3 past the end.  Scalars,
+// said so to the compiler: a resource it takes for divergent costs a loop
+// over the lanes at each load.
+struct ShellAt {
+  unsigned part, wave, seg;
+  int y, z;
+};
+
+__device__ __forceinline__ ShellAt shell_at(const ShellWork &P) {
+  const Shell &S = P.S;
+  const unsigned xcd = blockIdx.x & 7u, j = blockIdx.x >> 3;
+  const unsigned w = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
+  ShellAt at{};
+  unsigned y = 0, z = 0;
+  if (j < P.per0) {
+    at.wave = (xcd * P.per0 + j) * 4u + w;
+    const unsigned r = P.seg(at.wave);
+    at.seg = at.wave - r * P.seg.d;
+    const unsigned b = P.bundle(r), rem = r - b * P.bundle.d;
+    const bool whole = S.ny - b * kBundle >= kBundle;
+    const unsigned k = whole ? rem / kBundle : P.last(rem);
+    y = b * kBundle + (rem - k * (whole ? kBundle : P.last.d));
+    z = k < S.E ? k : S.nz - S.cz + k;
+    at.part = r < P.rows0 ? 0u : 3u;
+  } else if (j < P.per0 + P.per1) {
+    at.wave = (xcd * P.per1 + j - P.per0) * 4u + w;
+    const unsigned r = P.seg(at.wave);
+    at.seg = at.wave - r * P.seg.d;
+    const unsigned k = P.cy(r), i = r - k * P.cy.d;
+    y = i < S.E ? i : S.ny - S.cy + i;
+    z = S.E + k;
+    at.part = r < P.rows1 ? 1u : 3u;
+  } else {
+    at.wave = (xcd * P.per2 + j - P.per0 - P.per1) * 4u + w;
+    at.part = 2u;
+  }
+  at.part = __builtin_amdgcn_readfirstlane(at.part);
+  at.seg = __builtin_amdgcn_readfirstlane(at.seg);
+  at.y = __builtin_amdgcn_readfirstlane(static_cast<int>(y));
+  at.z = __builtin_amdgcn_readfirstlane(static_cast<int>(z));
+  return at;
+}
+
+// The row of nx floats at p, or nothing (every load from it is zero).
+__device__ __forceinline__ rsrc_t row_at(const float *p, bool in, unsigned nx) {
+  return make_rsrc(p, in ? nx * 4u : 0u);
 }
 
 template <int VEC> __device__ __forceinline__ void vload(const float *p, float *v) { lds_get<VEC>(p, v); }
 template <int VEC> __device__ __forceinline__ void vstore(float *p, const float *v) { lds_put<VEC>(p, v); }
 
-// psi_a update over the rows of the first two parts of the W-node shell, VEC
-// consecutive x nodes per thread (nx % VEC == 0): the y and z axes where the
-// row lies in their layers (whole rows), the x axis for the nodes of the row
-// in the x layers.
-template <int VEC>
-__global__ void __launch_bounds__(256) cpml_psi_rows_kernel(CpmlArgs c, const float *__restrict__ cur) {
-  const Shell S(c.W, c.nx, c.ny, c.nz);
-  const unsigned qx = static_cast<unsigned>(c.nx) / VEC;
-  const unsigned t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= (S.cz * S.ny + S.mz * S.cy) * qx) return;
-  const unsigned r = t / qx;
-  const int x = static_cast<int>((t - r * qx) * VEC);
-  int y, z;
-  shell_row(S, r, y, z);
+// psi_x over vector t of the x slabs (VX consecutive nodes; W and nx
+// divisible by VX): contiguous in the slab array, the window of A^n in
+// vectors of VX.
+template <int VX>
+__device__ __forceinline__ void psi_x_update(const CpmlArgs &c, const ShellWork &P, const float *__restrict__ cur,
+                                             unsigned t) {
+  if (t >= P.nslab) return;
+  const unsigned row = P.w2v(t);  // row z ny + y of the grid
+  const int s = static_cast<int>(t - row * P.w2v.d) * VX, nx = c.nx;
+  const int x = s < c.W ? s : nx - 2 * c.W + s;
+  const float *u = cur + static_cast<size_t>(row) * static_cast<unsigned>(nx);
+  constexpr int NV = (VX + 2 * R + VX - 1) / VX;  // vectors of the window x-R .. x+VX+R-1
+  float win[NV * VX];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int xk = x - R + k * VX;
+#pragma unroll
+    for (int e = 0; e < VX; ++e) win[k * VX + e] = 0.f;
+    if (xk >= 0 && xk < nx) vload<VX>(u + xk, win + k * VX);
+  }
+  float *ps = c.psi[0] + static_cast<size_t>(t) * VX;
+  float pv[VX];
+  vload<VX>(ps, pv);
+#pragma unroll
+  for (int e = 0; e < VX; ++e) {
+    float d = 0.f;
+#pragma unroll
+    for (int m = 1; m <= R; ++m) d = fmaf(c.d1w[0][m - 1], win[R + e + m] - win[R + e - m], d);
+    pv[e] = fmaf(c.cb[0][x + e], pv[e], c.ca[0][x + e] * d);
+  }
+  vstore<VX>(ps, pv);
+}
+
+// psi_a update over the W-node layers: along y and z by rows (VEC consecutive
+// x nodes per lane, nx % VEC == 0), along x over the slabs.
+template <int VEC, int VX>
+__global__ void __launch_bounds__(256) cpml_psi_kernel(CpmlArgs c, ShellWork P, const float *__restrict__ cur) {
+  const ShellAt at = shell_at(P);
+  const unsigned lane = threadIdx.x & 63u, seg = at.seg;
+  const int y = at.y, z = at.z;
+  if (at.part == 2) psi_x_update<VX>(c, P, cur, at.wave * 64u + lane);
+  if (at.part >= 2) return;
   const unsigned nx = c.nx, ny = c.ny, W2 = 2u * c.W;
-  const unsigned o = (static_cast<unsigned>(z) * ny + y) * nx + x;
+  const uint32_t xo = seg * (64u * kRowNodes * 4u) + lane * (VEC * 4u);  // past the row's end: loads zero, stores nothing
+  const float *row = cur + (static_cast<size_t>(z) * ny + static_cast<unsigned>(y)) * nx;
 #pragma unroll
   for (int a = 1; a < 3; ++a) {
     const int i = a == 1 ? y : z, n = a == 1 ? c.ny : c.nz;
     const int s = slab_index(i, n, c.W);
     if (s < 0) continue;
-    const unsigned stride = a == 1 ? nx : nx * ny;
-    float d[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) d[e] = 0.f;
+    const size_t stride = a == 1 ? nx : static_cast<size_t>(nx) * ny;
+    Row<VEC> up[R], dn[R];
 #pragma unroll
     for (int m = 1; m <= R; ++m) {
-      float up[VEC], dn[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) up[e] = dn[e] = 0.f;
-      if (i + m < n) vload<VEC>(cur + o + m * stride, up);
-      if (i - m >= 0) vload<VEC>(cur + o - m * stride, dn);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) d[e] = fmaf(c.d1w[a][m - 1], up[e] - dn[e], d[e]);
+      up[m - 1] = ld_row<VEC>(row_at(row + m * stride, i + m < n, nx), xo);
+      dn[m - 1] = ld_row<VEC>(row_at(row - m * stride, i - m >= 0, nx), xo);
     }
-    float *ps = c.psi[a] + (a == 1 ? (static_cast<unsigned>(z) * W2 + s) * nx : (s * ny + static_cast<unsigned>(y)) * nx) + x;
-    float pv[VEC];
-    vload<VEC>(ps, pv);
+    const rsrc_t rp = row_at(c.psi[a] + (a == 1 ? static_cast<size_t>(z) * W2 + s : static_cast<size_t>(s) * ny + y) * nx,
+                             true, nx);
+    const Row<VEC> pv = ld_row<VEC>(rp, xo);
+    const float ca = c.ca[a][i], cb = c.cb[a][i];
+    float out[kRowNodes];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) pv[e] = fmaf(c.cb[a][i], pv[e], c.ca[a][i] * d[e]);
-    vstore<VEC>(ps, pv);
-  }
-  if (x < c.W || x + VEC - 1 >= c.nx - c.W) {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int xe = x + e;
-      const int s = slab_index(xe, c.nx, c.W);
-      if (s < 0) continue;
+    for (int e = 0; e < kRowNodes; ++e) {
       float d = 0.f;
 #pragma unroll
-      for (int m = 1; m <= R; ++m) {
-        const float up = xe + m < c.nx ? cur[o + e + m] : 0.f;
-        const float dn = xe - m >= 0 ? cur[o + e - m] : 0.f;
-        d = fmaf(c.d1w[0][m - 1], up - dn, d);
-      }
-      float *ps = c.psi[0] + (static_cast<unsigned>(z) * ny + y) * W2 + s;
-      *ps = fmaf(c.cb[0][xe], *ps, c.ca[0][xe] * d);
+      for (int m = 1; m <= R; ++m)
+        d = fmaf(c.d1w[a][m - 1], up[m - 1].at(e) - dn[m - 1].at(e), d);
+      out[e] = fmaf(cb, pv.at(e), ca * d);
     }
-  }
-}
-
-// One thread per node of the W-node shell from node t0 on (the x-layer
-// columns of its third part, after cpml_psi_rows_kernel; or all of it).
-__global__ void __launch_bounds__(256) cpml_psi_kernel(CpmlArgs c, const float *__restrict__ cur, unsigned t0) {
-  const Shell S(c.W, c.nx, c.ny, c.nz);
-  const unsigned t = t0 + blockIdx.x * 256u + threadIdx.x;
-  if (t >= S.count()) return;
-  int x, y, z;
-  S.node(t, x, y, z);
-  const unsigned o = (static_cast<unsigned>(z) * c.ny + y) * c.nx + x;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const AxisAt A = axis_at(c, a, x, y, z);
-    const int s = slab_index(A.i, A.n, c.W);
-    if (s < 0) continue;
-    float d = 0.f;
-#pragma unroll
-    for (int m = 1; m <= R; ++m) d = fmaf(c.d1w[a][m - 1], cur_k(cur, o, A, m) - cur_k(cur, o, A, -m), d);
-    float *ps = c.psi[a] + A.slab_rest + static_cast<unsigned>(s) * A.slab_stride;
-    *ps = fmaf(c.cb[a][A.i], *ps, c.ca[a][A.i] * d);
+    st_row<VEC>(out, rp, xo);
   }
 }
 
 // The y and z terms after the step with the x part fused in:
 // out += m * sum_{a = y, z} (D1_a psi_a + zeta_a), zeta_a updated, over the
 // rows of the first two parts of the (W + R)-node shell (the other nodes get
-// no y or z term), VEC consecutive x nodes per thread (nx % VEC == 0).  Per
+// no y or z term), VEC consecutive x nodes per lane (nx % VEC == 0).  Per
 // node the same operations as cpml_fix_kernel with a0 = 1.
 template <int VEC>
-__global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, const float *__restrict__ cur,
+__global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, ShellWork P, const float *__restrict__ cur,
                                                           const float *__restrict__ m, float *out) {
-  const Shell S(c.W + R, c.nx, c.ny, c.nz);
-  const unsigned qx = static_cast<unsigned>(c.nx) / VEC;
-  const unsigned t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= (S.cz * S.ny + S.mz * S.cy) * qx) return;
-  const unsigned r = t / qx;
-  const int x = static_cast<int>((t - r * qx) * VEC);
-  int y, z;
-  shell_row(S, r, y, z);
+  const ShellAt at = shell_at(P);
+  if (at.part >= 2) return;
+  const unsigned seg = at.seg;
+  const int y = at.y, z = at.z;
   const unsigned nx = c.nx, ny = c.ny, W2 = 2u * c.W;
-  const unsigned o = (static_cast<unsigned>(z) * ny + y) * nx + x;
-  float extra[VEC];
+  const uint32_t xo = seg * (64u * kRowNodes * 4u) + (threadIdx.x & 63u) * (VEC * 4u);
+  const size_t o = (static_cast<size_t>(z) * ny + static_cast<unsigned>(y)) * nx;
+  const float *row = cur + o;
+  const rsrc_t ro = row_at(out + o, true, nx);
+  const Row<VEC> mv = ld_row<VEC>(row_at(m + o, true, nx), xo);
+  const Row<VEC> ov = ld_row<VEC>(ro, xo);
+  const Row<VEC> cc = ld_row<VEC>(row_at(row, true, nx), xo);
+  float extra[kRowNodes];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) extra[e] = 0.f;
+  for (int e = 0; e < kRowNodes; ++e) extra[e] = 0.f;
 #pragma unroll
   for (int a = 1; a < 3; ++a) {
     const int i = a == 1 ? y : z, n = a == 1 ? c.ny : c.nz;
     if (i >= c.W + R && i < n - c.W - R) continue;  // psi_a and zeta_a vanish this far in
-    const unsigned stride = a == 1 ? nx : nx * ny;
-    // slab element of slab index s: y: (z, s, x), z: (s, y, x)
+    const size_t stride = a == 1 ? nx : static_cast<size_t>(nx) * ny;
+    // slab row of slab index s: y: (z, s), z: (s, y)
     auto slab = [&](int sidx) {
-      return a == 1 ? (static_cast<unsigned>(z) * W2 + static_cast<unsigned>(sidx)) * nx + x
-                    : (static_cast<unsigned>(sidx) * ny + static_cast<unsigned>(y)) * nx + x;
+      return (a == 1 ? static_cast<size_t>(z) * W2 + sidx : static_cast<size_t>(sidx) * ny + static_cast<unsigned>(y)) * nx;
     };
-    float dpsi[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) dpsi[e] = 0.f;
+    const int s = slab_index(i, n, c.W);
+    Row<VEC> pp[R], pm[R], up[R], dn[R];
 #pragma unroll
     for (int k = 1; k <= R; ++k) {
-      float pp[VEC], pm[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) pp[e] = pm[e] = 0.f;
       const int sp = slab_index(i + k, n, c.W), sm = slab_index(i - k, n, c.W);
-      if (sp >= 0) vload<VEC>(c.psi[a] + slab(sp), pp);
-      if (sm >= 0) vload<VEC>(c.psi[a] + slab(sm), pm);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) dpsi[e] = fmaf(c.d1w[a][k - 1], pp[e] - pm[e], dpsi[e]);
+      pp[k - 1] = ld_row<VEC>(row_at(c.psi[a] + slab(sp < 0 ? 0 : sp), sp >= 0, nx), xo);
+      pm[k - 1] = ld_row<VEC>(row_at(c.psi[a] + slab(sm < 0 ? 0 : sm), sm >= 0, nx), xo);
     }
-    const int s = slab_index(i, n, c.W);
-    if (s < 0) {
+    if (s < 0) {  // beyond the layer: D1 psi alone
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) extra[e] += dpsi[e];
+      for (int e = 0; e < kRowNodes; ++e) {
+        float dpsi = 0.f;
+#pragma unroll
+        for (int k = 1; k <= R; ++k)
+          dpsi = fmaf(c.d1w[a][k - 1], pp[k - 1].at(e) - pm[k - 1].at(e), dpsi);
+        extra[e] += dpsi;
+      }
       continue;
     }
-    float cc[VEC], d2[VEC];
-    vload<VEC>(cur + o, cc);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) d2[e] = 0.f;
-#pragma unroll
-    for (int k = 1; k <= R; ++k) {  // second differences from the centre (no large centre term)
-      float up[VEC], dn[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) up[e] = dn[e] = 0.f;
-      if (i + k < n) vload<VEC>(cur + o + k * stride, up);
-      if (i - k >= 0) vload<VEC>(cur + o - k * stride, dn);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) d2[e] = fmaf(c.d2w[a][k], (up[e] - cc[e]) + (dn[e] - cc[e]), d2[e]);
+    for (int k = 1; k <= R; ++k) {
+      up[k - 1] = ld_row<VEC>(row_at(row + k * stride, i + k < n, nx), xo);
+      dn[k - 1] = ld_row<VEC>(row_at(row - k * stride, i - k >= 0, nx), xo);
     }
-    float *ze = c.zeta[a] + slab(s);
-    float zv[VEC];
-    vload<VEC>(ze, zv);
+    const rsrc_t rz = row_at(c.zeta[a] + slab(s), true, nx);
+    const Row<VEC> zv = ld_row<VEC>(rz, xo);
+    const float ca = c.ca[a][i], cb = c.cb[a][i];
+    float zn[kRowNodes];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      zv[e] = fmaf(c.cb[a][i], zv[e], c.ca[a][i] * (d2[e] + dpsi[e]));
-      extra[e] += dpsi[e] + zv[e];
+    for (int e = 0; e < kRowNodes; ++e) {
+      const float u = cc.at(e);
+      float dpsi = 0.f, d2 = 0.f;  // d2: second differences from the centre (no large centre term)
+#pragma unroll
+      for (int k = 1; k <= R; ++k) {
+        dpsi = fmaf(c.d1w[a][k - 1], pp[k - 1].at(e) - pm[k - 1].at(e), dpsi);
+        d2 = fmaf(c.d2w[a][k], (up[k - 1].at(e) - u) + (dn[k - 1].at(e) - u), d2);
+      }
+      zn[e] = fmaf(cb, zv.at(e), ca * (d2 + dpsi));
+      extra[e] += dpsi + zn[e];
     }
-    vstore<VEC>(ze, zv);
+    st_row<VEC>(zn, rz, xo);
   }
-  float mv[VEC], ov[VEC];
-  vload<VEC>(m + o, mv);
-  vload<VEC>(out + o, ov);
+  float res[kRowNodes];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) ov[e] = fmaf(mv[e], extra[e], ov[e]);
-  vstore<VEC>(out + o, ov);
+  for (int e = 0; e < kRowNodes; ++e) res[e] = fmaf(mv.at(e), extra[e], ov.at(e));
+  st_row<VEC>(res, ro, xo);
 }
 
 // One thread per node within W + R of a face, adding the terms of axes
@@ -713,18 +809,24 @@ hipError_t launch_grad_final(const float *img, const float *m, float dt, float *
   return hipGetLastError();
 }
 
+namespace {
+template <int VEC>
+void launch_psi(int vx, const ShellWork &P, const CpmlArgs &c, const float *cur, hipStream_t s) {
+  const dim3 g(P.grid()), b(256);
+  if (vx == 4) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 4>), g, b, 0, s, c, P, cur);
+  else if (vx == 2) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 2>), g, b, 0, s, c, P, cur);
+  else hipLaunchKernelGGL((cpml_psi_kernel<VEC, 1>), g, b, 0, s, c, P, cur);
+}
+// x nodes per lane: as many of 4, 2, 1 as divide every length given
+int lane_width(int a, int b) { return a % 4 == 0 && b % 4 == 0 ? 4 : (a % 2 == 0 && b % 2 == 0 ? 2 : 1); }
+}  // namespace
+
 hipError_t launch_cpml_psi(const CpmlArgs &c, const float *cur, hipStream_t s) {
-  const Shell S(c.W, c.nx, c.ny, c.nz);
-  const int vec = c.nx % 4 == 0 ? 4 : (c.nx % 2 == 0 ? 2 : 1);
-  const unsigned nrow = (S.cz * S.ny + S.mz * S.cy) * (static_cast<unsigned>(c.nx) / vec);
-  if (nrow > 0) {
-    const dim3 g((nrow + 255) / 256), b(256);
-    if (vec == 4) hipLaunchKernelGGL(cpml_psi_rows_kernel<4>, g, b, 0, s, c, cur);
-    else if (vec == 2) hipLaunchKernelGGL(cpml_psi_rows_kernel<2>, g, b, 0, s, c, cur);
-    else hipLaunchKernelGGL(cpml_psi_rows_kernel<1>, g, b, 0, s, c, cur);
-  }
-  if (S.n2 > 0)
-    hipLaunchKernelGGL(cpml_psi_kernel, dim3((S.n2 + 255) / 256), dim3(256), 0, s, c, cur, S.n0 + S.n1);
+  const int vec = lane_width(c.nx, 4), vx = lane_width(c.nx, c.W);
+  const ShellWork P(c, c.W, vx);
+  if (vec == 4) launch_psi<4>(vx, P, c, cur, s);
+  else if (vec == 2) launch_psi<2>(vx, P, c, cur, s);
+  else launch_psi<1>(vx, P, c, cur, s);
   return hipGetLastError();
 }
 
@@ -732,13 +834,12 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
                            hipStream_t s) {
   const Shell S(c.W + kRadius, c.nx, c.ny, c.nz);
   if (yz_only) {
-    const int vec = c.nx % 4 == 0 ? 4 : (c.nx % 2 == 0 ? 2 : 1);
-    const unsigned n = (S.cz * S.ny + S.mz * S.cy) * (static_cast<unsigned>(c.nx) / vec);
-    if (n == 0) return hipSuccess;
-    const dim3 g((n + 255) / 256), b(256);
-    if (vec == 4) hipLaunchKernelGGL(cpml_fix_yz_kernel<4>, g, b, 0, s, c, cur, m, out);
-    else if (vec == 2) hipLaunchKernelGGL(cpml_fix_yz_kernel<2>, g, b, 0, s, c, cur, m, out);
-    else hipLaunchKernelGGL(cpml_fix_yz_kernel<1>, g, b, 0, s, c, cur, m, out);
+    const int vec = lane_width(c.nx, 4);
+    const ShellWork P(c, c.W + kRadius, 0);
+    const dim3 g(P.grid()), b(256);
+    if (vec == 4) hipLaunchKernelGGL(cpml_fix_yz_kernel<4>, g, b, 0, s, c, P, cur, m, out);
+    else if (vec == 2) hipLaunchKernelGGL(cpml_fix_yz_kernel<2>, g, b, 0, s, c, P, cur, m, out);
+    else hipLaunchKernelGGL(cpml_fix_yz_kernel<1>, g, b, 0, s, c, P, cur, m, out);
     return hipGetLastError();
   }
   const unsigned n = S.count();
