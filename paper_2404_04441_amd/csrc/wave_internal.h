@@ -127,6 +127,13 @@ struct StepArgs {
   uint32_t *slots;    // 16-bit storage: per-level maxima (max_slot in the step kernels)
 };
 
+// The rows of a caller's array (nx nodes each) and the pitch of the
+// workspace's rows.
+struct GridRows {
+  int nx, pitch;
+  size_t rows;  // ny nz
+};
+
 struct Variant {
   int by;   // wavefronts per workgroup
   int ry;   // consecutive rows per wavefront (tile height = by * ry)
@@ -150,21 +157,23 @@ int step_blocks_per_cu(int storage, int variant, bool cpml);
 // Launchers; each returns the hipError_t of the launch.
 hipError_t launch_step(int storage, int variant, bool adjoint, const StepArgs &a, hipStream_t s);
 // m = (v dt)^2 (skipped when m is null) and the velocity range / validity into st
-hipError_t launch_init_m(const float *vel, float *m, size_t n, float dt, StepState *st, hipStream_t s);
+hipError_t launch_init_m(const float *vel, float *m, const GridRows &g, float dt, StepState *st, hipStream_t s);
 // codes u = round(((v dt)^2 - m_lo) / m_step), clamped to [0, 65535] (0 when m_step == 0)
-hipError_t launch_encode_m16(const float *vel, uint16_t *codes, size_t n, float dt, float m_lo, float m_step,
+hipError_t launch_encode_m16(const float *vel, uint16_t *codes, const GridRows &g, float dt, float m_lo, float m_step,
                              hipStream_t s);
 // st->n += count; with slots (16-bit storage) also the new level's maxima from them into st
 hipError_t launch_bump(StepState *st, int count, const uint32_t *slots, hipStream_t s);
 // 16-bit storage: encode float32 x into a stored field of step n (dst; the
 // V field with v_field) at the exponent the bound rule gives for max |x|,
 // and set that field's exponent and stored-maximum records for step n
-hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, uint32_t *slots,
-                              bool v_field, hipStream_t s);
-hipError_t launch_decode(int storage, const void *field, float *out, size_t n, const StepState *st,
+hipError_t launch_encode_field(int storage, const float *x, void *dst, const GridRows &g, StepState *st,
+                              uint32_t *slots, bool v_field, hipStream_t s);
+// float32 field := x
+hipError_t launch_copy_in(const float *x, float *dst, const GridRows &g, hipStream_t s);
+hipError_t launch_decode(int storage, const void *field, float *out, const GridRows &g, const StepState *st,
                          int slot_from_n_offset, bool v_field, hipStream_t s);
 hipError_t launch_decode_prev(int storage, const void *a, const void *v, float *out, const float *gx,
-                              const float *gy, const float *gz, int nx, int ny, int nz, const StepState *st,
+                              const float *gy, const float *gz, const GridRows &g, int ny, const StepState *st,
                               hipStream_t s);
 hipError_t launch_gather(int storage, const void *field, const int64_t *rec_lin, int nrec, float *traces,
                          const StepState *st, int k, hipStream_t s);
@@ -175,7 +184,7 @@ hipError_t launch_scatter(float *field, const int64_t *node, const int32_t *off,
 hipError_t launch_reset_state(StepState *st, uint32_t *slots, hipStream_t s);  // slots: null for float32
 hipError_t launch_set_n(StepState *st, int n, hipStream_t s);
 hipError_t launch_check_finite(int storage, const void *field, size_t n, StepState *st, hipStream_t s);
-hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, size_t n,
+hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, const GridRows &g,
                              hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // n field values (storage type) to time candidate configurations on

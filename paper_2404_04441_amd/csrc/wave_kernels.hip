@@ -6,6 +6,16 @@
 namespace wave {
 namespace {
 
+// n / d for n < 2^31: (n + mulhi(n, m)) >> s.
+struct FastDiv {
+  unsigned d, m, s;
+  explicit FastDiv(unsigned div = 1) : d(div), s(0) {
+    while ((1ull << s) < d) ++s;
+    m = static_cast<unsigned>((((1ull << s) - d) << 32) / d + 1);
+  }
+  __device__ unsigned operator()(unsigned n) const { return (__umulhi(n, m) + n) >> s; }
+};
+
 // ------------------------------------------------------------ CPML boundary
 //
 // The convolutional PML the paper names as its boundary (Sec. II, Sec.
@@ -134,16 +144,6 @@ template <int VEC> __device__ __forceinline__ void st_row(const float *v, rsrc_t
 // 150 us; at 401x333x301, where a lane held one node, a whole step went from
 // 398 to 362 us.  Bundles of 4, 32 and 64 rows differ by 1%.
 constexpr unsigned kBundle = 32;
-
-// n / d for n < 2^31: (n + mulhi(n, m)) >> s.
-struct FastDiv {
-  unsigned d, m, s;
-  explicit FastDiv(unsigned div = 1) : d(div), s(0) {
-    while ((1ull << s) < d) ++s;
-    m = static_cast<unsigned>((((1ull << s) - d) << 32) / d + 1);
-  }
-  __device__ unsigned operator()(unsigned n) const { return (__umulhi(n, m) + n) >> s; }
-};
 
 struct ShellWork {
   Shell S;
@@ -418,54 +418,171 @@ __global__ void __launch_bounds__(256) cpml_fix_kernel(CpmlArgs c, const float *
 
 // ------------------------------------------------------------ utilities
 
-__global__ void init_m_kernel(const float *__restrict__ vel, float *__restrict__ m, size_t n, float dt,
-                              StepState *st) {
+// ------------------------------------------------------------ conversion passes
+//
+// Copies, conversions and reductions between the caller's arrays (rows of nx
+// floats) and the workspace's fields (rows of their pitch): one wavefront per
+// 256 consecutive nodes of a row, in four-node vectors where both sides are
+// aligned for them (arrays without row padding count as one row), else one
+// node per lane and access.  Bound by memory: one 16-byte access per lane and
+// array in many short workgroups, the form that streams fastest here.  Against
+// one node per lane and access in a strided loop, 1024^3 bf16: reading a field
+// 1937 -> 1080 us, its maximum 1165 -> 773 us, encoding it 1509 -> 1105 us.  The
+// set-up of m at 256^3, which queued two atomics per workgroup on one line:
+// 378 -> 34 us.
+struct RowMap {
+  FastDiv seg;       // wavefronts per row
+  unsigned total;    // wavefronts
+  size_t len;        // nodes per row
+  size_t nu, nf;     // row pitch of the caller's array and of the field
+};
+
+template <int V> __device__ __forceinline__ void nt_get(const float *p, float *v) {
+  if constexpr (V == 4) {
+    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+    v[0] = t.x;
+    v[1] = t.y;
+    v[2] = t.z;
+    v[3] = t.w;
+  } else {
+    v[0] = __builtin_nontemporal_load(p);
+  }
+}
+template <int V> __device__ __forceinline__ void nt_put(float *p, const float *v) {
+  if constexpr (V == 4)
+    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(p));
+  else
+    __builtin_nontemporal_store(v[0], p);
+}
+// V stored values of type S at p, decoded (unscaled), and the inverse.
+template <int S, int V> __device__ __forceinline__ void field_get(const typename Codec<S>::raw *p, float *v) {
+  if constexpr (S == kF32) {
+    lds_get<V>(p, v);
+  } else if constexpr (V == 4) {
+    const u32x2 t = *reinterpret_cast<const u32x2 *>(p);
+    const Words<8> w{{t.x, t.y}};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = row_get<S>(w, e);
+  } else {
+    v[0] = Codec<S>::dec(p[0]);
+  }
+}
+template <int S, int V> __device__ __forceinline__ void field_put(typename Codec<S>::raw *p, const float *v) {
+  if constexpr (S == kF32) {
+    lds_put<V>(p, v);
+  } else if constexpr (V == 4) {
+    const Words<8> w = row_put<S, 4>(v);
+    *reinterpret_cast<u32x2 *>(p) = u32x2{w.w[0], w.w[1]};
+  } else {
+    p[0] = Codec<S>::enc(v[0]);
+  }
+}
+
+// Op::run<V>(u, f, row, col): V nodes at index u of the caller's array and f
+// of the field; Op::finish() once per thread.
+template <int V, class Op>
+__global__ void __launch_bounds__(256) rows_kernel(Op op, RowMap map) {
+  const unsigned lane = threadIdx.x & 63u;
+  const unsigned w0 = blockIdx.x * 4u + static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
+  for (unsigned w = w0; w < map.total; w += gridDim.x * 4u) {
+    const unsigned row = map.seg(w);
+    const size_t at = static_cast<size_t>(w - row * map.seg.d) * 256u;
+#pragma unroll
+    for (int k = 0; k < 4 / V; ++k) {
+      const size_t col = at + k * (64u * V) + lane * V;
+      if (col < map.len) op.template run<V>(row * map.nu + col, row * map.nf + col, row, col);
+    }
+  }
+  op.finish();
+}
+
+// lo, hi: smallest and largest of a value per thread over the workgroup;
+// thread 0 gets them.
+__device__ __forceinline__ void block_range(float &lo, float &hi, int &bad) {
   __shared__ float smin[4], smax[4];
   __shared__ int sbad[4];
-  float lo = __builtin_huge_valf(), hi = 0.f;
-  int bad = 0;
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const float v = vel[i];
-    const float t = v * dt;
-    if (m) m[i] = t * t;
-    if (!(v > 0.f) || !(v < __builtin_huge_valf())) bad = 1;
-    lo = fminf(lo, v);
-    hi = fmaxf(hi, v);
-  }
+#pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     lo = fminf(lo, __shfl_xor(lo, off, 64));
     hi = fmaxf(hi, __shfl_xor(hi, off, 64));
     bad |= __shfl_xor(bad, off, 64);
   }
-  const int w = threadIdx.x / 64;
+  const int w = static_cast<int>(threadIdx.x) >> 6;
   if ((threadIdx.x & 63) == 0) {
     smin[w] = lo;
     smax[w] = hi;
     sbad[w] = bad;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < 4; ++k) {
-      lo = fminf(lo, smin[k]);
-      hi = fmaxf(hi, smax[k]);
-      bad |= sbad[k];
-    }
-    if (bad) atomicOr(&st->flags, 2u);
-    if (lo > 0.f) atomicMin(&st->vmin_bits, __float_as_uint(lo));
-    atomicMax(&st->vmax_bits, __float_as_uint(fmaxf(hi, 0.f)));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    lo = fminf(lo, smin[k]);
+    hi = fmaxf(hi, smax[k]);
+    bad |= sbad[k];
   }
+}
+// Raise (lower) a shared word, whose atomics queue at 11 ns each, only where
+// the value read says that it would change.
+__device__ __forceinline__ void raise(uint32_t *p, uint32_t v) {
+  if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
+}
+__device__ __forceinline__ void lower(uint32_t *p, uint32_t v) {
+  if (v < __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(p, v);
 }
 
-__global__ void encode_m16_kernel(const float *__restrict__ vel, uint16_t *__restrict__ codes, size_t n, float dt,
-                                  float m_lo, float m_step) {
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const float t = vel[i] * dt;
-    const float u = m_step > 0.f ? rintf((t * t - m_lo) / m_step) : 0.f;
-    codes[i] = static_cast<uint16_t>(fminf(fmaxf(u, 0.f), 65535.f));
+// m = (v dt)^2 (not written where m is null), the velocity's range and whether
+// every value is finite and positive.
+struct InitM {
+  const float *vel;
+  float *m;
+  float dt;
+  StepState *st;
+  float lo = __builtin_huge_valf(), hi = 0.f;
+  int bad = 0;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    float v[V], o[V];
+    lds_get<V>(vel + u, v);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float t = v[e] * dt;
+      o[e] = t * t;
+      if (!(v[e] > 0.f) || !(v[e] < __builtin_huge_valf())) bad = 1;
+      lo = fminf(lo, v[e]);
+      hi = fmaxf(hi, v[e]);
+    }
+    if (m) lds_put<V>(m + f, o);
   }
-}
+  __device__ void finish() {
+    block_range(lo, hi, bad);
+    if (threadIdx.x == 0) {
+      if (bad) atomicOr(&st->flags, 2u);
+      if (lo > 0.f) lower(&st->vmin_bits, __float_as_uint(lo));
+      raise(&st->vmax_bits, __float_as_uint(fmaxf(hi, 0.f)));
+    }
+  }
+};
+
+struct EncodeM16 {
+  const float *vel;
+  uint16_t *codes;
+  float dt, m_lo, m_step;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    float v[V];
+    lds_get<V>(vel + u, v);
+    uint16_t c[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float t = v[e] * dt;
+      const float q = m_step > 0.f ? rintf((t * t - m_lo) / m_step) : 0.f;
+      c[e] = static_cast<uint16_t>(fminf(fmaxf(q, 0.f), 65535.f));
+    }
+    if constexpr (V == 4)
+      *reinterpret_cast<u32x2 *>(codes + f) = u32x2{c[0] | static_cast<uint32_t>(c[1]) << 16, c[2] | static_cast<uint32_t>(c[3]) << 16};
+    else
+      codes[f] = c[0];
+  }
+  __device__ void finish() {}
+};
 
 // Setting a 16-bit stored field from float32 values (wave_write_field): the
 // field's maximum record of step n first holds max |x| (float bits; the
@@ -477,31 +594,40 @@ __global__ void scale_record_clear_kernel(StepState *st, uint32_t *slots, int v_
   if (threadIdx.x < kMaxSlots) slots[max_slot(st->n, threadIdx.x) + v_field] = 0u;
 }
 
-__global__ void __launch_bounds__(256) absmax_kernel(const float *__restrict__ x, size_t n, StepState *st,
-                                                     int v_field) {
-  __shared__ float part[4];
+struct AbsMax {
+  const float *x;
+  StepState *st;
+  int v_field;
   float mx = 0.f;
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    mx = fmaxf(mx, fabsf(x[i]));
+  template <int V> __device__ void run(size_t u, size_t, unsigned, size_t) {
+    float v[V];
+    lds_get<V>(x + u, v);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    atomicMax(&(v_field ? st->amax_v : st->amax)[st->n & 3],
-              __float_as_uint(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]))));
-}
+    for (int e = 0; e < V; ++e) mx = fmaxf(mx, fabsf(v[e]));
+  }
+  __device__ void finish() {
+    float lo = 0.f;
+    int bad = 0;
+    block_range(lo, mx, bad);
+    if (threadIdx.x == 0) raise(&(v_field ? st->amax_v : st->amax)[st->n & 3], __float_as_uint(mx));
+  }
+};
 
-template <int S>
-__global__ void encode_field_kernel(const float *__restrict__ x, typename Codec<S>::raw *__restrict__ dst, size_t n,
-                                    const StepState *st, int v_field) {
-  const float bound = __uint_as_float((v_field ? st->amax_v : st->amax)[st->n & 3]);
-  const float sc = exp2i(scale_exponent(bound));
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    dst[i] = Codec<S>::enc(x[i] * sc);
-}
+template <int S> struct EncodeField {
+  const float *x;
+  typename Codec<S>::raw *dst;
+  const StepState *st;
+  int v_field;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    const float sc = exp2i(scale_exponent(__uint_as_float((v_field ? st->amax_v : st->amax)[st->n & 3])));
+    float v[V];
+    nt_get<V>(x + u, v);
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] *= sc;
+    field_put<S, V>(dst + f, v);
+  }
+  __device__ void finish() {}
+};
 
 template <int S>
 __global__ void scale_record_kernel(StepState *st, int v_field) {
@@ -512,6 +638,97 @@ __global__ void scale_record_kernel(StepState *st, int v_field) {
   const int e = scale_exponent(bound);
   rec[slot] = __float_as_uint(fabsf(Codec<S>::dec(Codec<S>::enc(bound * exp2i(e)))));
   (v_field ? st->exps_v : st->exps)[slot] = e;
+}
+
+// Float32 values into a field (S = kF32) or between two fields.
+struct CopyIn {
+  const float *x;
+  float *dst;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    float v[V];
+    nt_get<V>(x + u, v);
+    lds_put<V>(dst + f, v);
+  }
+  __device__ void finish() {}
+};
+
+template <int S> struct Decode {
+  const typename Codec<S>::raw *src;
+  float *out;
+  const StepState *st;
+  int slot_off, v_field;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    float v[V];
+    field_get<S, V>(src + f, v);
+    if constexpr (S != kF32) {
+      const int slot = (st->n + slot_off) & 3;
+      const float inv = exp2i(-(v_field ? st->exps_v[slot] : st->exps[slot]));
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] *= inv;
+    }
+    nt_put<V>(out + u, v);
+  }
+  __device__ void finish() {}
+};
+
+// A^{n-1} = (A^n - V^n) / g from the 16-bit velocity-form pair; rows are grid
+// rows here.
+template <int S> struct DecodePrev {
+  const typename Codec<S>::raw *fa, *fv;
+  float *out;
+  const float *gx, *gy, *gz;
+  int ny;
+  const StepState *st;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned row, size_t col) {
+    const int slot = st->n & 3;
+    const float ia = exp2i(-st->exps[slot]), iv = exp2i(-st->exps_v[slot]);
+    float a[V], v[V];
+    field_get<S, V>(fa + f, a);
+    field_get<S, V>(fv + f, v);
+    const float gyz = gy[row % static_cast<unsigned>(ny)] * gz[row / static_cast<unsigned>(ny)];  // the step kernel's association
+#pragma unroll
+    for (int e = 0; e < V; ++e) a[e] = (a[e] * ia - v[e] * iv) / (gx[col + e] * gyz);
+    nt_put<V>(out + u, a);
+  }
+  __device__ void finish() {}
+};
+
+// dJ/dv = 2 img dt / sqrt(m)
+struct GradFinal {
+  const float *img, *m;
+  float dt;
+  float *grad;
+  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+    float a[V], b[V];
+    lds_get<V>(img + f, a);
+    lds_get<V>(m + f, b);
+#pragma unroll
+    for (int e = 0; e < V; ++e) a[e] = 2.f * a[e] * dt / sqrtf(b[e]);
+    nt_put<V>(grad + u, a);
+  }
+  __device__ void finish() {}
+};
+
+// nx, pitch, rows: the caller's rows of nx nodes, the field's pitch.  by_row:
+// rows stay rows where the pitch equals nx too (the operation needs them).
+template <class Op>
+hipError_t launch_rows(Op op, const void *user, const GridRows &g, bool reduces, bool by_row, hipStream_t s) {
+  const bool one = !by_row && g.pitch == g.nx;
+  RowMap map;
+  const size_t rows = one ? 1 : g.rows;
+  map.len = one ? static_cast<size_t>(g.nx) * g.rows : g.nx;
+  map.nu = g.nx;
+  map.nf = g.pitch;
+  const unsigned nseg = static_cast<unsigned>((map.len + 255) / 256);
+  map.seg = FastDiv(nseg);
+  map.total = static_cast<unsigned>(rows * nseg);
+  const bool vec = map.len % 4 == 0 && g.pitch % 4 == 0 && (one || g.nx % 4 == 0) && reinterpret_cast<uintptr_t>(user) % 16 == 0;
+  const unsigned want = (map.total + 3) / 4;
+  // a reduction ends in an atomic per workgroup: 8 workgroups per CU read the array
+  const dim3 grid(reduces && want > 2048 ? 2048u : want), b(256);
+  if (vec) hipLaunchKernelGGL((rows_kernel<4, Op>), grid, b, 0, s, op, map);
+  else hipLaunchKernelGGL((rows_kernel<1, Op>), grid, b, 0, s, op, map);
+  return hipGetLastError();
 }
 
 __global__ void bump_kernel(StepState *st, int count, const uint32_t *slots) {  // one wavefront
@@ -544,36 +761,6 @@ __global__ void reset_state_kernel(StepState *st, uint32_t *slots) {
     st->exps[t] = 0;
     st->amax_v[t] = 0u;
     st->exps_v[t] = 0;
-  }
-}
-
-template <int S>
-__global__ void decode_kernel(const typename Codec<S>::raw *__restrict__ f, float *__restrict__ out, size_t n,
-                              const StepState *st, int slot_off, int v_field) {
-  const int slot = (st->n + slot_off) & 3;
-  const int e = S == kF32 ? 0 : (v_field ? st->exps_v[slot] : st->exps[slot]);
-  const float inv = exp2i(-e);
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    out[i] = Codec<S>::dec(f[i]) * inv;
-}
-
-// A^{n-1} = (A^n - V^n) / g from the 16-bit velocity-form pair.
-template <int S>
-__global__ void decode_prev_kernel(const typename Codec<S>::raw *__restrict__ fa,
-                                   const typename Codec<S>::raw *__restrict__ fv, float *__restrict__ out,
-                                   const float *__restrict__ gx, const float *__restrict__ gy,
-                                   const float *__restrict__ gz, int nx, int ny, int nz, const StepState *st) {
-  const int slot = st->n & 3;
-  const float ia = exp2i(-st->exps[slot]), iv = exp2i(-st->exps_v[slot]);
-  const size_t total = static_cast<size_t>(nx) * ny * nz;
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const int x = static_cast<int>(i % nx);
-    const int y = static_cast<int>((i / nx) % ny);
-    const int z = static_cast<int>(i / (static_cast<size_t>(nx) * ny));
-    const float g = gx[x] * (gy[y] * gz[z]);  // the step kernel's association
-    out[i] = (Codec<S>::dec(fa[i]) * ia - Codec<S>::dec(fv[i]) * iv) / g;
   }
 }
 
@@ -612,13 +799,6 @@ __global__ void finite_kernel(const typename Codec<S>::raw *__restrict__ f, size
     if (!(fabsf(v) < __builtin_huge_valf())) bad = 1;
   }
   if (bad) atomicOr(&st->flags, 1u);
-}
-
-__global__ void grad_kernel(const float *__restrict__ img, const float *__restrict__ m, float dt,
-                            float *__restrict__ grad, size_t n) {
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    grad[i] = 2.f * img[i] * dt / sqrtf(m[i]);
 }
 
 // Field values to time candidate configurations on (hash of the node index):
@@ -687,32 +867,34 @@ hipError_t launch_step(int storage, int variant, bool adjoint, const StepArgs &a
   }
 }
 
-hipError_t launch_init_m(const float *vel, float *m, size_t n, float dt, StepState *st, hipStream_t s) {
-  hipLaunchKernelGGL(init_m_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, vel, m, n, dt, st);
-  return hipGetLastError();
+hipError_t launch_init_m(const float *vel, float *m, const GridRows &g, float dt, StepState *st, hipStream_t s) {
+  return launch_rows(InitM{vel, m, dt, st}, vel, g, true, false, s);
 }
 
-hipError_t launch_encode_m16(const float *vel, uint16_t *codes, size_t n, float dt, float m_lo, float m_step,
+hipError_t launch_encode_m16(const float *vel, uint16_t *codes, const GridRows &g, float dt, float m_lo, float m_step,
                              hipStream_t s) {
-  hipLaunchKernelGGL(encode_m16_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, vel, codes, n, dt, m_lo, m_step);
-  return hipGetLastError();
+  return launch_rows(EncodeM16{vel, codes, dt, m_lo, m_step}, vel, g, false, false, s);
 }
 
-hipError_t launch_encode_field(int storage, const float *x, void *dst, size_t n, StepState *st, uint32_t *slots,
-                              bool v_field, hipStream_t s) {
+hipError_t launch_encode_field(int storage, const float *x, void *dst, const GridRows &g, StepState *st,
+                              uint32_t *slots, bool v_field, hipStream_t s) {
   if (storage != kF16 && storage != kBF16) return hipErrorInvalidValue;
   const int vf = v_field ? 1 : 0;
-  const dim3 g(grid_for(n, 256)), b(256);
   hipLaunchKernelGGL(scale_record_clear_kernel, dim3(1), dim3(64), 0, s, st, slots, vf);
-  hipLaunchKernelGGL(absmax_kernel, g, b, 0, s, x, n, st, vf);
+  hipError_t e = launch_rows(AbsMax{x, st, vf}, x, g, true, false, s);
+  if (e != hipSuccess) return e;
   if (storage == kF16) {
-    hipLaunchKernelGGL(encode_field_kernel<kF16>, g, b, 0, s, x, static_cast<uint16_t *>(dst), n, st, vf);
+    e = launch_rows(EncodeField<kF16>{x, static_cast<uint16_t *>(dst), st, vf}, x, g, false, false, s);
     hipLaunchKernelGGL(scale_record_kernel<kF16>, dim3(1), dim3(64), 0, s, st, vf);
   } else {
-    hipLaunchKernelGGL(encode_field_kernel<kBF16>, g, b, 0, s, x, static_cast<uint16_t *>(dst), n, st, vf);
+    e = launch_rows(EncodeField<kBF16>{x, static_cast<uint16_t *>(dst), st, vf}, x, g, false, false, s);
     hipLaunchKernelGGL(scale_record_kernel<kBF16>, dim3(1), dim3(64), 0, s, st, vf);
   }
-  return hipGetLastError();
+  return e != hipSuccess ? e : hipGetLastError();
+}
+
+hipError_t launch_copy_in(const float *x, float *dst, const GridRows &g, hipStream_t s) {
+  return launch_rows(CopyIn{x, dst}, x, g, false, false, s);
 }
 
 hipError_t launch_bump(StepState *st, int count, const uint32_t *slots, hipStream_t s) {
@@ -741,36 +923,27 @@ hipError_t launch_reset_state(StepState *st, uint32_t *slots, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_decode(int storage, const void *field, float *out, size_t n, const StepState *st,
+hipError_t launch_decode(int storage, const void *field, float *out, const GridRows &g, const StepState *st,
                          int slot_off, bool v_field, hipStream_t s) {
-  const dim3 g(grid_for(n, 256)), b(256);
   const int vf = v_field ? 1 : 0;
   switch (storage) {
-    case kF32: hipLaunchKernelGGL(decode_kernel<kF32>, g, b, 0, s, (const float *)field, out, n, st, slot_off, vf); break;
-    case kF16: hipLaunchKernelGGL(decode_kernel<kF16>, g, b, 0, s, (const uint16_t *)field, out, n, st, slot_off, vf); break;
-    case kBF16: hipLaunchKernelGGL(decode_kernel<kBF16>, g, b, 0, s, (const uint16_t *)field, out, n, st, slot_off, vf); break;
+    case kF32:
+      return launch_rows(Decode<kF32>{static_cast<const float *>(field), out, st, slot_off, vf}, out, g, false, false, s);
+    case kF16:
+      return launch_rows(Decode<kF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, out, g, false, false, s);
+    case kBF16:
+      return launch_rows(Decode<kBF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, out, g, false, false, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_decode_prev(int storage, const void *fa, const void *fv, float *out, const float *gx,
-                              const float *gy, const float *gz, int nx, int ny, int nz, const StepState *st,
+                              const float *gy, const float *gz, const GridRows &g, int ny, const StepState *st,
                               hipStream_t s) {
-  const size_t n = static_cast<size_t>(nx) * ny * nz;
-  const dim3 g(grid_for(n, 256)), b(256);
-  switch (storage) {
-    case kF16:
-      hipLaunchKernelGGL(decode_prev_kernel<kF16>, g, b, 0, s, (const uint16_t *)fa, (const uint16_t *)fv, out, gx,
-                         gy, gz, nx, ny, nz, st);
-      break;
-    case kBF16:
-      hipLaunchKernelGGL(decode_prev_kernel<kBF16>, g, b, 0, s, (const uint16_t *)fa, (const uint16_t *)fv, out,
-                         gx, gy, gz, nx, ny, nz, st);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  const uint16_t *a = static_cast<const uint16_t *>(fa), *v = static_cast<const uint16_t *>(fv);
+  if (storage == kF16) return launch_rows(DecodePrev<kF16>{a, v, out, gx, gy, gz, ny, st}, out, g, false, true, s);
+  if (storage == kBF16) return launch_rows(DecodePrev<kBF16>{a, v, out, gx, gy, gz, ny, st}, out, g, false, true, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_gather(int storage, const void *field, const int64_t *lin, int nrec, float *traces,
@@ -804,9 +977,8 @@ hipError_t launch_check_finite(int storage, const void *field, size_t n, StepSta
   return hipGetLastError();
 }
 
-hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(grad_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, img, m, dt, grad, n);
-  return hipGetLastError();
+hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, const GridRows &g, hipStream_t s) {
+  return launch_rows(GradFinal{img, m, dt, grad}, grad, g, false, false, s);
 }
 
 namespace {

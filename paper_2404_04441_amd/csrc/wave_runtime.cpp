@@ -354,6 +354,7 @@ struct wave_ctx {
         g = nullptr;
       }
   }
+  GridRows rows() const { return GridRows{p.nx, p.nx, static_cast<size_t>(p.ny) * p.nz}; }
   // A^k lives in field(k): buffer k mod 2, or k mod 4 with two steps per pass
   void *field(int k) const {
     if (p.time_block == 2) {
@@ -980,7 +981,7 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   w->m16 = p->model_bits == 16;
   // float32 m is written by the range pass itself; 16-bit codes need the
   // range first (encoded below, once it is known on the host)
-  if (!rc) rc = hip_rc(launch_init_m(vel_dev, w->m16 ? nullptr : w->m, w->N, static_cast<float>(p->dt), w->st,
+  if (!rc) rc = hip_rc(launch_init_m(vel_dev, w->m16 ? nullptr : w->m, w->rows(), static_cast<float>(p->dt), w->st,
                                      w->stream));
   if (!rc && !w->m16) rc = hip_rc(launch_fill_zero(w->m + w->N, 4 * (w->Np - w->N), w->stream));
   if (!rc) rc = hip_rc(hipMemcpyAsync(&back, w->st, sizeof(back), hipMemcpyDeviceToHost, w->stream));
@@ -1004,7 +1005,8 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
       w->m_lo = tlo * tlo;  // the float32 m of the extreme nodes, as the float32 path computes it
       w->m_step = (thi * thi - w->m_lo) / 65535.f;
       uint16_t *codes = reinterpret_cast<uint16_t *>(w->m);
-      rc = hip_rc(launch_encode_m16(vel_dev, codes, w->N, static_cast<float>(p->dt), w->m_lo, w->m_step, w->stream));
+      rc = hip_rc(launch_encode_m16(vel_dev, codes, w->rows(), static_cast<float>(p->dt), w->m_lo, w->m_step,
+                                    w->stream));
       if (!rc) rc = hip_rc(launch_fill_zero(codes + w->N, 2 * (w->Np - w->N), w->stream));
     }
     if (!rc && p->cpml_width > 0) rc = setup_cpml(w, vmax);
@@ -1153,7 +1155,7 @@ int wave_adjoint(wave_t w, int32_t nt, const float *wavelet_dev, const float *re
       std::swap(mu1, mu2);
     }
   }
-  if (!rc) rc = hip_rc(launch_grad_final(img, w->m, static_cast<float>(w->p.dt), grad_vel_dev, w->N, w->stream));
+  if (!rc) rc = hip_rc(launch_grad_final(img, w->m, static_cast<float>(w->p.dt), grad_vel_dev, w->rows(), w->stream));
   if (!rc) rc = do_reset(w);
   return rc;
 }
@@ -1162,15 +1164,15 @@ int wave_read_field(wave_t w, int32_t which, float *out_dev) {
   if (!w || !out_dev || which < 0 || which > 2) return WAVE_EINVAL;
   const bool f32 = w->p.storage == WAVE_F32;
   if (which == 0)
-    return hip_rc(launch_decode(w->p.storage, w->field(w->n), out_dev, w->N, w->st, 0, false, w->stream));
+    return hip_rc(launch_decode(w->p.storage, w->field(w->n), out_dev, w->rows(), w->st, 0, false, w->stream));
   if (which == 2) {
     if (f32) return WAVE_EINVAL;
-    return hip_rc(launch_decode(w->p.storage, w->fv, out_dev, w->N, w->st, 0, true, w->stream));
+    return hip_rc(launch_decode(w->p.storage, w->fv, out_dev, w->rows(), w->st, 0, true, w->stream));
   }
   if (f32)
-    return hip_rc(launch_decode(w->p.storage, w->field(w->n + 3), out_dev, w->N, w->st, 3, false, w->stream));
-  return hip_rc(launch_decode_prev(w->p.storage, w->field(w->n), w->fv, out_dev, w->gx, w->gy, w->gz, w->p.nx,
-                                   w->p.ny, w->p.nz, w->st, w->stream));
+    return hip_rc(launch_decode(w->p.storage, w->field(w->n + 3), out_dev, w->rows(), w->st, 3, false, w->stream));
+  return hip_rc(launch_decode_prev(w->p.storage, w->field(w->n), w->fv, out_dev, w->gx, w->gy, w->gz, w->rows(),
+                                   w->p.ny, w->st, w->stream));
 }
 
 int wave_write_field(wave_t w, int32_t which, const float *in_dev) {
@@ -1178,11 +1180,11 @@ int wave_write_field(wave_t w, int32_t which, const float *in_dev) {
   if (w->p.storage == WAVE_F32) {
     if (which < 0 || which > 1) return WAVE_EINVAL;
     void *dst = w->field(which == 0 ? w->n : w->n + 3);
-    return hip_rc(hipMemcpyAsync(dst, in_dev, 4 * w->N, hipMemcpyDeviceToDevice, w->stream));
+    return hip_rc(launch_copy_in(in_dev, static_cast<float *>(dst), w->rows(), w->stream));
   }
   if (which != 0 && which != 2) return WAVE_EINVAL;  // 16-bit storage keeps A^n and V^n
-  return hip_rc(launch_encode_field(w->p.storage, in_dev, which == 0 ? w->field(w->n) : w->fv, w->N, w->st,
-                                    w->slots, which == 2, w->stream));
+  return hip_rc(launch_encode_field(w->p.storage, in_dev, which == 0 ? w->field(w->n) : w->fv, w->rows(),
+                                    w->st, w->slots, which == 2, w->stream));
 }
 
 // Snapshot layout: 256-B header | step state | A fields 0 and 1 | V (16-bit)
