@@ -69,7 +69,8 @@ enum wave_storage {
 enum { WAVE_FLAG_NONFINITE = 1u };
 
 typedef struct {
-  int32_t nx, ny, nz;        /* grid nodes per axis, >= 1; nx*ny <= 2^24 */
+  int32_t nx, ny, nz;        /* grid nodes per axis, >= 1; nx*ny <= 2^24 (rows need no alignment:
+                                with variant = 0 the workspace pads them to whole vectors) */
   double dx, dy, dz;         /* grid spacing (m), > 0 */
   double dt;                 /* time step (s), > 0, at most the stability limit */
   int32_t sponge_width;      /* damping strip width in nodes; 0 = zero-Dirichlet only */
@@ -190,7 +191,8 @@ int wave_create(const wave_params *p, const float *vel_dev, void *ws_dev, size_t
  * static context synchronises its stream so that the next one starts on an
  * idle array.  Work from any other source that writes the array while a
  * static context's work is in flight on that device races with it.  Errors
- * as wave_create, plus WAVE_ENOSPC when wave_workspace_bytes(p) exceeds
+ * as wave_create, plus WAVE_ENOSPC when its workspace (wave_workspace_bytes(p)
+ * less any row padding) exceeds
  * WAVE_STATIC_BYTES and WAVE_ESTATE as above. */
 #define WAVE_STATIC_BYTES ((size_t)64 << 20)
 int wave_create_static(const wave_params *p, const float *vel_dev, void *hip_stream, wave_t *out);
@@ -290,7 +292,10 @@ int wave_variant_count(void);
  * Family 0 is the 2.5D blocking of paper Sec. IV-A (tile x and y, stream
  * along z): by wavefronts of 64 lanes, ry rows and vec nodes along x per lane,
  * pd planes of loads in flight; tiles of 64*vec x by*ry nodes (variants up to
- * 19) or of the same number of nodes in another width (from 20 on).
+ * 19) or of the same number of nodes in another width (from 20 on).  The last
+ * ones (from 29 on) are the shapes of several nodes per lane again, in their
+ * order, for any nx: the workspace's rows are padded to whole vectors (info
+ * reports vec = 1).  Variant 0 may choose them; wave_tiling then reports them.
  * Variant 0 means "automatic"; its info is the shape that choice falls back
  * to (also available explicitly as another variant).
  * Families 1 and 2 are the paper's 3D-blocking designs of the same section

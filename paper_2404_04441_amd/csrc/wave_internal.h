@@ -201,6 +201,8 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
 // (scratch_bytes long): at most one such context per device at a time
 // (WAVE_ESTATE otherwise); tuning off; graph_steps must be 0.  wave_destroy
 // of that context synchronises its stream and frees the device's slot.
+// The bytes such a context takes (its rows are not padded).
+int static_workspace_bytes(const wave_params *p, size_t *bytes);
 int create_static_ctx(const wave_params *p, const float *vel_dev, void *scratch, size_t scratch_bytes,
                       void *hip_stream, wave_t *out, int device);
 

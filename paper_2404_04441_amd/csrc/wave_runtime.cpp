@@ -30,10 +30,43 @@ size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 struct Layout {
   size_t st, slots, gx, gy, gz, rz, rec_lin, rec_node, rec_off, rec_ord, grec, m, fa, fb, fc, fd, fv, ckpt, seg, mua, mub, img;
   size_t cpml_ab, cpml_slab[3], total;  // CPML: a/b tables, psi+zeta slab pair per axis
-  int K, nck;
+  int K, nck, pitch;  // pitch: nodes per row of the arrays
 };
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
+
+// The variants of the interface: the shapes of the kernel table and behind
+// them, for every 2.5D shape with more than one node per lane, its form with
+// padded rows (any nx; reported with vec = 1).
+std::vector<int> padded_shapes() {
+  std::vector<int> v;
+  for (int k = 1; k < variant_count(); ++k)
+    if (variant_info(k).family == 0 && variant_info(k).vec > 1) v.push_back(k);
+  return v;
+}
+const std::vector<int> kPadded = padded_shapes();
+int interface_count() { return variant_count() + static_cast<int>(kPadded.size()); }
+bool is_padded(int v) { return v >= variant_count() && v < interface_count(); }
+int base_shape(int v) { return is_padded(v) ? kPadded[v - variant_count()] : v; }
+int padded_shape(int base) {
+  for (size_t k = 0; k < kPadded.size(); ++k)
+    if (kPadded[k] == base) return variant_count() + static_cast<int>(k);
+  return base;
+}
+
+// Nodes per row of the workspace's arrays: nx, or nx rounded up to whole
+// four-node vectors where the caller leaves the shape open (or asks for a
+// padded one).  The added columns have sponge factor 0 and stay zero.  Rows
+// that are not whole vectors could only be walked one or two nodes per lane,
+// at 0.5 to 0.7 of the rate (301x211x157: 35 -> 31 us a step); three columns
+// cost at most 9% of the shortest row that is padded, 32 nodes.  CPML keeps
+// its slabs and two-steps-per-pass its fixed shape on unpadded rows.
+int row_pitch(const wave_params *p) {
+  if (p->nx % 4 == 0 || p->cpml_width > 0 || p->time_block == 2) return p->nx;
+  if (p->variant > 0 ? !is_padded(p->variant) : p->nx < 32) return p->nx;
+  const int pitch = (p->nx + 3) / 4 * 4;
+  return static_cast<int64_t>(pitch) * p->ny <= (int64_t(1) << 24) ? pitch : p->nx;
+}
 
 int validate(const wave_params *p) {
   if (!p) return WAVE_EINVAL;
@@ -73,8 +106,8 @@ int validate(const wave_params *p) {
   if (p->adjoint) {
     if (p->storage != WAVE_F32 || p->nt_max < 1 || p->ckpt_interval < 0) return WAVE_EINVAL;
   }
-  if (p->variant < 0 || p->variant >= variant_count()) return WAVE_EINVAL;
-  if (p->variant > 0) {
+  if (p->variant < 0 || p->variant >= interface_count()) return WAVE_EINVAL;
+  if (p->variant > 0 && !is_padded(p->variant)) {
     const Variant v = variant_info(p->variant);
     // a tile shape with VEC > 1 x nodes per lane needs whole vectors per row
     if (p->nx % v.vec) return WAVE_EINVAL;
@@ -89,25 +122,26 @@ int validate(const wave_params *p) {
   if (p->time_block != 0 && p->time_block != 2) return WAVE_EINVAL;
   if (p->time_block == 2) {
     if (p->storage != WAVE_F32 || p->cpml_width > 0 || p->adjoint || p->cache_hint != 0) return WAVE_EINVAL;
-    if (p->variant > 0 && variant_info(p->variant).family != 4) return WAVE_EINVAL;
+    if (p->variant > 0 && variant_info(base_shape(p->variant)).family != 4) return WAVE_EINVAL;
     if (p->graph_steps % 4) return WAVE_EINVAL;  // replays start at the same buffer phase (n mod 4)
-  } else if (p->variant > 0 && variant_info(p->variant).family == 4) {
+  } else if (p->variant > 0 && variant_info(base_shape(p->variant)).family == 4) {
     return WAVE_EINVAL;
   }
   // 16-bit model codes exist for the 16-bit storage forward step only
   if (p->model_bits != 0 && p->model_bits != 32 && p->model_bits != 16) return WAVE_EINVAL;
   if (p->model_bits == 16 && p->storage == WAVE_F32) return WAVE_EINVAL;
-  if (p->cache_hint == 1 && (p->cpml_width > 0 || (p->variant > 0 && variant_info(p->variant).family != 0)))
+  if (p->cache_hint == 1 && (p->cpml_width > 0 || (p->variant > 0 && variant_info(base_shape(p->variant)).family != 0)))
     return WAVE_EINVAL;
   return WAVE_OK;
 }
 
-int plan(const wave_params *p, Layout *L) {
+int plan(const wave_params *p, Layout *L, bool pad) {
   const int rc = validate(p);
   if (rc) return rc;
-  const size_t N = static_cast<size_t>(p->nx) * p->ny * p->nz;
+  L->pitch = pad ? row_pitch(p) : p->nx;
+  const size_t N = static_cast<size_t>(L->pitch) * p->ny * p->nz;
   // fields the step kernel touches carry kPadZ zero planes after the interior
-  const size_t Np = static_cast<size_t>(p->nx) * p->ny * (static_cast<size_t>(p->nz) + kPadZ);
+  const size_t Np = static_cast<size_t>(L->pitch) * p->ny * (static_cast<size_t>(p->nz) + kPadZ);
   const size_t es = p->storage == WAVE_F32 ? 4 : 2;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -117,7 +151,7 @@ int plan(const wave_params *p, Layout *L) {
   };
   L->st = take(sizeof(StepState));
   L->slots = p->storage == WAVE_F32 ? off : take(kMaxSlotBytes);
-  L->gx = take(4 * static_cast<size_t>(p->nx));
+  L->gx = take(4 * static_cast<size_t>(L->pitch));
   L->gy = take(4 * static_cast<size_t>(p->ny));
   L->gz = take(4 * (static_cast<size_t>(p->nz) + kPadZ));
   L->rz = take(4 * (static_cast<size_t>(p->nz) + kPadZ));
@@ -225,6 +259,8 @@ int auto_variant(const wave_params *p) {
   if (p->nx % 2 == 0) return 8;
   return p->storage == WAVE_F32 ? 0 : 3;
 }
+// The one-node-per-lane shape that also has the CPML terms fused in.
+constexpr int kNarrowVariant = 3;
 // The adjoint kernel keeps two z queues: its default is a one-node-per-lane
 // shape that fits in registers (8 wavefronts x 4 rows, one plane in flight).
 constexpr int kAdjointVariant = 5;
@@ -312,7 +348,8 @@ Tiling make_tiling(const wave_params *p, int variant) {
 }  // namespace
 
 struct wave_ctx {
-  wave_params p{};
+  wave_params p{};  // the caller's, with nx the row pitch and variant a shape of the kernel table
+  int nx = 0;       // the caller's nx
   std::vector<int32_t> rec;
   hipStream_t stream = nullptr;
   char *ws = nullptr;
@@ -354,7 +391,7 @@ struct wave_ctx {
         g = nullptr;
       }
   }
-  GridRows rows() const { return GridRows{p.nx, p.nx, static_cast<size_t>(p.ny) * p.nz}; }
+  GridRows rows() const { return GridRows{nx, p.nx, static_cast<size_t>(p.ny) * p.nz}; }
   // A^k lives in field(k): buffer k mod 2, or k mod 4 with two steps per pass
   void *field(int k) const {
     if (p.time_block == 2) {
@@ -851,7 +888,7 @@ int wave_stable_dt(const wave_params *p, double vmax, double *dt_max) {
 int wave_workspace_bytes(const wave_params *p, size_t *bytes) {
   if (!bytes) return WAVE_EINVAL;
   Layout L;
-  const int rc = plan(p, &L);
+  const int rc = plan(p, &L, true);
   if (rc) return rc;
   *bytes = L.total;
   return WAVE_OK;
@@ -871,7 +908,8 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   if (!out || !vel_dev || !ws_dev) return WAVE_EINVAL;
   *out = nullptr;
   Layout L;
-  int rc = plan(p, &L);
+  // the static array keeps unpadded rows: every grid that fitted it still does
+  int rc = plan(p, &L, static_dev < 0);
   if (rc) return rc;
   if (reinterpret_cast<uintptr_t>(ws_dev) % 256) return WAVE_EINVAL;
   if (ws_bytes < L.total) return WAVE_ENOSPC;
@@ -880,6 +918,13 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   if (!w) return WAVE_EINVAL;
   w->static_dev = static_dev;
   w->p = *p;
+  w->nx = p->nx;
+  w->p.nx = L.pitch;
+  if (is_padded(p->variant)) {  // its shape, or one node per lane where the rows stay as they are
+    w->p.variant = base_shape(p->variant);
+    if (L.pitch % variant_info(w->p.variant).vec || (w->p.cpml_width > 0 && !variant_fuses_cpml(w->p.variant)))
+      w->p.variant = kNarrowVariant;
+  }
   w->rec.assign(p->rec, p->rec + 3 * static_cast<size_t>(p->nrec));
   w->p.rec = nullptr;  // never keep the caller's pointer
   w->stream = static_cast<hipStream_t>(hip_stream);
@@ -904,9 +949,9 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
     w->fc = w->ws + L.fc;
     w->fd = w->ws + L.fd;
   }
-  const int nx = p->nx, ny = p->ny, nz = p->nz;
-  w->N = static_cast<size_t>(nx) * ny * nz;
-  w->Np = static_cast<size_t>(nx) * ny * (static_cast<size_t>(nz) + kPadZ);
+  const int nx = p->nx, ny = p->ny, nz = p->nz, pitch = L.pitch;
+  w->N = static_cast<size_t>(pitch) * ny * nz;
+  w->Np = static_cast<size_t>(pitch) * ny * (static_cast<size_t>(nz) + kPadZ);
 
   // FP64 host tables
   const double ix2 = 1.0 / (p->dx * p->dx), iy2 = 1.0 / (p->dy * p->dy), iz2 = 1.0 / (p->dz * p->dz);
@@ -920,13 +965,14 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
     w->c.kz[m - 1] = static_cast<float>(kC[m] * iz2);
   }
   w->src_scale = static_cast<float>(p->dt * p->dt / (p->dx * p->dy * p->dz));
-  const std::vector<float> gx = sponge_table(nx, p->sponge_width, p->sponge_alpha);
+  std::vector<float> gx = sponge_table(nx, p->sponge_width, p->sponge_alpha);
+  gx.resize(pitch, 0.f);  // padding columns stay zero
   const std::vector<float> gy = sponge_table(ny, p->sponge_width, p->sponge_alpha);
   std::vector<float> gz = sponge_table(nz, p->sponge_width, p->sponge_alpha);
   std::vector<int64_t> lin(p->nrec);
   for (int r = 0; r < p->nrec; ++r) {
     const int x = w->rec[3 * r], y = w->rec[3 * r + 1], z = w->rec[3 * r + 2];
-    lin[r] = x + static_cast<int64_t>(nx) * (y + static_cast<int64_t>(ny) * z);
+    lin[r] = x + static_cast<int64_t>(pitch) * (y + static_cast<int64_t>(ny) * z);
   }
   // receivers grouped by node, each group in receiver order: the adjoint
   // sums a node's residuals in that fixed order (duplicates included)
@@ -956,10 +1002,11 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
 
   // tiling: the forward step and (for adjoint contexts) the adjoint step
   // each get a shape; variant 0 picks the measured-best ones
-  w->fwd = make_tiling(p, (p->variant > 0 && p->time_block == 0) ? p->variant : auto_variant(p));
-  w->fwd.keep = p->cache_hint == 1;
-  if (p->time_block == 2) w->pair = make_tiling(p, kPairVariant);
-  if (p->adjoint) w->adj = make_tiling(p, p->variant > 0 ? p->variant : kAdjointVariant);
+  const wave_params *g = &w->p;
+  w->fwd = make_tiling(g, (g->variant > 0 && g->time_block == 0) ? g->variant : auto_variant(g));
+  w->fwd.keep = g->cache_hint == 1;
+  if (g->time_block == 2) w->pair = make_tiling(g, kPairVariant);
+  if (g->adjoint) w->adj = make_tiling(g, g->variant > 0 ? g->variant : kAdjointVariant);
 
   StepState init{};
   init.vmin_bits = 0x7f800000u;
@@ -980,7 +1027,9 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   }
   w->m16 = p->model_bits == 16;
   // float32 m is written by the range pass itself; 16-bit codes need the
-  // range first (encoded below, once it is known on the host)
+  // range first (encoded below, once it is known on the host).  Padding
+  // planes and columns hold zero
+  if (!rc && pitch != nx) rc = hip_rc(launch_fill_zero(w->m, (w->m16 ? 2 : 4) * w->N, w->stream));
   if (!rc) rc = hip_rc(launch_init_m(vel_dev, w->m16 ? nullptr : w->m, w->rows(), static_cast<float>(p->dt), w->st,
                                      w->stream));
   if (!rc && !w->m16) rc = hip_rc(launch_fill_zero(w->m + w->N, 4 * (w->Np - w->N), w->stream));
@@ -1034,6 +1083,13 @@ std::mutex g_static_mu;
 constexpr int kMaxStaticDevices = 64;
 bool g_static_live[kMaxStaticDevices] = {};
 }  // namespace
+
+int wave::static_workspace_bytes(const wave_params *p, size_t *bytes) {
+  Layout L;
+  const int rc = plan(p, &L, false);
+  if (!rc) *bytes = L.total;
+  return rc;
+}
 
 int wave::create_static_ctx(const wave_params *p, const float *vel_dev, void *scratch, size_t scratch_bytes,
                             void *hip_stream, wave_t *out, int device) {
@@ -1199,12 +1255,25 @@ constexpr uint64_t kStateMagic = 0x31544154534556ull;  // "VESTAT1"
 
 size_t state_bytes(const wave_ctx *w, size_t *field_bytes, size_t *slabs) {
   const size_t es = w->p.storage == WAVE_F32 ? 4 : 2;
-  *field_bytes = es * w->N;
+  *field_bytes = es * static_cast<size_t>(w->nx) * w->p.ny * w->p.nz;
   *slabs = 0;
   if (w->cpml)
     for (int a = 0; a < 3; ++a) *slabs += slab_bytes(w, a);
   const int nfields = w->p.storage == WAVE_F32 ? 2 : 3;
   return 256 + 256 + nfields * align256(*field_bytes) + align256(*slabs);
+}
+}  // namespace
+
+namespace {
+// The rows of a field to (from) a snapshot, which holds them without padding.
+hipError_t copy_rows(const wave_ctx *w, char *snap, void *field, bool save) {
+  const size_t es = w->p.storage == WAVE_F32 ? 4 : 2, row = es * w->nx, pitch = es * w->p.nx;
+  const size_t rows = static_cast<size_t>(w->p.ny) * w->p.nz;
+  if (row == pitch)
+    return save ? hipMemcpyAsync(snap, field, row * rows, hipMemcpyDeviceToDevice, w->stream)
+                : hipMemcpyAsync(field, snap, row * rows, hipMemcpyDeviceToDevice, w->stream);
+  return save ? hipMemcpy2DAsync(snap, row, field, pitch, row, rows, hipMemcpyDeviceToDevice, w->stream)
+              : hipMemcpy2DAsync(field, pitch, snap, row, row, rows, hipMemcpyDeviceToDevice, w->stream);
 }
 }  // namespace
 
@@ -1225,7 +1294,7 @@ int wave_save_state(wave_t w, void *dst_dev) {
   h.field_bytes = fb;
   h.slab_bytes = sb;
   h.n = w->n;
-  h.nx = w->p.nx;
+  h.nx = w->nx;
   h.ny = w->p.ny;
   h.nz = w->p.nz;
   h.storage = w->p.storage;
@@ -1244,7 +1313,7 @@ int wave_save_state(wave_t w, void *dst_dev) {
   }
   const int nfields = w->p.storage == WAVE_F32 ? 2 : 3;
   for (int k = 0; k < nfields && !rc; ++k, off += align256(fb))
-    rc = hip_rc(hipMemcpyAsync(d + off, fields[k], fb, hipMemcpyDeviceToDevice, w->stream));
+    rc = hip_rc(copy_rows(w, d + off, fields[k], true));
   for (int a = 0; a < 3 && w->cpml && !rc; ++a) {
     rc = hip_rc(hipMemcpyAsync(d + off, w->ws + w->L.cpml_slab[a], slab_bytes(w, a), hipMemcpyDeviceToDevice,
                                w->stream));
@@ -1263,7 +1332,7 @@ int wave_load_state(wave_t w, const void *src_dev) {
   int rc = hip_rc(hipMemcpyAsync(&h, src, sizeof(h), hipMemcpyDeviceToHost, w->stream));
   if (!rc) rc = hip_rc(hipStreamSynchronize(w->stream));
   if (rc) return rc;
-  if (h.magic != kStateMagic || h.bytes != total || h.field_bytes != fb || h.slab_bytes != sb || h.nx != w->p.nx ||
+  if (h.magic != kStateMagic || h.bytes != total || h.field_bytes != fb || h.slab_bytes != sb || h.nx != w->nx ||
       h.ny != w->p.ny || h.nz != w->p.nz || h.storage != w->p.storage || h.cpml_width != w->p.cpml_width || h.n < 0 ||
       h.pad[0] != w->p.time_block)
     return WAVE_EINVAL;
@@ -1278,7 +1347,7 @@ int wave_load_state(wave_t w, const void *src_dev) {
   }
   const int nfields = w->p.storage == WAVE_F32 ? 2 : 3;
   for (int k = 0; k < nfields && !rc; ++k, off += align256(fb))
-    rc = hip_rc(hipMemcpyAsync(fields[k], src + off, fb, hipMemcpyDeviceToDevice, w->stream));
+    rc = hip_rc(copy_rows(w, const_cast<char *>(src) + off, fields[k], false));
   for (int a = 0; a < 3 && w->cpml && !rc; ++a) {
     rc = hip_rc(hipMemcpyAsync(w->ws + w->L.cpml_slab[a], src + off, slab_bytes(w, a), hipMemcpyDeviceToDevice,
                                w->stream));
@@ -1322,7 +1391,7 @@ int wave_destroy(wave_t w) {
   return rc;
 }
 
-int wave_variant_count(void) { return variant_count(); }
+int wave_variant_count(void) { return interface_count(); }
 
 int wave_tiling(wave_t w, int32_t *out) {
   if (!w || !out) return WAVE_EINVAL;
@@ -1333,6 +1402,8 @@ int wave_tiling(wave_t w, int32_t *out) {
     const Variant a = variant_info(0), b = variant_info(k);
     if (a.family == b.family && a.by == b.by && a.ry == b.ry && a.pd == b.pd && a.vec == b.vec) v = k;
   }
+  // on padded rows a shape that the caller's nx does not admit is its padded form
+  if (w->nx != w->p.nx && w->nx % variant_info(v).vec) v = padded_shape(v);
   out[0] = v;
   out[1] = w->p.time_block == 2 ? w->pair.zchunk : w->fwd.zchunk;
   out[2] = w->fwd.keep ? 1 : 0;
@@ -1340,8 +1411,9 @@ int wave_tiling(wave_t w, int32_t *out) {
 }
 
 int wave_variant_info(int32_t variant, int32_t *info) {
-  if (!info || variant < 0 || variant >= variant_count()) return WAVE_EINVAL;
-  const Variant v = variant_info(variant);
+  if (!info || variant < 0 || variant >= interface_count()) return WAVE_EINVAL;
+  Variant v = variant_info(base_shape(variant));
+  if (is_padded(variant)) v.vec = 1;  // no divisor of nx is asked for
   info[0] = v.family;
   info[1] = v.by;
   info[2] = v.ry;

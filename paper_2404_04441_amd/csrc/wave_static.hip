@@ -47,7 +47,7 @@ int wave_create_static(const wave_params *p, const float *vel_dev, void *hip_str
   *out = nullptr;
   if (p->graph_steps != 0) return WAVE_EINVAL;
   size_t need = 0;
-  int rc = wave_workspace_bytes(p, &need);
+  int rc = wave::static_workspace_bytes(p, &need);
   if (rc) return rc;
   if (need > kScratchBytes) return WAVE_ENOSPC;
   int dev = -1;
