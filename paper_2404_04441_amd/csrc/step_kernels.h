@@ -435,8 +435,21 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   __shared__ float red[BY], redv[BY];
 
   // XCD-aware tile order: hardware id b runs on XCD b % 8.
-  const int nwg = static_cast<int>(gridDim.x);
+  const int nwg = (a.total_tiles + 7) & ~7;
   const int bid = static_cast<int>(blockIdx.x);
+  if (bid >= nwg) {
+    // Workgroups past the tiles sample a receiver list, one step late: the
+    // nodes of A^n, which this launch reads.  A gather of its own after each
+    // step costs its launch (4.7 us at 301x211x157, where the step takes 26);
+    // sampling in the tiles' prologue put its chain of loads on every step.
+    const int r = (bid - nwg) * (64 * BY) + static_cast<int>(threadIdx.x);
+    if (!ADJ && r < a.gcount) {
+      const int n = a.st->n + a.k;
+      const float v = Codec<S>::dec(static_cast<const typename Codec<S>::raw *>(a.cur)[a.glin[r]]);
+      a.traces[static_cast<size_t>(n - 1) * a.nrec + r] = S == kF32 ? v : v * exp2i(-a.st->exps[n & 3]);
+    }
+    return;
+  }
   const int logical = (bid & 7) * (nwg >> 3) + (bid >> 3);
   if (logical >= a.total_tiles) return;
   const int tix = logical % a.tiles_x;
@@ -1672,7 +1685,8 @@ int blocks_variant(int v, bool cpml) {
 
 template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, bool ADJ, bool M16 = false>
 hipError_t launch_one(const StepArgs &a, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>((a.total_tiles + 7) / 8 * 8);
+  unsigned grid = static_cast<unsigned>((a.total_tiles + 7) / 8 * 8);
+  if constexpr (FAM == 0 || FAM == 3) grid += (static_cast<unsigned>(a.gcount) + 64 * BY - 1) / (64 * BY);
   if constexpr (M16) {  // 16-bit storage forward with 16-bit model codes
     if constexpr (FAM != 0 || S == kF32 || ADJ) {
       return hipErrorInvalidValue;

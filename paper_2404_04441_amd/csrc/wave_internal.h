@@ -125,6 +125,10 @@ struct StepArgs {
   int m16;
   float m_lo, m_step;
   uint32_t *slots;    // 16-bit storage: per-level maxima (max_slot in the step kernels)
+  // 2.5D forward: sample the current level A^n at nodes glin[0 .. gcount) into
+  // trace row n-1 (receiver lists, by workgroups past the tiles; 0: none)
+  const int64_t *glin;
+  int gcount;
 };
 
 // The rows of a caller's array (nx nodes each) and the pitch of the

@@ -58,7 +58,7 @@ int padded_shape(int base) {
 // four-node vectors where the caller leaves the shape open (or asks for a
 // padded one).  The added columns have sponge factor 0 and stay zero.  Rows
 // that are not whole vectors could only be walked one or two nodes per lane,
-// at 0.5 to 0.7 of the rate (301x211x157: 35 -> 31 us a step); three columns
+// at 0.5 to 0.8 of the rate (301x211x157: 34.8 -> 29 us a step); three columns
 // cost at most 9% of the shortest row that is padded, 32 nodes.  CPML keeps
 // its slabs and two-steps-per-pass its fixed shape on unpadded rows.
 int row_pitch(const wave_params *p) {
@@ -453,6 +453,11 @@ int enqueue_steps(wave_ctx *w, int count, const float *wavelet, float *traces, b
   }
   if (sample && w->fused_rec && !fix_pass) a.box = w->box;
   const bool gather = sample && (!w->fused_rec || fix_pass) && w->p.nrec > 0;
+  // the 2.5D kernels sample the level they read: each step the receivers of
+  // the step before, the last one a gather of its own
+  const int family = variant_info(w->fwd.variant).family;
+  const bool late = gather && w->p.time_block != 2 && (family == 0 || family == 3);
+  if (late) a.glin = w->rec_lin;
   for (int k = 0; k < count; ++k) {
     const int nk = w->n + k;
     if (w->p.time_block == 2 && count - k >= 2) {  // steps nk and nk+1 in one pass
@@ -478,6 +483,7 @@ int enqueue_steps(wave_ctx *w, int count, const float *wavelet, float *traces, b
     a.prev = w->p.storage == WAVE_F32 ? w->field(nk + 3) : w->fv;
     a.vout = w->fv;
     a.k = k;
+    a.gcount = late && k > 0 ? w->p.nrec : 0;
     int rc = 0;
     if (w->cpml) rc = hip_rc(launch_cpml_psi(w->cp, static_cast<const float *>(a.cur), w->stream));
     if (!rc) rc = hip_rc(launch_step(w->p.storage, w->fwd.variant, false, a, w->stream));
@@ -485,7 +491,7 @@ int enqueue_steps(wave_ctx *w, int count, const float *wavelet, float *traces, b
       rc = hip_rc(launch_cpml_fix(w->cp, static_cast<const float *>(a.cur), w->m, static_cast<float *>(a.out),
                                   w->cpml_fused, w->stream));
     if (rc) return rc;
-    if (gather) {
+    if (gather && (!late || k == count - 1)) {
       rc = hip_rc(launch_gather(w->p.storage, a.out, w->rec_lin, w->p.nrec, traces, w->st, k, w->stream));
       if (rc) return rc;
     }
