@@ -92,7 +92,7 @@ typedef struct {
   int32_t tune;              /* 1 (the default) with variant = 0 and zchunk = 0: wave_create
                                 times candidate configurations for a few steps on fields of
                                 noise (zeroed afterwards): the 2.5D shapes and z-chunks, both cache policies
-                                (without CPML or adjoint), and for float32 forward runs without
+                                (without CPML), and for float32 forward runs without
                                 CPML or adjoint also the 3D-blocked gmem and smem shapes.  It
                                 keeps the fastest (the fixed rule's choice unless another is more
                                 than 3% faster).  With adjoint != 0 it also times the adjoint

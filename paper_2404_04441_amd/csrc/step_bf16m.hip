@@ -3,6 +3,6 @@
 
 namespace wave {
 
-hipError_t launch_variant_bf16m(int v, const StepArgs &a, hipStream_t s) { return launch_variant<kBF16, false, true>(v, a, s); }
+hipError_t launch_variant_bf16m(int v, const StepArgs &a, hipStream_t s) { return launch_variant<kBF16, kForward, true>(v, a, s); }
 
 }  // namespace wave

@@ -3,7 +3,7 @@
 
 namespace wave {
 
-hipError_t launch_variant_f32(int v, const StepArgs &a, hipStream_t s) { return launch_variant<kF32, false>(v, a, s); }
-int blocks_variant_f32(int v, bool cpml) { return blocks_variant<kF32, false>(v, cpml); }
+hipError_t launch_variant_f32(int v, const StepArgs &a, hipStream_t s) { return launch_variant<kF32, kForward>(v, a, s); }
+int blocks_variant_f32(int v, bool cpml) { return blocks_variant<kF32>(v, cpml); }
 
 }  // namespace wave

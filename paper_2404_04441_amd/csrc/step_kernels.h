@@ -255,7 +255,7 @@ __device__ __forceinline__ int slab_index(int i, int n, int W) {
 // vector-memory load of the z loop lives here: s_waitcnt vmcnt retires loads
 // in issue order, so a load consumed in the same iteration would also wait for
 // every prefetch issued before it.
-template <int S, int RY, int VEC, int NYH, bool ADJ, bool CP, bool M16 = false>
+template <int S, int RY, int VEC, int NYH, bool IMG, bool CP, bool M16 = false>
 struct Stage {
   static constexpr int NA = VEC * (S == kF32 ? 4 : 2);  // bytes of one A-type row
   static constexpr int NF = VEC * 4;                    // bytes of one float row
@@ -267,14 +267,14 @@ struct Stage {
   Words<S == kF32 ? 4 : 2> xh;    // x-halo value of A^n at plane z (lanes < 8*RY)
   float gz;                       // sponge factor of plane z
   int rz;                         // receiver-box plane index of plane z, or -1
-  Words<NF> leadF[ADJ ? RY : 1];  // adjoint: forward field, same roles
-  Words<NF> img[ADJ ? RY : 1];    // adjoint: imaging accumulator at plane z
-  Words<NF> yhF[ADJ ? NYH : 1];
-  float xhF;
+  Words<NF> img[IMG ? RY : 1];           // imaging: accumulator and L(A^k), L(A^{k+1}) at plane z
+  Words<NF> la0[IMG ? RY : 1], la1[IMG ? RY : 1];
   float psx[CP ? RY : 1][CP ? VEC : 1];  // CPML: psi_x at the lane's columns (0 off the x layers)
   float zex[CP ? RY : 1][CP ? VEC : 1];  // CPML: zeta_x at the lane's columns
   float psxh;                            // CPML: psi_x at this lane's x-halo node (lanes < 8*RY)
 };
+
+enum StepMode { kForward = 0, kAdjoint = 1, kImaging = 2, kStoreLap = 3 };
 
 constexpr int kQ = 2 * R + 1;  // z-queue length (planes z-4 .. z+4)
 
@@ -382,12 +382,24 @@ static_assert(kPadZ >= (kQ - 1) + kMaxPD + R, "z padding must cover the last tri
 // there from step to step (forward; chosen by create-time tuning or the
 // caller).
 // M16: m is read as 16-bit codes (m = m_lo + u m_step; 16-bit storage only).
-template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, bool ADJ, bool CP, bool KEEP, bool M16 = false>
+// MODE: what the float32 gradient needs of a step.  kStoreLap, a forward step
+// that also stores L(A^n) (the recomputation of a segment).  kAdjoint, the
+// same update run backwards on mu = m g lambda, with the residuals of the
+// receivers' plane added to the Laplacian.  kImaging, an adjoint step that also
+// adds mu^{k+1} L(A^k) + mu^{k+2} L(A^{k+1}) to the image, both mu being at
+// hand: every second adjoint step is one.  With the Laplacian kept
+// from the recomputation (it is computed there in any case) the adjoint
+// step has one stencil, one queue and one ring instead of two, and the image is
+// read and written every second step: 60 instead of 64 bytes per node and step
+// of the whole gradient, and an adjoint step of 256^3 went from 87 us to 42
+// and 73 us in turn.
+template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, int MODE, bool CP, bool KEEP, bool M16 = false>
 __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
+  constexpr bool ADJ = MODE == kAdjoint || MODE == kImaging, IMG = MODE == kImaging, LAP = MODE == kStoreLap;
   constexpr int ROWS = 64 * BY / LX;  // row groups of LX lanes
   static_assert(64 * BY % LX == 0, "whole rows of lanes");
-  using StageT = Stage<S, RY, VEC, (2 * R + ROWS - 1) / ROWS, ADJ, CP, M16>;
-  static_assert(!M16 || (S != kF32 && !ADJ && !CP && !SEMI), "16-bit model codes: 16-bit storage forward");
+  using StageT = Stage<S, RY, VEC, (2 * R + ROWS - 1) / ROWS, IMG, CP, M16>;
+  static_assert(!M16 || (S != kF32 && MODE == kForward && !CP && !SEMI), "16-bit model codes: 16-bit storage forward");
   constexpr int NA = StageT::NA, NF = StageT::NF;
   constexpr int TX = LX * VEC;
   constexpr int TY = ROWS * RY;
@@ -399,9 +411,10 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   static_assert(kQ % PD == 0, "pipeline depth must divide the queue length");
   static_assert(PD <= kMaxPD, "z padding assumes at most kMaxPD planes in flight");
   static_assert(VEC == 1 || VEC == 2 || VEC == 4, "lane width");
-  static_assert(!(SEMI && ADJ), "the semi-stencil form is forward only");
-  static_assert(!CP || (S == kF32 && !SEMI && !ADJ), "the fused CPML step is float32 forward");
-  static_assert(!KEEP || (!SEMI && !ADJ && !CP), "the cached policy is for the plain forward step");
+  static_assert(!SEMI || MODE == kForward, "the semi-stencil form is forward only");
+  static_assert(MODE == kForward || S == kF32, "the gradient's modes are float32");
+  static_assert(!CP || (S == kF32 && !SEMI && MODE == kForward), "the fused CPML step is float32 forward");
+  static_assert(!KEEP || (!SEMI && !CP), "the cached policy is for the plain steps");
   constexpr int NTP = KEEP ? 0 : kNT;  // cache policy of the fields read or written once
   // f16 storage with 16-bit m sums the Laplacian from its centre weight (Eq. 1
   // as written) instead of as centred differences: 25 instead of 48 vector
@@ -424,10 +437,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // beside it) fits 150 KB of LDS; the others stage the centre plane
   // double-buffered.  The CPML step of 512^3 reads 1.70 instead of 1.96 GB
   // with it.
-  constexpr bool LEADH = !ADJ && 6 * LP * 4 + (CP ? 2 * (TY * LW + 64 * VEC) * 4 : 0) <= 150 * 1024;
+  constexpr bool LEADH = 6 * LP * 4 + (CP ? 2 * (TY * LW + 64 * VEC) * 4 : 0) <= 150 * 1024;
   constexpr int NSLOT = LEADH ? R + 2 : 2;
   __shared__ __attribute__((aligned(16))) float lds[NSLOT][LP];
-  __shared__ __attribute__((aligned(16))) float ldsF[ADJ ? 2 : 1][ADJ ? LP : 1];
   // CPML: psi_x rows of the tile (TY rows of LW, no y halo) and a scratch row
   constexpr int LPX = TY * LW + 64 * VEC;
   constexpr int DUMMYX = TY * LW;
@@ -506,8 +518,10 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const rsrc_t rM_ = M16 ? make_rsrc(reinterpret_cast<const char *>(a.m) + base * 2, span)
                          : make_rsrc(a.m + base, span_f);
   const rsrc_t rnull = make_rsrc(a.gz, 0u);
-  const rsrc_t rF = make_rsrc((ADJ ? a.fwd : a.m) + base, span_f);
-  const rsrc_t rI = make_rsrc((ADJ ? a.img : a.m) + base, ADJ ? span_f : 0u);
+  const rsrc_t rI_ = make_rsrc((IMG ? a.img : a.m) + base, IMG ? span_f : 0u);
+  const rsrc_t rL0_ = make_rsrc((IMG ? a.la0 : a.m) + base, IMG ? span_f : 0u);
+  const rsrc_t rL1_ = make_rsrc((IMG && a.la1 ? a.la1 : a.m) + base, IMG && a.la1 ? span_f : 0u);
+  const rsrc_t rLo = make_rsrc((LAP ? a.lap : const_cast<float *>(a.m)) + base, LAP ? span_f : 0u);
   auto so = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes; };     // plane offset, A fields
   auto so_f = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes_f; };  // plane offset, float fields
 
@@ -607,7 +621,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   auto load_stage = [&](StageT &st, int z) {
     const bool live = !kSkipTail || z < zend;
     const rsrc_t rU = live ? rU_ : rnull, rP = live ? rP_ : rnull, rM = live ? rM_ : rnull;
-    const uint32_t sl = so(z + R), slf = so_f(z + R);
+    const uint32_t sl = so(z + R);
     const uint32_t sc = so(z), scf = so_f(z);
     st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
     st.rz = static_cast<int>(ld_words<4, 0>(rgz, 0u, rz_off + static_cast<uint32_t>(z) * 4u).w[0]);
@@ -620,15 +634,14 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
     for (int i = 0; i < NYH; ++i) st.yh[i] = ld_words<NA, 0>(rU, vyh[i], LEADH ? sl : sc);
     st.xh = ld_words<S == kF32 ? 4 : 2, 0>(rU, vxh, LEADH ? sl : sc);
-    if constexpr (ADJ) {
+    if constexpr (IMG) {
+      const rsrc_t rI = live ? rI_ : rnull, rL0 = live ? rL0_ : rnull, rL1 = live ? rL1_ : rnull;
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
-        st.leadF[j] = ld_words<NF, 0>(rF, vrow_f[j], slf);
         st.img[j] = ld_words<NF, kNT>(rI, vrow_f[j], scf);
+        st.la0[j] = ld_words<NF, kNT>(rL0, vrow_f[j], scf);
+        st.la1[j] = ld_words<NF, kNT>(rL1, vrow_f[j], scf);
       }
-#pragma unroll
-      for (int i = 0; i < NYH; ++i) st.yhF[i] = ld_words<NF, 0>(rF, vyh_f[i], scf);
-      st.xhF = __uint_as_float(ld_words<4, 0>(rF, vxh_f, scf).w[0]);
     }
     if constexpr (CP) {  // x slab plane z (none past nz); zero off the x layers
       const bool zin = z < a.nz;
@@ -654,7 +667,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // are in flight.  Queue slot (p - zb + R) mod 9 holds plane p; stages hold
   // planes zb .. zb+PD-1.
   Words<NA> pq[2 * R][RY];
-  Words<NF> pqF[ADJ ? 2 * R : 1][RY];
   Words<NA> pyh[LEADH ? R : 1][NYH];
   Words<S == kF32 ? 4 : 2> pxh[LEADH ? R : 1];
 #pragma unroll
@@ -662,13 +674,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const int zz = zb - R + k;
     const bool zok = zz >= 0;
     const rsrc_t r = zok ? rU_ : rnull;
-    const rsrc_t rf = zok ? rF : rnull;
-    const uint32_t s0 = zok ? so(zz) : 0u, s0f = zok ? so_f(zz) : 0u;
+    const uint32_t s0 = zok ? so(zz) : 0u;
 #pragma unroll
-    for (int j = 0; j < RY; ++j) {
-      pq[k][j] = ld_words<NA, 0>(r, vrow[j], s0);
-      if constexpr (ADJ) pqF[k][j] = ld_words<NF, 0>(rf, vrow_f[j], s0f);
-    }
+    for (int j = 0; j < RY; ++j) pq[k][j] = ld_words<NA, 0>(r, vrow[j], s0);
   }
   if constexpr (LEADH) {
 #pragma unroll
@@ -762,16 +770,12 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 
   // ---- queue and ring from the prologue's loads
   float q[kQ][RY][VEC];
-  float qF[ADJ ? kQ : 1][RY][VEC];
 #pragma unroll
   for (int k = 0; k < 2 * R; ++k)
 #pragma unroll
     for (int j = 0; j < RY; ++j)
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) {
-        q[k][j][i] = row_get<S>(pq[k][j], i);
-        if constexpr (ADJ) qF[k][j][i] = __uint_as_float(pqF[k][j].w[i]);
-      }
+      for (int i = 0; i < VEC; ++i) q[k][j][i] = row_get<S>(pq[k][j], i);
   if constexpr (LEADH) {  // ring slots 0 .. R-1: planes zb .. zb+R-1 with their halo
 #pragma unroll
     for (int k = 0; k < R; ++k) {
@@ -961,7 +965,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       // in this iteration (plane z+R with LEADH, else plane z)
       float *L = lds[LEADH ? (z - zb) % NSLOT : par];
       float *Lw = LEADH ? lds[(z - zb + R) % NSLOT] : L;
-      float *LF = ldsF[ADJ ? par : 0];
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
 #pragma unroll
@@ -977,11 +980,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
             X[(s + 2 * R) % kQ][j][i] = t;
           }
         }
-        if constexpr (ADJ) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) qF[(s + 2 * R) % kQ][j][i] = __uint_as_float(cs.leadF[j].w[i]);
-          lds_put<VEC>(LF + (R + w * RY + j) * LW + R + VEC * lane, qF[cslot][j]);
-        }
       }
 #pragma unroll
       for (int k = 0; k < NYH; ++k) {
@@ -989,14 +987,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) t[i] = row_get<S>(cs.yh[k], i);
         lds_put<VEC>(Lw + yhlds[k], t);
-        if constexpr (ADJ) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) t[i] = __uint_as_float(cs.yhF[k].w[i]);
-          lds_put<VEC>(LF + yhlds[k], t);
-        }
       }
       Lw[xhlds] = row_get<S>(cs.xh, 0);
-      if constexpr (ADJ) LF[xhlds] = cs.xhF;
       float *Lpsi = ldsX[CP ? par : 0];
       float zex[CP ? RY : 1][CP ? VEC : 1];
       if constexpr (CP) {
@@ -1008,7 +1000,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
         }
         Lpsi[xhx] = cs.psxh;
       }
-      float pc[RY][VEC], mc[RY][VEC], ic[RY][VEC];
+      float pc[RY][VEC], mc[RY][VEC];
+      float im[IMG ? RY : 1][VEC];  // the imaging sum with mu^{k+1} L(A^k) and mu^{k+2} L(A^{k+1}) added
 #pragma unroll
       for (int j = 0; j < RY; ++j)
 #pragma unroll
@@ -1021,7 +1014,9 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
             mc[j][i] = __uint_as_float(cs.m[j].w[i]);
             if constexpr (S != kF32) mc[j][i] *= m_unit;
           }
-          ic[j][i] = ADJ ? __uint_as_float(cs.img[ADJ ? j : 0].w[i]) : 0.f;
+          if constexpr (IMG)
+            im[j][i] = fmaf(q[cslot][j][i], __uint_as_float(cs.la0[j].w[i]),
+                            fmaf(pc[j][i], __uint_as_float(cs.la1[j].w[i]), __uint_as_float(cs.img[j].w[i])));
         }
       const float gzv = cs.gz;
       const int rzi = ADJ ? rec_plane(z) : __builtin_amdgcn_readfirstlane(cs.rz);
@@ -1068,6 +1063,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
           for (int i = 0; i < VEC; ++i) lap[i] += ext[i];
         }
+        if constexpr (LAP) st_words<NF, kNT>(row_put<kF32, VEC>(lap), rLo, vrow_f[j], sz0f);
         if (ADJ && rzi >= 0) {  // residuals of a receiver plane
 #pragma unroll
           for (int i = 0; i < VEC; ++i) {
@@ -1121,16 +1117,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           }
           rkeep[S != kF32 ? j : 0] = ra;
         }
-        if constexpr (ADJ) {
-          // the imaging term L(A^k), only accumulated (no recurrence runs
-          // through it): summed from the centre weight, 25 instead of 48
-          // operations per node
-          float lapF[VEC], im[VEC], laxF[3][VEC], dyF[R][RY][VEC];
-          laplacian(qF, LF, cslot, s, j, lapF, X, laxF, dyF, std::integral_constant<bool, true>{});
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) im[i] = fmaf(q[cslot][j][i], lapF[i], ic[j][i]);
-          st_words<NF, kNT>(row_put<kF32, VEC>(im), rI, vrow_f[j], sz0f);
-        }
+        if constexpr (IMG) st_words<NF, kNT>(row_put<kF32, VEC>(im[j]), rI_, vrow_f[j], sz0f);
       }
       // receiver samples of A^{n+1} (forward), in the plane's own uniform branch
       if (!ADJ && rzi >= 0) {
@@ -1653,77 +1640,62 @@ constexpr bool fuses_cpml() {
   return RY <= 2 && RY * VEC <= 4;
 }
 
-template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, bool ADJ, bool CP = false>
+template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, bool CP = false>
 int blocks_per_cu() {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(step_kernel<S, BY, RY, PD, VEC, LX, SEMI, ADJ, CP, false>), 64 * BY, 0) !=
+          &nb, reinterpret_cast<const void *>(step_kernel<S, BY, RY, PD, VEC, LX, SEMI, kForward, CP, false>), 64 * BY, 0) !=
       hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 
-template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, bool ADJ>
+template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX>
 int blocks_fam(bool cpml) {
-  if constexpr (FAM == 0 && S == kF32 && !ADJ && fuses_cpml<RY, VEC>())
-    if (cpml) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false, false, true>();
-  if constexpr (FAM == 0) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false, ADJ>();
-  if constexpr (FAM == 3 && S == kF32 && !ADJ) return blocks_per_cu<S, BY, RY, PD, VEC, LX, true, false, false>();
+  if constexpr (FAM == 0 && S == kF32 && fuses_cpml<RY, VEC>())
+    if (cpml) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false, true>();
+  if constexpr (FAM == 0) return blocks_per_cu<S, BY, RY, PD, VEC, LX, false>();
+  if constexpr (FAM == 3 && S == kF32) return blocks_per_cu<S, BY, RY, PD, VEC, LX, true>();
   return 1;  // the 3D-blocked kernels size their grids from the block shape alone
 }
 
-template <int S, bool ADJ>
+template <int S>
 int blocks_variant(int v, bool cpml) {
   switch (v) {
 #define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec, lx) \
-  case id: return blocks_fam<fam, S, by, ry, pd, vec, lx, ADJ>(cpml);
+  case id: return blocks_fam<fam, S, by, ry, pd, vec, lx>(cpml);
     WAVE_VARIANTS(WAVE_VARIANT_CASE)
 #undef WAVE_VARIANT_CASE
     default: return 1;
   }
 }
 
-template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, bool ADJ, bool M16 = false>
+template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, int MODE, bool CP, bool KEEP, bool M16>
+void launch_step_kernel(const StepArgs &a, unsigned grid, hipStream_t s) {
+  hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, SEMI, MODE, CP, KEEP, M16>), dim3(grid), dim3(64 * BY), 0, s,
+                     a);
+}
+
+template <int FAM, int S, int BY, int RY, int PD, int VEC, int LX, int MODE, bool M16 = false>
 hipError_t launch_one(const StepArgs &a, hipStream_t s) {
   unsigned grid = static_cast<unsigned>((a.total_tiles + 7) / 8 * 8);
   if constexpr (FAM == 0 || FAM == 3) grid += (static_cast<unsigned>(a.gcount) + 64 * BY - 1) / (64 * BY);
-  if constexpr (M16) {  // 16-bit storage forward with 16-bit model codes
-    if constexpr (FAM != 0 || S == kF32 || ADJ) {
-      return hipErrorInvalidValue;
-    } else {
-      if (a.keep)
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, true, true>), dim3(grid),
-                           dim3(64 * BY), 0, s, a);
-      else
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, false, true>), dim3(grid),
-                           dim3(64 * BY), 0, s, a);
-      return hipGetLastError();
-    }
-  } else if constexpr (FAM == 0) {
-    if constexpr (S == kF32 && !ADJ && fuses_cpml<RY, VEC>()) {
+  if constexpr (FAM == 0) {
+    if constexpr (S == kF32 && MODE == kForward && fuses_cpml<RY, VEC>()) {
       if (a.cpml) {
         if (a.zchunk % kQ) return hipErrorInvalidValue;  // whole trips only (no skip branch)
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, true, false>), dim3(grid), dim3(64 * BY),
-                           0, s, a);
+        launch_step_kernel<S, BY, RY, PD, VEC, LX, false, MODE, true, false, M16>(a, grid, s);
         return hipGetLastError();
       }
     }
-    if constexpr (!ADJ) {
-      if (a.keep) {
-        hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, false, false, true>), dim3(grid), dim3(64 * BY),
-                           0, s, a);
-        return hipGetLastError();
-      }
-    }
-    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, false, ADJ, false, false>), dim3(grid), dim3(64 * BY), 0, s,
-                       a);
-  } else if constexpr (S != kF32 || ADJ) {
+    if (a.keep) launch_step_kernel<S, BY, RY, PD, VEC, LX, false, MODE, false, true, M16>(a, grid, s);
+    else launch_step_kernel<S, BY, RY, PD, VEC, LX, false, MODE, false, false, M16>(a, grid, s);
+  } else if constexpr (S != kF32 || MODE != kForward || M16) {
     return hipErrorInvalidValue;  // the study families are float32 forward only
   } else if constexpr (FAM == 4) {
     hipLaunchKernelGGL(step2_kernel, dim3(grid), dim3(64 * kTbBY), 0, s, a);
   } else if constexpr (FAM == 3) {
-    hipLaunchKernelGGL((step_kernel<S, BY, RY, PD, VEC, LX, true, false, false, false>), dim3(grid), dim3(64 * BY), 0, s,
-                       a);
+    launch_step_kernel<S, BY, RY, PD, VEC, LX, true, MODE, false, false, false>(a, grid, s);
   } else if constexpr (FAM == 1) {
     hipLaunchKernelGGL((gmem_kernel<BY, RY>), dim3(grid), dim3(64 * BY * RY), 0, s, a);
   } else {
@@ -1732,11 +1704,11 @@ hipError_t launch_one(const StepArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int S, bool ADJ, bool M16 = false>
+template <int S, int MODE, bool M16 = false>
 hipError_t launch_variant(int v, const StepArgs &a, hipStream_t s) {
   switch (v) {
 #define WAVE_VARIANT_CASE(id, fam, by, ry, pd, vec, lx) \
-  case id: return launch_one<fam, S, by, ry, pd, vec, lx, ADJ, M16>(a, s);
+  case id: return launch_one<fam, S, by, ry, pd, vec, lx, MODE, M16>(a, s);
     WAVE_VARIANTS(WAVE_VARIANT_CASE)
 #undef WAVE_VARIANT_CASE
     default: return hipErrorInvalidValue;
@@ -1745,12 +1717,13 @@ hipError_t launch_variant(int v, const StepArgs &a, hipStream_t s) {
 
 }  // namespace
 
-// The per-storage instantiations, each in a translation unit of its own:
-// launch a step variant, and how many of its workgroups fit on one CU.
+// The instantiations, each in a translation unit of its own: launch a step
+// variant, and how many of its workgroups fit on one CU.
 hipError_t launch_variant_f32(int v, const StepArgs &a, hipStream_t s);
 hipError_t launch_variant_f16(int v, const StepArgs &a, hipStream_t s);
 hipError_t launch_variant_bf16(int v, const StepArgs &a, hipStream_t s);
-hipError_t launch_variant_adj(int v, const StepArgs &a, hipStream_t s);
+hipError_t launch_variant_adj(int v, const StepArgs &a, hipStream_t s);  // adjoint; with imaging where a.img is set
+hipError_t launch_variant_lap(int v, const StepArgs &a, hipStream_t s);  // forward, storing L(A^n)
 hipError_t launch_variant_f16m(int v, const StepArgs &a, hipStream_t s);   // 16-bit model codes
 hipError_t launch_variant_bf16m(int v, const StepArgs &a, hipStream_t s);
 int blocks_variant_f32(int v, bool cpml);

@@ -109,10 +109,12 @@ struct StepArgs {
   int k;              // this launch advances step st->n + k
   float gamma;        // 16-bit storage: |m L A| <= gamma max|A| at every node
   // adjoint mode only
-  const float *fwd;   // forward field A^k for the imaging term
-  float *img;         // accumulator sum_k mu^{k+1} L(A^k)
+  float *img;         // accumulator sum_k mu^{k+1} L(A^k); null: no imaging in this step
+  const float *la0;   // imaging: L(A^k)
+  const float *la1;   // imaging: L(A^{k+1}), or null
   const float *resid; // [nt][nrec] residual, injected at receivers
   int resid_row;      // row of resid injected by this launch
+  float *lap;         // forward, float32: where L(A^n) is stored, or null
   // CPML (float32 forward, 2.5D kernels): 1 = add the x part of the boundary
   // terms and update zeta_x inside the step (psi is updated by a pass before
   // it, the y and z parts by a pass after it)

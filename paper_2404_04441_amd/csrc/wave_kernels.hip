@@ -860,7 +860,7 @@ hipError_t launch_step(int storage, int variant, bool adjoint, const StepArgs &a
     return launch_variant_adj(variant, a, s);
   }
   switch (storage) {
-    case kF32: return launch_variant_f32(variant, a, s);
+    case kF32: return a.lap ? launch_variant_lap(variant, a, s) : launch_variant_f32(variant, a, s);
     case kF16: return a.m16 ? launch_variant_f16m(variant, a, s) : launch_variant_f16(variant, a, s);
     case kBF16: return a.m16 ? launch_variant_bf16m(variant, a, s) : launch_variant_bf16(variant, a, s);
     default: return hipErrorInvalidValue;

@@ -261,9 +261,6 @@ int auto_variant(const wave_params *p) {
 }
 // The one-node-per-lane shape that also has the CPML terms fused in.
 constexpr int kNarrowVariant = 3;
-// The adjoint kernel keeps two z queues: its default is a one-node-per-lane
-// shape that fits in registers (8 wavefronts x 4 rows, one plane in flight).
-constexpr int kAdjointVariant = 5;
 // The two-steps-per-pass kernel (variant family 4).
 constexpr int kPairVariant = 19;
 
@@ -678,8 +675,7 @@ int tune_forward(wave_ctx *w) {
   };
   // stage 1: the fixed rule's choice, then every shape at its automatic
   // z-chunk, 2.5D shapes with both cache policies where they apply (only the
-  // cached one for cache_hint 1; not for adjoint contexts, whose recomputation
-  // streams the checkpoint buffer through the same cache).  The 3D-blocked families compute the same
+  // cached one for cache_hint 1).  The 3D-blocked families compute the same
   // bits as the 2.5D shapes (float32 forward); on small grids, where
   // everything stays in cache, they can win.
   const bool blocked_ok = p.storage == WAVE_F32 && !w->cpml && !p.adjoint && p.cache_hint == 0;
@@ -699,7 +695,7 @@ int tune_forward(wave_ctx *w) {
     Tiling t = make_tiling(&q, v);
     t.keep = p.cache_hint == 1;
     cands.push_back(t);
-    if (!w->cpml && p.cache_hint == 0 && !p.adjoint) {
+    if (!w->cpml && p.cache_hint == 0) {
       t.keep = true;
       cands.push_back(t);
     }
@@ -754,15 +750,16 @@ int tune_forward(wave_ctx *w) {
     auto time_adj = [&](const Tiling &t) {
       StepArgs b = base_args(w, t);
       b.sx = -1;
-      b.img = img;
       b.cur = mu1;
       b.prev = mu2;
       b.out = mu2;
-      b.fwd = seg;
+      b.la0 = seg;
+      b.la1 = seg + w->Np;
       if (w->fused_rec) b.box = w->box;
       int r = 0;
-      for (int i = 0; i < 4 && !r; ++i) {
-        if (i == 1) r = hip_rc(hipEventRecord(e0, w->stream));
+      for (int i = 0; i < 6 && !r; ++i) {  // plain and imaging steps in turn, two of each timed
+        if (i == 2) r = hip_rc(hipEventRecord(e0, w->stream));
+        b.img = i & 1 ? img : nullptr;
         if (!r) r = hip_rc(launch_step(WAVE_F32, t.variant, true, b, w->stream));
       }
       if (!r) r = hip_rc(hipEventRecord(e1, w->stream));
@@ -776,13 +773,16 @@ int tune_forward(wave_ctx *w) {
     std::vector<std::pair<float, Tiling>> ta{{time_adj(dflt), dflt}};
     for (int v = 0; v < variant_count() && !rc; ++v) {
       const Variant info = variant_info(v);
-      if (info.family != 0 || p.nx % info.vec || v == dflt.variant) continue;
+      if (info.family != 0 || p.nx % info.vec) continue;
       if (!fits(p, v, false, &best_overhang)) continue;
       wave_params q = p;
       q.variant = v;
       q.zchunk = 0;
-      const Tiling t = make_tiling(&q, v);
-      ta.emplace_back(time_adj(t), t);
+      Tiling t = make_tiling(&q, v);
+      for (const bool keep : {false, true}) {
+        t.keep = keep;
+        if (!rc) ta.emplace_back(time_adj(t), t);
+      }
     }
     std::vector<std::pair<float, Tiling>> top(ta.begin(), ta.end());
     std::sort(top.begin(), top.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
@@ -790,10 +790,11 @@ int tune_forward(wave_ctx *w) {
     for (const auto &c : top) {
       wave_params q = p;
       q.variant = c.second.variant;
-      for (int zc : {9, 18, 27, 36, 45, 72, 99}) {
-        if (rc || zc >= p.nz) break;
+      for (int zc : chunk_list(p, c.second)) {
+        if (rc) break;
         q.zchunk = zc;
-        const Tiling t = make_tiling(&q, q.variant);
+        Tiling t = make_tiling(&q, q.variant);
+        t.keep = c.second.keep;
         if (t.zchunk != c.second.zchunk) ta.emplace_back(time_adj(t), t);
       }
     }
@@ -1012,7 +1013,7 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   w->fwd = make_tiling(g, (g->variant > 0 && g->time_block == 0) ? g->variant : auto_variant(g));
   w->fwd.keep = g->cache_hint == 1;
   if (g->time_block == 2) w->pair = make_tiling(g, kPairVariant);
-  if (g->adjoint) w->adj = make_tiling(g, g->variant > 0 ? g->variant : kAdjointVariant);
+  if (g->adjoint) w->adj = make_tiling(g, g->variant > 0 ? g->variant : auto_variant(g));
 
   StepState init{};
   init.vmin_bits = 0x7f800000u;
@@ -1160,62 +1161,80 @@ int wave_adjoint(wave_t w, int32_t nt, const float *wavelet_dev, const float *re
   const int nseg = (nt + K - 1) / K;
   w->drop_graphs();
 
-  // 1) forward run storing (A^{jK}, A^{jK-1}) for j = 1..nseg-1
+  // 1) forward run to the last segment's start, storing (A^{jK}, A^{jK-1}) for
+  // j = 1..nseg-2 (the last pair stays in the fields)
+  const GridRows whole{w->p.nx, w->p.nx, static_cast<size_t>(w->p.ny) * w->p.nz};  // rows of the workspace
+  auto copy = [&](float *dst, const void *src) {
+    return hip_rc(launch_copy_in(static_cast<const float *>(src), dst, whole, w->stream));
+  };
+  auto level = [&](int n) { return static_cast<float *>(w->field(n)); };
   int rc = do_reset(w);
   for (int j = 1; j < nseg && !rc; ++j) {
     rc = enqueue_steps(w, K, wavelet_dev, nullptr, false);
     if (rc) break;
     w->n += K;
     float *ck = ckpt + 2 * static_cast<size_t>(j - 1) * w->N;
-    rc = hip_rc(hipMemcpyAsync(ck, w->field(w->n), fb, hipMemcpyDeviceToDevice, w->stream));
-    if (!rc) rc = hip_rc(hipMemcpyAsync(ck + w->N, w->field(w->n + 3), fb, hipMemcpyDeviceToDevice, w->stream));
+    if (j < nseg - 1) rc = copy(ck, level(w->n));
+    if (!rc && j < nseg - 1) rc = copy(ck + w->N, level(w->n + 3));
   }
   // padded fields start zero (their padding planes stay zero)
   const size_t fbp = 4 * w->Np;
   if (!rc) rc = hip_rc(launch_fill_zero(mu1, fbp, w->stream));
   if (!rc) rc = hip_rc(launch_fill_zero(mu2, fbp, w->stream));
   if (!rc) rc = hip_rc(launch_fill_zero(img, fbp, w->stream));
-  if (!rc) rc = hip_rc(launch_fill_zero(seg, fbp * (K + 2), w->stream));
 
-  // 2) segments from last to first: recompute A^{jK+1..}, then adjoint steps
+  // one adjoint step: mu^k from mu^{k+1} and mu^{k+2}, in whose place it goes.
+  // Its imaging term, mu^{k+1} L(A^k), is added by this step together with
+  // the one before's, or left to the next: every second step updates the image
+  StepArgs b = base_args(w, w->adj);
+  b.sx = -1;
+  b.resid = resid_dev;
+  if (w->fused_rec) b.box = w->box;
+  bool pending = false;
+  auto adjoint_step = [&](int k, bool images) {
+    const bool last = images && k == 1;
+    b.img = images && (pending || last) ? img : nullptr;
+    b.la0 = slot(k % (K + 2));
+    b.la1 = pending ? slot((k + 1) % (K + 2)) : nullptr;
+    if (images) pending = !b.img;
+    b.cur = mu1;
+    b.prev = mu2;
+    b.out = mu2;
+    b.resid_row = k - 1;
+    int r = hip_rc(launch_step(WAVE_F32, w->adj.variant, true, b, w->stream));
+    if (!r && !w->fused_rec && w->p.nrec > 0)
+      r = hip_rc(launch_scatter(mu2, w->rec_node, w->rec_off, w->rec_ord, w->nrec_nodes, w->p.nrec, w->m, w->grec,
+                                resid_dev, k - 1, w->stream));
+    std::swap(mu1, mu2);
+    return r;
+  };
+  // 2) the step k = nt (mu^{nt+1} = 0: no imaging term), then segments from
+  // last to first: recompute A^{jK+1..}, storing L(A^k) of k = jK.. in slot
+  // k mod (K+2) (a term left pending reaches K slots back at most), then the
+  // adjoint steps of those k
+  if (!rc) rc = adjoint_step(nt, false);
   for (int j = nseg - 1; j >= 0 && !rc; --j) {
-    const int k_lo = j * K + 1, k_hi = std::min((j + 1) * K, nt);
-    if (j == 0) {
-      rc = hip_rc(launch_fill_zero(slot(0), fb, w->stream));
-      if (!rc) rc = hip_rc(launch_fill_zero(slot(1), fb, w->stream));
-    } else {
+    const int k0 = j * K, k_hi = std::min((j + 1) * K, nt);
+    if (j == 0 && nseg > 1) {
+      rc = hip_rc(launch_fill_zero(level(k0), fb, w->stream));
+      if (!rc) rc = hip_rc(launch_fill_zero(level(k0 + 1), fb, w->stream));
+    } else if (j < nseg - 1) {
       const float *ck = ckpt + 2 * static_cast<size_t>(j - 1) * w->N;
-      rc = hip_rc(hipMemcpyAsync(slot(1), ck, fb, hipMemcpyDeviceToDevice, w->stream));
-      if (!rc) rc = hip_rc(hipMemcpyAsync(slot(0), ck + w->N, fb, hipMemcpyDeviceToDevice, w->stream));
+      rc = copy(level(k0), ck);
+      if (!rc) rc = copy(level(k0 + 1), ck + w->N);
     }
-    if (!rc) rc = hip_rc(launch_set_n(w->st, j * K, w->stream));
-    // slot s holds A^{jK - 1 + s}
+    if (!rc) rc = hip_rc(launch_set_n(w->st, k0, w->stream));
     StepArgs a = base_args(w, w->fwd);
     a.wavelet = wavelet_dev;
-    for (int k = 0; k < k_hi - j * K && !rc; ++k) {
-      a.cur = slot(k + 1);
-      a.prev = slot(k);
-      a.out = slot(k + 2);
-      a.k = k;
+    for (int k = k0; k < k_hi && !rc; ++k) {
+      a.cur = level(k);
+      a.prev = level(k + 1);  // A^{k-1}, overwritten by A^{k+1}
+      a.out = level(k + 1);
+      a.lap = slot(k % (K + 2));
+      a.k = k - k0;
       rc = hip_rc(launch_step(WAVE_F32, w->fwd.variant, false, a, w->stream));
     }
-    StepArgs b = base_args(w, w->adj);
-    b.sx = -1;
-    b.img = img;
-    b.resid = resid_dev;
-    if (w->fused_rec) b.box = w->box;
-    for (int k = k_hi; k >= k_lo && !rc; --k) {
-      b.cur = mu1;
-      b.prev = mu2;
-      b.out = mu2;  // mu^k overwrites mu^{k+2}
-      b.fwd = slot(k - j * K + 1);
-      b.resid_row = k - 1;
-      rc = hip_rc(launch_step(WAVE_F32, w->adj.variant, true, b, w->stream));
-      if (!rc && !w->fused_rec && w->p.nrec > 0)
-        rc = hip_rc(launch_scatter(mu2, w->rec_node, w->rec_off, w->rec_ord, w->nrec_nodes, w->p.nrec, w->m, w->grec,
-                                   resid_dev, k - 1, w->stream));
-      std::swap(mu1, mu2);
-    }
+    for (int k = k_hi - 1; k >= std::max(k0, 1) && !rc; --k) rc = adjoint_step(k, true);
   }
   if (!rc) rc = hip_rc(launch_grad_final(img, w->m, static_cast<float>(w->p.dt), grad_vel_dev, w->rows(), w->stream));
   if (!rc) rc = do_reset(w);
