@@ -572,9 +572,9 @@ def gradient_leg(nt: int = 0, reps: int = 3) -> dict:
     misfit = 0.5 * float((resid.double() ** 2).sum())
     s.close()
     # per gradient point-step: forward with checkpoints 16 + recomputation 16 +
-    # storing it 4 + adjoint step 16 + reading the forward field 4 + the
-    # imaging accumulator read and written 8
-    bytes_per_pt_step = 64
+    # storing its Laplacian 4 + adjoint step 16 + reading the Laplacian 4 + the
+    # imaging accumulator read and written every second step 4
+    bytes_per_pt_step = 60
     return {"workload": f"{W.name}, {nt} steps, two-layer model, smoothed start, 256x256 receivers, "
                         f"checkpoint every {int(np.ceil(np.sqrt(nt)))} steps",
             "forward_s": round(t_fwd, 4), "gradient_s": round(t_grad, 4), "ratio": round(t_grad / t_fwd, 3),

@@ -1,6 +1,6 @@
 // Step-kernel templates of libwave (gfx950), shared by the translation
 // units that instantiate them: one per storage type and one for the
-// adjoint, compiled in parallel.  Included only by HIP sources.
+// gradient, compiled in parallel.  Included only by HIP sources.
 //
 //
 // The fused step evaluates the 25-point, 8th-order star Laplacian of Eq. 1

@@ -735,9 +735,9 @@ int tune_forward(wave_ctx *w) {
   w->p.src[0] = src_x;
   w->fwd = best;
   w->cpml_fused = w->cpml && variant_fuses_cpml(w->fwd.variant);
-  // Adjoint contexts: the adjoint step (two z queues, the forward field and
-  // the imaging accumulator on top of the forward step's streams) is timed on
-  // its own, with no residual, on whatever its buffers hold (wave_adjoint
+  // Adjoint contexts: the adjoint step (every second one with two kept
+  // Laplacians and the imaging accumulator on top of the forward step's
+  // streams) is timed on its own, with no residual, on whatever its buffers hold (wave_adjoint
   // clears every buffer it reads before use): every 2.5D shape at its automatic z-chunk,
   // then the z-chunk list (a shorter one) for the two fastest, the default kept unless
   // another is more than 3% faster.  All compute the same bits.
@@ -917,6 +917,9 @@ int create_ctx(const wave_params *p, const float *vel_dev, void *ws_dev, size_t 
   Layout L;
   // the static array keeps unpadded rows: every grid that fitted it still does
   int rc = plan(p, &L, static_dev < 0);
+  // so does a workspace that unpadded rows fit and padded ones don't (the
+  // library's own choice of rows must not refuse it)
+  if (!rc && p->variant == 0 && ws_bytes < L.total) rc = plan(p, &L, false);
   if (rc) return rc;
   if (reinterpret_cast<uintptr_t>(ws_dev) % 256) return WAVE_EINVAL;
   if (ws_bytes < L.total) return WAVE_ENOSPC;

@@ -2,7 +2,8 @@
 // memory, for callers that cannot allocate (code under HIP graph capture,
 // tight serving loops, harnesses that forbid hipMalloc).
 //
-// The workspace is `scratch`, a file-scope device array of WAVE_STATIC_BYTES.
+// The workspace is `scratch`, a file-scope device array of WAVE_STATIC_BYTES
+// and the maxima slots.
 // Each GPU the library runs on holds its own copy until the process ends.
 // In host code the array's name is only a stand-in for the symbol, so its
 // device address is resolved once per device with hipGetSymbolAddress and
@@ -14,7 +15,8 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = WAVE_STATIC_BYTES;
+// the maxima slots of 16-bit storage come on top of the documented limit
+constexpr size_t kScratchBytes = WAVE_STATIC_BYTES + wave::kMaxSlotBytes;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -49,7 +51,8 @@ int wave_create_static(const wave_params *p, const float *vel_dev, void *hip_str
   size_t need = 0;
   int rc = wave::static_workspace_bytes(p, &need);
   if (rc) return rc;
-  if (need > kScratchBytes) return WAVE_ENOSPC;
+  const size_t slots = p->storage == WAVE_F32 ? 0 : wave::kMaxSlotBytes;
+  if (need > WAVE_STATIC_BYTES + slots) return WAVE_ENOSPC;
   int dev = -1;
   void *ptr = nullptr;
   rc = scratch_on_current_device(&dev, &ptr);

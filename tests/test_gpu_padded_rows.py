@@ -81,3 +81,32 @@ def test_padded_gradient_and_tiling(rec_kind):
         s.close()
     assert np.abs(grads[0]).max() > 0
     assert np.array_equal(grads[1], grads[0]) and np.array_equal(grads[2], grads[0])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_workspace_for_unpadded_rows_is_enough(storage):
+    """A workspace of the unpadded size (an explicit one-node shape's) takes
+    the library's choice of shape too, with the same bits."""
+    import ctypes
+
+    from paper_2404_04441_amd import _lib as L
+
+    nx = 71
+    shape, vel, dt, nt, wav, rec = _case(nx, "list")
+    w = torch.from_numpy(wav).cuda()
+    ref = _solver(vel, dt, rec, nx, storage=storage, variant=7)
+    auto = _solver(vel, dt, rec, nx, storage=storage, tune=False)
+    assert ref.workspace_bytes < auto.workspace_bytes
+    want = [ref.run(nt, w).cpu(), ref.read_field(0).cpu(), ref.read_field(1).cpu()]
+    p, v = auto._params, torch.from_numpy(vel).cuda()
+    L.lib().wave_destroy(auto._h)
+    auto._h = ctypes.c_void_p()
+    assert L.lib().wave_create(ctypes.byref(p), v.data_ptr(), auto._ws_ptr, ref.workspace_bytes - 256,
+                               auto.stream.cuda_stream, ctypes.byref(auto._h)) == L.WAVE_ENOSPC
+    L.check(L.lib().wave_create(ctypes.byref(p), v.data_ptr(), auto._ws_ptr, ref.workspace_bytes,
+                                auto.stream.cuda_stream, ctypes.byref(auto._h)), "wave_create")
+    got = [auto.run(nt, w).cpu(), auto.read_field(0).cpu(), auto.read_field(1).cpu()]
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    auto.close()
+    ref.close()
