@@ -49,6 +49,9 @@ struct Shell {
     n2 = mz * my * cx;
   }
   __host__ __device__ unsigned count() const { return n0 + n1 + n2; }
+  // the k-th layer plane and y-layer row
+  __device__ unsigned z_at(unsigned k) const { return k < E ? k : nz - cz + k; }
+  __device__ unsigned y_at(unsigned k) const { return k < E ? k : ny - cy + k; }
   __device__ void node(unsigned t, int &x, int &y, int &z) const {
     if (t < n0) {
       const unsigned k = t / (ny * nx), r = t - k * (ny * nx);
@@ -140,8 +143,7 @@ template <int VEC> __device__ __forceinline__ void st_row(const float *v, rsrc_t
 // Every XCD takes an eighth of each part (z-layer rows, y-layer rows, nodes of
 // the x slabs), so that they end together.  Measured at 512^3, W = 20: the psi
 // update (before: a row kernel of 95 us and a column kernel of 37 us) 83 us,
-// 0.44 GB; the correction reads 0.45 instead of 0.80 GB and takes the same
-// 150 us; at 401x333x301, where a lane held one node, a whole step went from
+// 0.44 GB; the correction reads 0.45 instead of 0.80 GB; at 401x333x301, where a lane held one node, a whole step went from
 // 398 to 362 us.  Bundles of 4, 32 and 64 rows differ by 1%.
 constexpr unsigned kBundle = 32;
 
@@ -150,16 +152,18 @@ struct ShellWork {
   unsigned per0, per1, per2;  // workgroups (4 wavefronts) of each part per XCD
   unsigned rows0, rows1;      // rows of the first two parts
   unsigned nslab;             // vectors of the x slabs
+  unsigned group;             // rows of a wavefront: consecutive planes (part 0) or rows (part 1)
   FastDiv seg, bundle, last, cy, w2v;  // wavefronts per row; rows per bundle and in the last one; rows per y-layer plane; vectors per x-slab row
-  ShellWork(const CpmlArgs &c, int E, int vx) : S(E, c.nx, c.ny, c.nz) {
+  ShellWork(const CpmlArgs &c, int E, int vx, unsigned g = 1) : S(E, c.nx, c.ny, c.nz), group(g) {
+    const unsigned gz = (S.cz + g - 1) / g, gy = (S.cy + g - 1) / g;
     const unsigned nseg = (static_cast<unsigned>(c.nx) + 64 * kRowNodes - 1) / (64 * kRowNodes);
     seg = FastDiv(nseg);
-    bundle = FastDiv(S.cz * kBundle);
+    bundle = FastDiv(gz * kBundle);
     const unsigned tail = S.ny % kBundle;
     last = FastDiv(tail ? tail : kBundle);
-    cy = FastDiv(S.cy);
-    rows0 = S.cz * S.ny;
-    rows1 = S.mz * S.cy;
+    cy = FastDiv(gy);
+    rows0 = gz * S.ny;
+    rows1 = S.mz * gy;
     w2v = FastDiv(vx ? 2u * c.W / vx : 1u);
     nslab = vx ? static_cast<unsigned>(c.nz) * c.ny * (2u * c.W / vx) : 0u;
     auto share = [](size_t waves) { return static_cast<unsigned>((waves + 31) / 32); };  // 4 wavefronts, 8 XCDs
@@ -177,6 +181,7 @@ struct ShellWork {
 // over the lanes at each load.
 struct ShellAt {
   unsigned part, wave, seg;
+  unsigned k;  // the (first) row's index among the layers' planes (part 0) or rows (part 1)
   int y, z;
 };
 
@@ -185,24 +190,26 @@ __device__ __forceinline__ ShellAt shell_at(const ShellWork &P) {
   const unsigned xcd = blockIdx.x & 7u, j = blockIdx.x >> 3;
   const unsigned w = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
   ShellAt at{};
-  unsigned y = 0, z = 0;
+  unsigned y = 0, z = 0, k = 0;
   if (j < P.per0) {
     at.wave = (xcd * P.per0 + j) * 4u + w;
     const unsigned r = P.seg(at.wave);
     at.seg = at.wave - r * P.seg.d;
     const unsigned b = P.bundle(r), rem = r - b * P.bundle.d;
     const bool whole = S.ny - b * kBundle >= kBundle;
-    const unsigned k = whole ? rem / kBundle : P.last(rem);
-    y = b * kBundle + (rem - k * (whole ? kBundle : P.last.d));
-    z = k < S.E ? k : S.nz - S.cz + k;
+    const unsigned g = whole ? rem / kBundle : P.last(rem);
+    y = b * kBundle + (rem - g * (whole ? kBundle : P.last.d));
+    k = g * P.group;
+    z = S.z_at(k);
     at.part = r < P.rows0 ? 0u : 3u;
   } else if (j < P.per0 + P.per1) {
     at.wave = (xcd * P.per1 + j - P.per0) * 4u + w;
     const unsigned r = P.seg(at.wave);
     at.seg = at.wave - r * P.seg.d;
-    const unsigned k = P.cy(r), i = r - k * P.cy.d;
-    y = i < S.E ? i : S.ny - S.cy + i;
-    z = S.E + k;
+    const unsigned zi = P.cy(r);
+    k = (r - zi * P.cy.d) * P.group;
+    y = S.y_at(k);
+    z = S.E + zi;
     at.part = r < P.rows1 ? 1u : 3u;
   } else {
     at.wave = (xcd * P.per2 + j - P.per0 - P.per1) * 4u + w;
@@ -210,6 +217,7 @@ __device__ __forceinline__ ShellAt shell_at(const ShellWork &P) {
   }
   at.part = __builtin_amdgcn_readfirstlane(at.part);
   at.seg = __builtin_amdgcn_readfirstlane(at.seg);
+  at.k = __builtin_amdgcn_readfirstlane(k);
   at.y = __builtin_amdgcn_readfirstlane(static_cast<int>(y));
   at.z = __builtin_amdgcn_readfirstlane(static_cast<int>(z));
   return at;
@@ -297,20 +305,13 @@ __global__ void __launch_bounds__(256) cpml_psi_kernel(CpmlArgs c, ShellWork P, 
   }
 }
 
-// The y and z terms after the step with the x part fused in:
-// out += m * sum_{a = y, z} (D1_a psi_a + zeta_a), zeta_a updated, over the
-// rows of the first two parts of the (W + R)-node shell (the other nodes get
-// no y or z term), VEC consecutive x nodes per lane (nx % VEC == 0).  Per
-// node the same operations as cpml_fix_kernel with a0 = 1.
+// The y and z terms of one row: out += m * sum_{a = y, z} (D1_a psi_a +
+// zeta_a), zeta_a updated, VEC consecutive x nodes per lane (nx % VEC == 0).
+// Per node the same operations as cpml_fix_kernel with a0 = 1.
 template <int VEC>
-__global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, ShellWork P, const float *__restrict__ cur,
-                                                          const float *__restrict__ m, float *out) {
-  const ShellAt at = shell_at(P);
-  if (at.part >= 2) return;
-  const unsigned seg = at.seg;
-  const int y = at.y, z = at.z;
+__device__ __forceinline__ void fix_row(const CpmlArgs &c, const float *cur, const float *m, float *out, int y, int z,
+                                        uint32_t xo) {
   const unsigned nx = c.nx, ny = c.ny, W2 = 2u * c.W;
-  const uint32_t xo = seg * (64u * kRowNodes * 4u) + (threadIdx.x & 63u) * (VEC * 4u);
   const size_t o = (static_cast<size_t>(z) * ny + static_cast<unsigned>(y)) * nx;
   const float *row = cur + o;
   const rsrc_t ro = row_at(out + o, true, nx);
@@ -375,6 +376,121 @@ __global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, ShellWork 
 #pragma unroll
   for (int e = 0; e < kRowNodes; ++e) res[e] = fmaf(mv.at(e), extra[e], ov.at(e));
   st_row<VEC>(res, ro, xo);
+}
+
+// A lane's vectors of a row as offsets into a resource of several rows: past
+// the row's end, out of every resource.
+template <int VEC> struct RowOff {
+  uint32_t o[kRowNodes / VEC];
+  __device__ RowOff(uint32_t xo, unsigned nx) {
+#pragma unroll
+    for (int k = 0; k < kRowNodes / VEC; ++k) {
+      const uint32_t x = xo + k * (256u * VEC);
+      o[k] = x < nx * 4u ? x : kOOB;
+    }
+  }
+  // the row at byte `at` (zeros if not in)
+  __device__ Row<VEC> ld(rsrc_t r, uint32_t at, bool in) const {
+    Row<VEC> out;
+#pragma unroll
+    for (int k = 0; k < kRowNodes / VEC; ++k) out.v[k] = ld_words<VEC * 4, 0>(r, in ? o[k] : kOOB, in ? at : 0u);
+    return out;
+  }
+  __device__ void st(const float *v, rsrc_t r, uint32_t at) const {
+#pragma unroll
+    for (int k = 0; k < kRowNodes / VEC; ++k) st_words<VEC * 4, 0>(row_put<kF32, VEC>(v + k * VEC), r, o[k], at);
+  }
+};
+
+// The same for G consecutive rows along axis A (1: y, 2: z) that have that
+// axis' terms alone, each psi and A^n row of their window loaded once.  One
+// resource per array (the window's rows or the axis' slab, each below 2^31
+// bytes) and a scalar offset per row: a resource per row spilled 300 scalar
+// registers.
+template <int VEC, int A, int G>
+__device__ __forceinline__ void fix_rows(const CpmlArgs &c, const float *cur, const float *m, float *out, int y, int z,
+                                         uint32_t xo) {
+  const unsigned nx = c.nx, ny = c.ny, W2 = 2u * c.W;
+  const int i0 = A == 1 ? y : z, n = A == 1 ? c.ny : c.nz;
+  const size_t o = (static_cast<size_t>(z) * ny + static_cast<unsigned>(y)) * nx;
+  const uint32_t row = nx * 4u, stride = A == 1 ? row : row * ny;
+  const RowOff<VEC> off(xo, nx);
+  // byte of the row of slab index s: y: (z, s), z: (s, y)
+  auto slab = [&](int s) { return (A == 1 ? static_cast<uint32_t>(z) * W2 + s : s * ny + static_cast<uint32_t>(y)) * row; };
+  const uint32_t slab_bytes = (A == 1 ? static_cast<uint32_t>(c.nz) : ny) * W2 * row;
+  const rsrc_t rs = make_rsrc(c.psi[A], slab_bytes), rz = make_rsrc(c.zeta[A], slab_bytes);
+  const int b = max(i0 - R, 0), top = min(i0 + G - 1 + R, n - 1);  // the window's rows within the grid
+  const rsrc_t ru = make_rsrc(cur + o - static_cast<size_t>(i0 - b) * (stride / 4u), static_cast<uint32_t>(top - b) * stride + row);
+  const rsrc_t rm = make_rsrc(m + o, (G - 1) * stride + row), ro = make_rsrc(out + o, (G - 1) * stride + row);
+  bool layer = false;  // rows with zeta_a (and a second difference) among them
+#pragma unroll
+  for (int j = 0; j < G; ++j) layer |= slab_index(i0 + j, n, c.W) >= 0;
+  Row<VEC> ps[G + 2 * R], u[G + 2 * R], mv[G], ov[G], zv[G];
+#pragma unroll
+  for (int k = 0; k < G + 2 * R; ++k) {
+    const int i = i0 + k - R, s = slab_index(i, n, c.W);
+    ps[k] = off.ld(rs, slab(s), s >= 0);
+    u[k] = off.ld(ru, static_cast<uint32_t>(i - b) * stride, layer && i >= 0 && i < n);
+  }
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    const int s = slab_index(i0 + j, n, c.W);
+    zv[j] = off.ld(rz, slab(s), s >= 0);
+    mv[j] = off.ld(rm, j * stride, true);
+    ov[j] = off.ld(ro, j * stride, true);
+  }
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    const int s = slab_index(i0 + j, n, c.W);
+    const float ca = c.ca[A][i0 + j], cb = c.cb[A][i0 + j];
+    float zn[kRowNodes], res[kRowNodes];
+#pragma unroll
+    for (int e = 0; e < kRowNodes; ++e) {
+      const float cc = u[j + R].at(e);
+      float dpsi = 0.f, d2 = 0.f;  // d2: second differences from the centre (no large centre term)
+#pragma unroll
+      for (int k = 1; k <= R; ++k) {
+        dpsi = fmaf(c.d1w[A][k - 1], ps[j + R + k].at(e) - ps[j + R - k].at(e), dpsi);
+        d2 = fmaf(c.d2w[A][k], (u[j + R + k].at(e) - cc) + (u[j + R - k].at(e) - cc), d2);
+      }
+      zn[e] = fmaf(cb, zv[j].at(e), ca * (d2 + dpsi));
+      const float extra = 0.f + (s < 0 ? dpsi : dpsi + zn[e]);  // beyond the layer: D1 psi alone
+      res[e] = fmaf(mv[j].at(e), extra, ov[j].at(e));
+    }
+    if (s >= 0) off.st(zn, rz, slab(s));
+    off.st(res, ro, j * stride);
+  }
+}
+
+// The y and z terms after the step with the x part fused in, over the rows of
+// the first two parts of the (W + R)-node shell (the other nodes get no y or z
+// term).  A wavefront takes kFixRows rows along the axis of its layer: with
+// one row each it was bound by its loads through L1 and L2, 16 neighbour rows
+// of psi and A^n for every row, of which neighbouring rows share most: four
+// rows together need 24 where they loaded 68.  Rows with both terms (edges of the box) and groups across the end of a
+// layer go row by row.  Measured, a whole CPML step, one row and four rows per
+// wavefront: 512^3 647 -> 626 us, 401x333x301 362 -> 355 us, 256^3 and
+// 300x99x174 equal.
+constexpr unsigned kFixRows = 4;
+template <int VEC>
+__global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, ShellWork P, const float *__restrict__ cur,
+                                                          const float *__restrict__ m, float *out) {
+  const ShellAt at = shell_at(P);
+  if (at.part >= 2) return;
+  const Shell &S = P.S;
+  const uint32_t xo = at.seg * (64u * kRowNodes * 4u) + (threadIdx.x & 63u) * (VEC * 4u);
+  const int y = at.y, z = at.z;
+  const unsigned k1 = at.k + kFixRows - 1, count = at.part == 0 ? S.cz : S.cy;
+  const int E = c.W + R;
+  if (at.part == 0) {
+    if (k1 < count && S.z_at(k1) == z + kFixRows - 1 && y >= E && y < c.ny - E)
+      return fix_rows<VEC, 2, kFixRows>(c, cur, m, out, y, z, xo);
+  } else if (k1 < count && S.y_at(k1) == y + kFixRows - 1) {
+    return fix_rows<VEC, 1, kFixRows>(c, cur, m, out, y, z, xo);
+  }
+  for (unsigned k = at.k; k <= k1 && k < count; ++k)
+    fix_row<VEC>(c, cur, m, out, at.part == 0 ? y : static_cast<int>(S.y_at(k)),
+                 at.part == 0 ? static_cast<int>(S.z_at(k)) : z, xo);
 }
 
 // One thread per node within W + R of a face, adding the terms of axes
@@ -1007,7 +1123,7 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
   const Shell S(c.W + kRadius, c.nx, c.ny, c.nz);
   if (yz_only) {
     const int vec = lane_width(c.nx, 4);
-    const ShellWork P(c, c.W + kRadius, 0);
+    const ShellWork P(c, c.W + kRadius, 0, kFixRows);
     const dim3 g(P.grid()), b(256);
     if (vec == 4) hipLaunchKernelGGL(cpml_fix_yz_kernel<4>, g, b, 0, s, c, P, cur, m, out);
     else if (vec == 2) hipLaunchKernelGGL(cpml_fix_yz_kernel<2>, g, b, 0, s, c, P, cur, m, out);
