@@ -302,7 +302,7 @@ __device__ __forceinline__ void max_slots(const uint32_t *slots, int level, uint
 
 constexpr int kFarScales = 40;  // factors up to 2^40 keep every product of the step in range
 
-// 16-bit storage with exponents far apart: the step on the nodes of one
+// f16 storage with exponents far apart: the step on the nodes of one
 // workgroup's column, in true units, every stencil value loaded on its own.
 // The operations and their order are the main loop's, so the bits are the
 // ones it would give if its factors did not overflow.
@@ -727,14 +727,24 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // decoding a value multiplies nothing and the scales enter once per node
   // through m (2^(ev-ea)) and the factors of the stores.  Scaling by powers
   // of two is exact, so the bits are those of the update in true units.
+  // bf16 is the exception: its exponent range is float32's, so that the far
+  // tails of a wave are float32 subnormals in true units and rounded there;
+  // it decodes to true units (kTrue: two multiplications more per node).  At
+  // 1024^3 with 16-bit m 2260 us a step before both, 2050 us now; f16 at 512^3
+  // 294 and 290 us, both on fields of waves.
   // Where the exponents lie so far apart that a factor could overflow (fields
   // set to arbitrary scales by wave_write_field), the chunk is advanced in
   // true units, node by node (step_far).
   const int n = ADJ ? 0 : a.st->n + a.k;
   bool far = false;
   int ea = 0, ev = 0, ea_next = 0, ev_next = 0;
+  constexpr bool kTrue = S == kBF16;
+  float ua = 1.f, uv = 1.f;  // kTrue: 2^-ea, 2^-ev
+  auto dec_a = [&](auto raw, int i) __attribute__((always_inline)) {
+    return kTrue ? row_get<S>(raw, i) * ua : row_get<S>(raw, i);
+  };
   float m_unit = 1.f, v_unit = 1.f, inv_next = 1.f;
-  float out_a = 1.f, out_va = 1.f, out_v = 1.f;  // 2^(ea_next - ea), 2^(ea_next - ev), 2^(ev_next - ev)
+  float out_a = 1.f, out_va = 1.f, out_v = 1.f;  // 2^(ea_next - ea), 2^(ea_next - ev), 2^(ev_next - ev); kTrue: 1, 2^ea_next, 2^ev_next
   if constexpr (S != kF32) {
     ea = a.st->exps[n & 3];
     ev = a.st->exps_v[n & 3];
@@ -746,9 +756,19 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const float bv = a_v + a.gamma * a_a + qmag;
     ea_next = scale_exponent(a_a + bv);
     ev_next = scale_exponent(bv);
+    // A field of zeros (a shot's first step, from rest) is zero at any scale:
+    // it takes the next level's, else that step would be a far one (8.4 ms
+    // instead of 0.3 ms at 512^3).
+    if (ma == 0u) ea = ea_next;
+    if (mv == 0u) ev = ev_next;
     const int apart = max(max(abs(ev - ea), abs(ea_next - ea)), max(abs(ea_next - ev), abs(ev_next - ev)));
-    far = __builtin_amdgcn_readfirstlane(apart) > kFarScales;
-    if (!far) {
+    far = !kTrue && __builtin_amdgcn_readfirstlane(apart) > kFarScales;
+    if constexpr (kTrue) {
+      ua = exp2i(-ea);
+      uv = exp2i(-ev);
+      out_va = exp2i(ea_next);
+      out_v = exp2i(ev_next);
+    } else if (!far) {
       m_unit = exp2i(ev - ea);
       v_unit = exp2i(ev);
       out_a = exp2i(ea_next - ea);
@@ -775,7 +795,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
     for (int j = 0; j < RY; ++j)
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) q[k][j][i] = row_get<S>(pq[k][j], i);
+      for (int i = 0; i < VEC; ++i) q[k][j][i] = dec_a(pq[k][j], i);
   if constexpr (LEADH) {  // ring slots 0 .. R-1: planes zb .. zb+R-1 with their halo
 #pragma unroll
     for (int k = 0; k < R; ++k) {
@@ -786,10 +806,10 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       for (int i = 0; i < NYH; ++i) {
         float v[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = row_get<S>(pyh[k][i], e);
+        for (int e = 0; e < VEC; ++e) v[e] = dec_a(pyh[k][i], e);
         lds_put<VEC>(Lk + yhlds[i], v);
       }
-      Lk[xhlds] = row_get<S>(pxh[k], 0);
+      Lk[xhlds] = dec_a(pxh[k], 0);
     }
   }
   // semi-stencil partials: slot (p - zb + R) mod 9 holds sum_m kz_m A(p-m) of plane p
@@ -947,8 +967,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     }
   };
 
-  if (S != kF32 && far)
-    step_far<S, M16, kSumForm>(a, n, x0, y0, TX, TY, zb, zend, ea, ev, ea_next, ev_next, amax_loc, amaxv_loc);
+  if constexpr (S != kF32 && !kTrue)
+    if (far) step_far<S, M16, kSumForm>(a, n, x0, y0, TX, TY, zb, zend, ea, ev, ea_next, ev_next, amax_loc, amaxv_loc);
   for (int zs = far ? ze : zb; zs < ze; zs += kQ) {
     // nine planes per trip with compile-time queue slots and stage indices, so
     // the queue rotates by register renaming (a runtime index would move the
@@ -968,7 +988,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) q[(s + 2 * R) % kQ][j][i] = row_get<S>(cs.lead[j], i);
+        for (int i = 0; i < VEC; ++i) q[(s + 2 * R) % kQ][j][i] = dec_a(cs.lead[j], i);
         lds_put<VEC>(Lw + (R + w * RY + j) * LW + R + VEC * lane, q[LEADH ? (s + 2 * R) % kQ : cslot][j]);
         if constexpr (SEMI) {  // left half of plane z+R from planes z .. z+R-1
 #pragma unroll
@@ -985,10 +1005,10 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       for (int k = 0; k < NYH; ++k) {
         float t[VEC];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) t[i] = row_get<S>(cs.yh[k], i);
+        for (int i = 0; i < VEC; ++i) t[i] = dec_a(cs.yh[k], i);
         lds_put<VEC>(Lw + yhlds[k], t);
       }
-      Lw[xhlds] = row_get<S>(cs.xh, 0);
+      Lw[xhlds] = dec_a(cs.xh, 0);
       float *Lpsi = ldsX[CP ? par : 0];
       float zex[CP ? RY : 1][CP ? VEC : 1];
       if constexpr (CP) {
@@ -1006,13 +1026,13 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
       for (int j = 0; j < RY; ++j)
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-          pc[j][i] = row_get<S>(cs.p[j], i);
+          pc[j][i] = kTrue ? row_get<S>(cs.p[j], i) * uv : row_get<S>(cs.p[j], i);
           if constexpr (M16) {
             const uint32_t u = (cs.m[j].w[i >> 1] >> (16 * (i & 1))) & 0xffffu;
             mc[j][i] = fmaf(static_cast<float>(u), m_step, m_lo);
           } else {
             mc[j][i] = __uint_as_float(cs.m[j].w[i]);
-            if constexpr (S != kF32) mc[j][i] *= m_unit;
+            if constexpr (S != kF32 && !kTrue) mc[j][i] *= m_unit;
           }
           if constexpr (IMG)
             im[j][i] = fmaf(q[cslot][j][i], __uint_as_float(cs.la0[j].w[i]),
@@ -1099,7 +1119,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
             v[i] = vn;
           } else {
             vv[i] = vn * out_v;
-            v[i] = fmaf(gxa[i] * gyz, q[cslot][j][i], vn * out_va);
+            v[i] = kTrue ? fmaf(gxv[i] * gyz, q[cslot][j][i], vn) * out_va
+                         : fmaf(gxa[i] * gyz, q[cslot][j][i], vn * out_va);
           }
         }
         if constexpr (S == kF32) {
