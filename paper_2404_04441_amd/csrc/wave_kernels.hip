@@ -938,6 +938,14 @@ __global__ void zero_kernel(uint4 *p, size_t n16, uint8_t *tail, size_t ntail) {
   if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
 }
 
+// The columns that pad a field's rows, set to zero.
+template <typename T>
+__global__ void zero_padding_kernel(T *f, int nx, int pitch, size_t rows) {
+  for (size_t r = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; r < rows;
+       r += static_cast<size_t>(gridDim.x) * blockDim.x)
+    for (int x = nx; x < pitch; ++x) f[r * pitch + x] = 0;
+}
+
 unsigned grid_for(size_t n, unsigned block) {
   const size_t want = (n + block - 1) / block;
   const size_t cap = 256 * 64;  // enough workgroups to cover all CUs many times over
@@ -1133,6 +1141,16 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
   const unsigned n = S.count();
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(cpml_fix_kernel, dim3((n + 255) / 256), dim3(256), 0, s, c, cur, m, out, 0, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero_padding(int storage, void *field, const GridRows &g, hipStream_t s) {
+  if (g.pitch == g.nx) return hipSuccess;
+  const dim3 grid(grid_for(g.rows, 256)), b(256);
+  if (storage == kF32)
+    hipLaunchKernelGGL(zero_padding_kernel<float>, grid, b, 0, s, static_cast<float *>(field), g.nx, g.pitch, g.rows);
+  else
+    hipLaunchKernelGGL(zero_padding_kernel<uint16_t>, grid, b, 0, s, static_cast<uint16_t *>(field), g.nx, g.pitch, g.rows);
   return hipGetLastError();
 }
 

@@ -1264,11 +1264,13 @@ int wave_write_field(wave_t w, int32_t which, const float *in_dev) {
   if (w->p.storage == WAVE_F32) {
     if (which < 0 || which > 1) return WAVE_EINVAL;
     void *dst = w->field(which == 0 ? w->n : w->n + 3);
-    return hip_rc(launch_copy_in(in_dev, static_cast<float *>(dst), w->rows(), w->stream));
+    const int rc = hip_rc(launch_copy_in(in_dev, static_cast<float *>(dst), w->rows(), w->stream));
+    return rc ? rc : hip_rc(launch_zero_padding(w->p.storage, dst, w->rows(), w->stream));
   }
   if (which != 0 && which != 2) return WAVE_EINVAL;  // 16-bit storage keeps A^n and V^n
-  return hip_rc(launch_encode_field(w->p.storage, in_dev, which == 0 ? w->field(w->n) : w->fv, w->rows(),
-                                    w->st, w->slots, which == 2, w->stream));
+  void *dst = which == 0 ? w->field(w->n) : w->fv;
+  const int rc = hip_rc(launch_encode_field(w->p.storage, in_dev, dst, w->rows(), w->st, w->slots, which == 2, w->stream));
+  return rc ? rc : hip_rc(launch_zero_padding(w->p.storage, dst, w->rows(), w->stream));
 }
 
 // Snapshot layout: 256-B header | step state | A fields 0 and 1 | V (16-bit)
@@ -1374,8 +1376,10 @@ int wave_load_state(wave_t w, const void *src_dev) {
     fields[1] = w->field(h.n + 3);
   }
   const int nfields = w->p.storage == WAVE_F32 ? 2 : 3;
-  for (int k = 0; k < nfields && !rc; ++k, off += align256(fb))
+  for (int k = 0; k < nfields && !rc; ++k, off += align256(fb)) {
     rc = hip_rc(copy_rows(w, const_cast<char *>(src) + off, fields[k], false));
+    if (!rc) rc = hip_rc(launch_zero_padding(w->p.storage, fields[k], w->rows(), w->stream));
+  }
   for (int a = 0; a < 3 && w->cpml && !rc; ++a) {
     rc = hip_rc(hipMemcpyAsync(w->ws + w->L.cpml_slab[a], src + off, slab_bytes(w, a), hipMemcpyDeviceToDevice,
                                w->stream));
