@@ -153,6 +153,7 @@ struct ShellWork {
   unsigned rows0, rows1;      // rows of the first two parts
   unsigned nslab;             // vectors of the x slabs
   unsigned group;             // rows of a wavefront: consecutive planes (part 0) or rows (part 1)
+  unsigned first = 0;         // this launch's first workgroup of each XCD's run
   FastDiv seg, bundle, last, cy, w2v;  // wavefronts per row; rows per bundle and in the last one; rows per y-layer plane; vectors per x-slab row
   ShellWork(const CpmlArgs &c, int E, int vx, unsigned g = 1) : S(E, c.nx, c.ny, c.nz), group(g) {
     const unsigned gz = (S.cz + g - 1) / g, gy = (S.cy + g - 1) / g;
@@ -171,7 +172,13 @@ struct ShellWork {
     per1 = share(size_t(rows1) * nseg);
     per2 = share((size_t(nslab) + 63) / 64);
   }
-  unsigned grid() const { return 8 * (per0 + per1 + per2); }
+  // launch(grid, work) until every workgroup had its turn: one launch but for
+  // grids of tens of millions of rows, as a launch holds fewer than 2^32 threads
+  template <typename F> void run(F &&launch) {
+    constexpr unsigned kMost = 1u << 20;  // per XCD: 2^31 threads a launch
+    const unsigned n = per0 + per1 + per2;
+    for (first = 0; first < n; first += kMost) launch(dim3(8 * (n - first < kMost ? n - first : kMost)), *this);
+  }
 };
 
 // This wavefront's part, its index there and, in the row parts, its row: part
@@ -187,7 +194,7 @@ struct ShellAt {
 
 __device__ __forceinline__ ShellAt shell_at(const ShellWork &P) {
   const Shell &S = P.S;
-  const unsigned xcd = blockIdx.x & 7u, j = blockIdx.x >> 3;
+  const unsigned xcd = blockIdx.x & 7u, j = P.first + (blockIdx.x >> 3);
   const unsigned w = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
   ShellAt at{};
   unsigned y = 0, z = 0, k = 0;
@@ -840,8 +847,10 @@ hipError_t launch_rows(Op op, const void *user, const GridRows &g, bool reduces,
   map.total = static_cast<unsigned>(rows * nseg);
   const bool vec = map.len % 4 == 0 && g.pitch % 4 == 0 && (one || g.nx % 4 == 0) && reinterpret_cast<uintptr_t>(user) % 16 == 0;
   const unsigned want = (map.total + 3) / 4;
-  // a reduction ends in an atomic per workgroup: 8 workgroups per CU read the array
-  const dim3 grid(reduces && want > 2048 ? 2048u : want), b(256);
+  // a reduction ends in an atomic per workgroup: 8 workgroups per CU read the
+  // array; else one access per wavefront, within the 2^32 threads of a launch
+  const unsigned most = reduces ? 2048u : 1u << 22;
+  const dim3 grid(want < most ? want : most), b(256);
   if (vec) hipLaunchKernelGGL((rows_kernel<4, Op>), grid, b, 0, s, op, map);
   else hipLaunchKernelGGL((rows_kernel<1, Op>), grid, b, 0, s, op, map);
   return hipGetLastError();
@@ -1107,11 +1116,13 @@ hipError_t launch_grad_final(const float *img, const float *m, float dt, float *
 
 namespace {
 template <int VEC>
-void launch_psi(int vx, const ShellWork &P, const CpmlArgs &c, const float *cur, hipStream_t s) {
-  const dim3 g(P.grid()), b(256);
-  if (vx == 4) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 4>), g, b, 0, s, c, P, cur);
-  else if (vx == 2) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 2>), g, b, 0, s, c, P, cur);
-  else hipLaunchKernelGGL((cpml_psi_kernel<VEC, 1>), g, b, 0, s, c, P, cur);
+void launch_psi(int vx, ShellWork &work, const CpmlArgs &c, const float *cur, hipStream_t s) {
+  const dim3 b(256);
+  work.run([&](dim3 g, const ShellWork &P) {
+    if (vx == 4) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 4>), g, b, 0, s, c, P, cur);
+    else if (vx == 2) hipLaunchKernelGGL((cpml_psi_kernel<VEC, 2>), g, b, 0, s, c, P, cur);
+    else hipLaunchKernelGGL((cpml_psi_kernel<VEC, 1>), g, b, 0, s, c, P, cur);
+  });
 }
 // x nodes per lane: as many of 4, 2, 1 as divide every length given
 int lane_width(int a, int b) { return a % 4 == 0 && b % 4 == 0 ? 4 : (a % 2 == 0 && b % 2 == 0 ? 2 : 1); }
@@ -1119,7 +1130,7 @@ int lane_width(int a, int b) { return a % 4 == 0 && b % 4 == 0 ? 4 : (a % 2 == 0
 
 hipError_t launch_cpml_psi(const CpmlArgs &c, const float *cur, hipStream_t s) {
   const int vec = lane_width(c.nx, 4), vx = lane_width(c.nx, c.W);
-  const ShellWork P(c, c.W, vx);
+  ShellWork P(c, c.W, vx);
   if (vec == 4) launch_psi<4>(vx, P, c, cur, s);
   else if (vec == 2) launch_psi<2>(vx, P, c, cur, s);
   else launch_psi<1>(vx, P, c, cur, s);
@@ -1131,11 +1142,13 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
   const Shell S(c.W + kRadius, c.nx, c.ny, c.nz);
   if (yz_only) {
     const int vec = lane_width(c.nx, 4);
-    const ShellWork P(c, c.W + kRadius, 0, kFixRows);
-    const dim3 g(P.grid()), b(256);
-    if (vec == 4) hipLaunchKernelGGL(cpml_fix_yz_kernel<4>, g, b, 0, s, c, P, cur, m, out);
-    else if (vec == 2) hipLaunchKernelGGL(cpml_fix_yz_kernel<2>, g, b, 0, s, c, P, cur, m, out);
-    else hipLaunchKernelGGL(cpml_fix_yz_kernel<1>, g, b, 0, s, c, P, cur, m, out);
+    ShellWork work(c, c.W + kRadius, 0, kFixRows);
+    const dim3 b(256);
+    work.run([&](dim3 g, const ShellWork &P) {
+      if (vec == 4) hipLaunchKernelGGL(cpml_fix_yz_kernel<4>, g, b, 0, s, c, P, cur, m, out);
+      else if (vec == 2) hipLaunchKernelGGL(cpml_fix_yz_kernel<2>, g, b, 0, s, c, P, cur, m, out);
+      else hipLaunchKernelGGL(cpml_fix_yz_kernel<1>, g, b, 0, s, c, P, cur, m, out);
+    });
     return hipGetLastError();
   }
   const unsigned n = S.count();
