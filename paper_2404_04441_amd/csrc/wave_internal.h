@@ -133,7 +133,9 @@ struct StepArgs {
 };
 
 // The rows of a caller's array (nx nodes each) and the pitch of the
-// workspace's rows.
+// workspace's rows.  Columns nx .. pitch-1 pad a field's rows.  A step leaves
+// them zero only while the field is finite (it stores g t there with g = 0):
+// whatever sets a field anew sets them to zero too.
 struct GridRows {
   int nx, pitch;
   size_t rows;  // ny nz
@@ -192,10 +194,9 @@ hipError_t launch_check_finite(int storage, const void *field, size_t n, StepSta
 hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, const GridRows &g,
                              hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
-// the columns that pad a field's rows := 0 (nothing where they have none).  A
-// step leaves them zero only while the field is finite (it stores g t with g =
-// 0 there): whatever sets a field anew sets them too.
-hipError_t launch_zero_padding(int storage, void *field, const GridRows &g, hipStream_t s);
+// the rows of a field to (from) a snapshot, which holds them without padding
+// and starts at any byte
+hipError_t launch_copy_rows(int storage, void *snap, void *field, const GridRows &g, bool save, hipStream_t s);
 // n field values (storage type) to time candidate configurations on
 hipError_t launch_noise(int storage, void *field, size_t n, uint32_t seed, hipStream_t s);
 // psi_a^n = b psi_a^{n-1} + a D1_a cur, on the W-node layers

@@ -544,80 +544,156 @@ __global__ void __launch_bounds__(256) cpml_fix_kernel(CpmlArgs c, const float *
 // ------------------------------------------------------------ conversion passes
 //
 // Copies, conversions and reductions between the caller's arrays (rows of nx
-// floats) and the workspace's fields (rows of their pitch): one wavefront per
-// 256 consecutive nodes of a row, in four-node vectors where both sides are
-// aligned for them (arrays without row padding count as one row), else one
-// node per lane and access.  Bound by memory: one 16-byte access per lane and
-// array in many short workgroups, the form that streams fastest here.  Against
-// one node per lane and access in a strided loop, 1024^3 bf16: reading a field
-// 1937 -> 1080 us, its maximum 1165 -> 773 us, encoding it 1509 -> 1105 us.  The
-// set-up of m at 256^3, which queued two atomics per workgroup on one line:
-// 378 -> 34 us.
-struct RowMap {
-  FastDiv seg;       // wavefronts per row
-  unsigned total;    // wavefronts
-  size_t len;        // nodes per row
-  size_t nu, nf;     // row pitch of the caller's array and of the field
+// nodes) and the workspace's fields (rows of their pitch): a lane takes four
+// consecutive nodes, as one vector on both sides.  A pass that sets a field
+// goes through the field's vectors and loads the caller's nodes where they
+// start, at any element (which a global access may); the columns that pad a row
+// become zero.  A pass that reads one goes through the caller's vectors; one
+// that lies across the end of a row takes the two parts from two loads.  Arrays
+// without row padding count as one row.  Bound by memory: one access per lane
+// and array in many short workgroups, the form that streams fastest here.
+// Against one node per lane and access in a strided loop, 1024^3 bf16: reading a
+// field 1937 -> 1080 us, its maximum 1165 -> 773 us, encoding it 1509 -> 1105 us.
+// The set-up of m at 256^3, which queued two atomics per workgroup on one line:
+// 378 -> 34 us.  Rows of a vector each, a wavefront per row and single accesses
+// in padded rows, took 2 to 14 times as long where rows are short or padded: A^{n-1}
+// of 4x2048x2048 f16 783 -> 40 us, reading 33x896x896 f32 87 -> 41 us, writing it
+// 133 -> 44 us, and a snapshot of 301x512x512 f16, then copied by
+// hipMemcpy2DAsync, 1208 -> 227 us.
+
+// n / d for n d < 2^64.
+struct FastDiv64 {
+  unsigned d;
+  uint64_t m;
+  explicit FastDiv64(unsigned div = 1) : d(div), m(~uint64_t(0) / div + 1) {}  // d = 1: m = 0, not used
+  __host__ __device__ uint64_t operator()(uint64_t n) const {
+    return d == 1 ? n : static_cast<uint64_t>((static_cast<unsigned __int128>(n) * m) >> 64);
+  }
 };
 
-template <int V> __device__ __forceinline__ void nt_get(const float *p, float *v) {
-  if constexpr (V == 4) {
-    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-    v[0] = t.x;
-    v[1] = t.y;
-    v[2] = t.z;
-    v[3] = t.w;
-  } else {
-    v[0] = __builtin_nontemporal_load(p);
-  }
-}
-template <int V> __device__ __forceinline__ void nt_put(float *p, const float *v) {
-  if constexpr (V == 4)
-    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(p));
-  else
-    __builtin_nontemporal_store(v[0], p);
-}
-// V stored values of type S at p, decoded (unscaled), and the inverse.
-template <int S, int V> __device__ __forceinline__ void field_get(const typename Codec<S>::raw *p, float *v) {
-  if constexpr (S == kF32) {
-    lds_get<V>(p, v);
-  } else if constexpr (V == 4) {
-    const u32x2 t = *reinterpret_cast<const u32x2 *>(p);
-    const Words<8> w{{t.x, t.y}};
+struct RowMap {
+  size_t total;     // nodes of the caller's array
+  size_t nvec;      // vectors gone through: of the field (set), of the caller's array (read)
+  unsigned nx, pitch;
+  FastDiv64 row;    // vectors per row of the field (set), nodes per row of the caller's array (read)
+  FastDiv in_row;   // the same for indices within a row and a wavefront
+};
+
+// Four values of type T at an address aligned to ALIGN bytes, or the first n
+// of them (single accesses).
+template <int ALIGN, bool NT, typename T> __device__ __forceinline__ void get4(const T *p, T (&v)[4]) {
+  typedef T four __attribute__((ext_vector_type(4), aligned(ALIGN)));
+  const four *q = reinterpret_cast<const four *>(p);
+  const four t = NT ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = row_get<S>(w, e);
-  } else {
-    v[0] = Codec<S>::dec(p[0]);
-  }
+  for (int e = 0; e < 4; ++e) v[e] = t[e];
 }
-template <int S, int V> __device__ __forceinline__ void field_put(typename Codec<S>::raw *p, const float *v) {
+template <int ALIGN, bool NT, typename T> __device__ __forceinline__ void put4(T *p, const T (&v)[4]) {
+  typedef T four __attribute__((ext_vector_type(4), aligned(ALIGN)));
+  four t;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t[e] = v[e];
+  four *q = reinterpret_cast<four *>(p);
+  if constexpr (NT) __builtin_nontemporal_store(t, q);
+  else *q = t;
+}
+template <int ALIGN, bool NT, typename T> __device__ __forceinline__ void get4(const T *p, T (&v)[4], unsigned n) {
+  typedef T one __attribute__((aligned(ALIGN)));
+  if (n >= 4u) return get4<ALIGN, NT>(p, v);
+#pragma unroll
+  for (unsigned e = 0; e < 4u; ++e) v[e] = e < n ? reinterpret_cast<const one *>(p)[e] : T(0);
+}
+template <int ALIGN, bool NT, typename T> __device__ __forceinline__ void put4(T *p, const T (&v)[4], unsigned n) {
+  typedef T one __attribute__((aligned(ALIGN)));
+  if (n >= 4u) return put4<ALIGN, NT>(p, v);
+#pragma unroll
+  for (unsigned e = 0; e < 4u; ++e)
+    if (e < n) reinterpret_cast<one *>(p)[e] = v[e];
+}
+// Four values encoded in storage type S.
+template <int S> __device__ __forceinline__ void encode4(const float (&v)[4], typename Codec<S>::raw (&r)[4]) {
   if constexpr (S == kF32) {
-    lds_put<V>(p, v);
-  } else if constexpr (V == 4) {
-    const Words<8> w = row_put<S, 4>(v);
-    *reinterpret_cast<u32x2 *>(p) = u32x2{w.w[0], w.w[1]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = v[e];
   } else {
-    p[0] = Codec<S>::enc(v[0]);
+    const Words<8> w = row_put<S, 4>(v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = static_cast<uint16_t>(w.w[e >> 1] >> (16 * (e & 1)));
   }
 }
 
-// Op::run<V>(u, f, row, col): V nodes at index u of the caller's array and f
-// of the field; Op::finish() once per thread.
-template <int V, class Op>
-__global__ void __launch_bounds__(256) rows_kernel(Op op, RowMap map) {
+// Passes that set a field or reduce over the caller's array.  Op::in(u, v, n):
+// n of four nodes from index u of the caller's array; Op::set(f, v, n, k): k of
+// four nodes of the field from index f, which hold v[0 .. n) and zeros;
+// Op::finish() once per thread.
+template <bool FLAT, class Op>
+__global__ void __launch_bounds__(256) set_kernel(Op op, RowMap map) {
   const unsigned lane = threadIdx.x & 63u;
-  const unsigned w0 = blockIdx.x * 4u + static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
-  for (unsigned w = w0; w < map.total; w += gridDim.x * 4u) {
-    const unsigned row = map.seg(w);
-    const size_t at = static_cast<size_t>(w - row * map.seg.d) * 256u;
-#pragma unroll
-    for (int k = 0; k < 4 / V; ++k) {
-      const size_t col = at + k * (64u * V) + lane * V;
-      if (col < map.len) op.template run<V>(row * map.nu + col, row * map.nf + col, row, col);
+  const unsigned wave = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
+  for (size_t t0 = (static_cast<size_t>(blockIdx.x) * 4u + wave) * 64u; t0 < map.nvec; t0 += static_cast<size_t>(gridDim.x) * 256u) {
+    if (t0 + lane >= map.nvec) break;
+    const size_t f = (t0 + lane) * 4u;
+    size_t u = f;
+    unsigned n = 4u;
+    if constexpr (!FLAT) {
+      const uint64_t r0 = map.row(t0);
+      const unsigned i = static_cast<unsigned>(t0 - r0 * map.row.d) + lane, k = map.in_row(i);
+      const unsigned col = (i - k * map.in_row.d) * 4u;
+      u = (r0 + k) * map.nx + col;
+      n = min(4u, map.nx - col);
     }
+    // the nodes past a row's end are the next row's, but for the array's last
+    const unsigned have = static_cast<unsigned>(min(map.total - u, size_t(4)));
+    typename Op::T v[4];
+    op.in(u, v, have);
+    if constexpr (FLAT) op.set(f, v, have, have);
+    else op.set(f, v, n, 4u);
   }
   op.finish();
 }
+
+// Passes that read a field.  Op::at(f, v): four stored nodes of the field from
+// index f; Op::out(u, v, row, col, n): n of them to index u of the caller's array,
+// the first one node col of row `row` (FLAT: row 0, col = u).
+template <bool FLAT, class Op>
+__global__ void __launch_bounds__(256) read_kernel(Op op, RowMap map) {
+  const unsigned lane = threadIdx.x & 63u;
+  const unsigned wave = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
+  for (size_t t0 = (static_cast<size_t>(blockIdx.x) * 4u + wave) * 64u; t0 < map.nvec; t0 += static_cast<size_t>(gridDim.x) * 256u) {
+    if (t0 + lane >= map.nvec) break;
+    const size_t u = (t0 + lane) * 4u;
+    typename Op::Raw v;
+    size_t row = 0, col = u;
+    if constexpr (FLAT) {
+      op.at(u, v);
+    } else {
+      const size_t u0 = t0 * 4u;
+      const uint64_t r0 = map.row(u0);
+      const unsigned i = static_cast<unsigned>(u0 - r0 * map.row.d) + 4u * lane, k = map.in_row(i);
+      row = r0 + k;
+      col = i - k * map.in_row.d;
+      op.at(row * map.pitch + col, v);
+      const unsigned n = static_cast<unsigned>(map.nx - col);
+      if (n < 4u) {
+        typename Op::Raw w;
+        op.at((row + 1) * map.pitch - n, w);
+        v.from(w, n);
+      }
+    }
+    op.out(u, v, row, col, static_cast<unsigned>(min(map.total - u, size_t(4))));
+  }
+}
+
+// Four stored values of each of K fields.
+template <typename T, int K> struct Raw4 {
+  T v[K][4];
+  __device__ void from(const Raw4 &o, unsigned n) {  // the values from the nth on are o's
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (unsigned e = 1; e < 4u; ++e) v[k][e] = e < n ? v[k][e] : o.v[k][e];
+  }
+};
 
 // lo, hi: smallest and largest of a value per thread over the workgroup;
 // thread 0 gets them.
@@ -656,24 +732,27 @@ __device__ __forceinline__ void lower(uint32_t *p, uint32_t v) {
 // m = (v dt)^2 (not written where m is null), the velocity's range and whether
 // every value is finite and positive.
 struct InitM {
+  using T = float;
   const float *vel;
   float *m;
   float dt;
   StepState *st;
   float lo = __builtin_huge_valf(), hi = 0.f;
   int bad = 0;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
-    float v[V], o[V];
-    lds_get<V>(vel + u, v);
+  __device__ void in(size_t u, float (&v)[4], unsigned n) { get4<4, false>(vel + u, v, n); }
+  __device__ void set(size_t f, const float (&v)[4], unsigned n, unsigned k) {
+    float o[4];
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
+    for (unsigned e = 0; e < 4u; ++e) {
       const float t = v[e] * dt;
-      o[e] = t * t;
-      if (!(v[e] > 0.f) || !(v[e] < __builtin_huge_valf())) bad = 1;
-      lo = fminf(lo, v[e]);
-      hi = fmaxf(hi, v[e]);
+      o[e] = e < n ? t * t : 0.f;
+      if (e < n) {
+        if (!(v[e] > 0.f) || !(v[e] < __builtin_huge_valf())) bad = 1;
+        lo = fminf(lo, v[e]);
+        hi = fmaxf(hi, v[e]);
+      }
     }
-    if (m) lds_put<V>(m + f, o);
+    if (m) put4<16, false>(m + f, o, k);
   }
   __device__ void finish() {
     block_range(lo, hi, bad);
@@ -686,23 +765,20 @@ struct InitM {
 };
 
 struct EncodeM16 {
+  using T = float;
   const float *vel;
   uint16_t *codes;
   float dt, m_lo, m_step;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
-    float v[V];
-    lds_get<V>(vel + u, v);
-    uint16_t c[V];
+  __device__ void in(size_t u, float (&v)[4], unsigned n) { get4<4, false>(vel + u, v, n); }
+  __device__ void set(size_t f, const float (&v)[4], unsigned n, unsigned k) {
+    uint16_t c[4];
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
+    for (unsigned e = 0; e < 4u; ++e) {
       const float t = v[e] * dt;
       const float q = m_step > 0.f ? rintf((t * t - m_lo) / m_step) : 0.f;
-      c[e] = static_cast<uint16_t>(fminf(fmaxf(q, 0.f), 65535.f));
+      c[e] = e < n ? static_cast<uint16_t>(fminf(fmaxf(q, 0.f), 65535.f)) : uint16_t(0);
     }
-    if constexpr (V == 4)
-      *reinterpret_cast<u32x2 *>(codes + f) = u32x2{c[0] | static_cast<uint32_t>(c[1]) << 16, c[2] | static_cast<uint32_t>(c[3]) << 16};
-    else
-      codes[f] = c[0];
+    put4<8, false>(codes + f, c, k);
   }
   __device__ void finish() {}
 };
@@ -718,15 +794,16 @@ __global__ void scale_record_clear_kernel(StepState *st, uint32_t *slots, int v_
 }
 
 struct AbsMax {
+  using T = float;
   const float *x;
   StepState *st;
   int v_field;
   float mx = 0.f;
-  template <int V> __device__ void run(size_t u, size_t, unsigned, size_t) {
-    float v[V];
-    lds_get<V>(x + u, v);
+  __device__ void in(size_t u, float (&v)[4], unsigned n) { get4<4, false>(x + u, v, n); }
+  __device__ void set(size_t, const float (&v)[4], unsigned n, unsigned) {
 #pragma unroll
-    for (int e = 0; e < V; ++e) mx = fmaxf(mx, fabsf(v[e]));
+    for (unsigned e = 0; e < 4u; ++e)
+      if (e < n) mx = fmaxf(mx, fabsf(v[e]));
   }
   __device__ void finish() {
     float lo = 0.f;
@@ -737,17 +814,20 @@ struct AbsMax {
 };
 
 template <int S> struct EncodeField {
+  using T = float;
   const float *x;
   typename Codec<S>::raw *dst;
   const StepState *st;
   int v_field;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
+  __device__ void in(size_t u, float (&v)[4], unsigned n) { get4<4, true>(x + u, v, n); }
+  __device__ void set(size_t f, const float (&v)[4], unsigned n, unsigned k) {
     const float sc = exp2i(scale_exponent(__uint_as_float((v_field ? st->amax_v : st->amax)[st->n & 3])));
-    float v[V];
-    nt_get<V>(x + u, v);
+    float s[4];
+    typename Codec<S>::raw r[4];
 #pragma unroll
-    for (int e = 0; e < V; ++e) v[e] *= sc;
-    field_put<S, V>(dst + f, v);
+    for (unsigned e = 0; e < 4u; ++e) s[e] = e < n ? v[e] * sc : 0.f;
+    encode4<S>(s, r);
+    put4<8, false>(dst + f, r, k);
   }
   __device__ void finish() {}
 };
@@ -763,96 +843,153 @@ __global__ void scale_record_kernel(StepState *st, int v_field) {
   (v_field ? st->exps_v : st->exps)[slot] = e;
 }
 
-// Float32 values into a field (S = kF32) or between two fields.
-struct CopyIn {
-  const float *x;
-  float *dst;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
-    float v[V];
-    nt_get<V>(x + u, v);
-    lds_put<V>(dst + f, v);
+// Values as they are into a field, from an array that starts at any multiple
+// of ALIGN bytes (float32 between two fields too, of which a checkpoint starts at
+// any element).
+template <typename V, int ALIGN> struct CopyIn {
+  using T = V;
+  const V *x;
+  V *dst;
+  __device__ void in(size_t u, V (&v)[4], unsigned n) { get4<ALIGN, false>(x + u, v, n); }
+  __device__ void set(size_t f, const V (&v)[4], unsigned n, unsigned k) {
+    V o[4];
+#pragma unroll
+    for (unsigned e = 0; e < 4u; ++e) o[e] = e < n ? v[e] : V(0);
+    put4<sizeof(V), false>(dst + f, o, k);
   }
   __device__ void finish() {}
 };
 
+// The reverse.
+template <typename V, int ALIGN> struct CopyOut {
+  using Raw = Raw4<V, 1>;
+  const V *src;
+  V *dst;
+  __device__ void at(size_t f, Raw &r) { get4<sizeof(V), false>(src + f, r.v[0]); }
+  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) { put4<ALIGN, true>(dst + u, r.v[0], n); }
+};
+
 template <int S> struct Decode {
-  const typename Codec<S>::raw *src;
-  float *out;
+  using raw = typename Codec<S>::raw;
+  using Raw = Raw4<raw, 1>;
+  const raw *src;
+  float *dst;
   const StepState *st;
   int slot_off, v_field;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
-    float v[V];
-    field_get<S, V>(src + f, v);
+  __device__ void at(size_t f, Raw &r) { get4<sizeof(raw), false>(src + f, r.v[0]); }
+  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = Codec<S>::dec(r.v[0][e]);
     if constexpr (S != kF32) {
       const int slot = (st->n + slot_off) & 3;
       const float inv = exp2i(-(v_field ? st->exps_v[slot] : st->exps[slot]));
 #pragma unroll
-      for (int e = 0; e < V; ++e) v[e] *= inv;
+      for (int e = 0; e < 4; ++e) v[e] *= inv;
     }
-    nt_put<V>(out + u, v);
+    put4<4, true>(dst + u, v, n);
   }
-  __device__ void finish() {}
 };
 
-// A^{n-1} = (A^n - V^n) / g from the 16-bit velocity-form pair; rows are grid
-// rows here.
+// A^{n-1} = (A^n - V^n) / g from the 16-bit velocity-form pair.
 template <int S> struct DecodePrev {
-  const typename Codec<S>::raw *fa, *fv;
-  float *out;
+  using raw = typename Codec<S>::raw;
+  using Raw = Raw4<raw, 2>;
+  const raw *fa, *fv;
+  float *dst;
   const float *gx, *gy, *gz;
-  int ny;
+  FastDiv64 nx, ny;
   const StepState *st;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned row, size_t col) {
+  __device__ void at(size_t f, Raw &r) {
+    get4<sizeof(raw), false>(fa + f, r.v[0]);
+    get4<sizeof(raw), false>(fv + f, r.v[1]);
+  }
+  __device__ float gyz(size_t row) const {  // the step kernel's association; gz goes on past the grid
+    const uint64_t z = ny(row);
+    return gy[row - z * ny.d] * gz[z];
+  }
+  __device__ void out(size_t u, const Raw &r, size_t row, size_t col, unsigned n) {
     const int slot = st->n & 3;
     const float ia = exp2i(-st->exps[slot]), iv = exp2i(-st->exps_v[slot]);
-    float a[V], v[V];
-    field_get<S, V>(fa + f, a);
-    field_get<S, V>(fv + f, v);
-    const float gyz = gy[row % static_cast<unsigned>(ny)] * gz[row / static_cast<unsigned>(ny)];  // the step kernel's association
+    if (col >= nx.d) {  // counted through the rows
+      row = nx(col);
+      col -= row * nx.d;
+    }
+    float v[4], g[4], gr = gyz(row);
+    if (col + 4u <= nx.d) {
+      get4<4, false>(gx + col, g);
 #pragma unroll
-    for (int e = 0; e < V; ++e) a[e] = (a[e] * ia - v[e] * iv) / (gx[col + e] * gyz);
-    nt_put<V>(out + u, a);
+      for (int e = 0; e < 4; ++e) g[e] *= gr;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (col == nx.d) {
+          col = 0;
+          gr = gyz(++row);
+        }
+        g[e] = gx[col++] * gr;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (Codec<S>::dec(r.v[0][e]) * ia - Codec<S>::dec(r.v[1][e]) * iv) / g[e];
+    put4<4, true>(dst + u, v, n);
   }
-  __device__ void finish() {}
 };
 
 // dJ/dv = 2 img dt / sqrt(m)
 struct GradFinal {
+  using Raw = Raw4<float, 2>;
   const float *img, *m;
   float dt;
   float *grad;
-  template <int V> __device__ void run(size_t u, size_t f, unsigned, size_t) {
-    float a[V], b[V];
-    lds_get<V>(img + f, a);
-    lds_get<V>(m + f, b);
-#pragma unroll
-    for (int e = 0; e < V; ++e) a[e] = 2.f * a[e] * dt / sqrtf(b[e]);
-    nt_put<V>(grad + u, a);
+  __device__ void at(size_t f, Raw &r) {
+    get4<4, false>(img + f, r.v[0]);
+    get4<4, false>(m + f, r.v[1]);
   }
-  __device__ void finish() {}
+  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = 2.f * r.v[0][e] * dt / sqrtf(r.v[1][e]);
+    put4<4, true>(grad + u, v, n);
+  }
 };
 
-// nx, pitch, rows: the caller's rows of nx nodes, the field's pitch.  by_row:
-// rows stay rows where the pitch equals nx too (the operation needs them).
-template <class Op>
-hipError_t launch_rows(Op op, const void *user, const GridRows &g, bool reduces, bool by_row, hipStream_t s) {
-  const bool one = !by_row && g.pitch == g.nx;
+// One access per lane, within the 2^32 threads of a launch; a reduction ends in
+// an atomic per workgroup: 8 workgroups per CU read the array.
+dim3 vec_grid(size_t nvec, size_t most) {
+  const size_t want = (nvec + 255) / 256;
+  return dim3(static_cast<unsigned>(want < most ? want : most));
+}
+constexpr size_t kMostGroups = 1u << 22;
+
+template <class Op> hipError_t launch_set(Op op, const GridRows &g, bool reduces, hipStream_t s) {
   RowMap map;
-  const size_t rows = one ? 1 : g.rows;
-  map.len = one ? static_cast<size_t>(g.nx) * g.rows : g.nx;
-  map.nu = g.nx;
-  map.nf = g.pitch;
-  const unsigned nseg = static_cast<unsigned>((map.len + 255) / 256);
-  map.seg = FastDiv(nseg);
-  map.total = static_cast<unsigned>(rows * nseg);
-  const bool vec = map.len % 4 == 0 && g.pitch % 4 == 0 && (one || g.nx % 4 == 0) && reinterpret_cast<uintptr_t>(user) % 16 == 0;
-  const unsigned want = (map.total + 3) / 4;
-  // a reduction ends in an atomic per workgroup: 8 workgroups per CU read the
-  // array; else one access per wavefront, within the 2^32 threads of a launch
-  const unsigned most = reduces ? 2048u : 1u << 22;
-  const dim3 grid(want < most ? want : most), b(256);
-  if (vec) hipLaunchKernelGGL((rows_kernel<4, Op>), grid, b, 0, s, op, map);
-  else hipLaunchKernelGGL((rows_kernel<1, Op>), grid, b, 0, s, op, map);
+  map.total = g.rows * g.nx;
+  map.nvec = (g.rows * g.pitch + 3) / 4;  // padded pitches are whole vectors
+  map.nx = g.nx;
+  map.pitch = g.pitch;
+  map.row = FastDiv64(map.pitch > 4u ? map.pitch / 4u : 1u);
+  map.in_row = FastDiv(map.row.d);
+  const dim3 grid = vec_grid(map.nvec, reduces ? 2048 : kMostGroups), b(256);
+  if (g.pitch == g.nx) hipLaunchKernelGGL((set_kernel<true, Op>), grid, b, 0, s, op, map);
+  else hipLaunchKernelGGL((set_kernel<false, Op>), grid, b, 0, s, op, map);
+  return hipGetLastError();
+}
+
+// by_row: the operation needs rows and columns, which rows of whole vectors give
+// it without a division per lane.  The field's allocation goes on for a vector
+// past its last node (padding planes).
+template <class Op> hipError_t launch_read(Op op, const GridRows &g, bool by_row, hipStream_t s) {
+  RowMap map;
+  map.total = g.rows * g.nx;
+  map.nvec = (map.total + 3) / 4;
+  map.nx = g.nx;
+  map.pitch = g.pitch;
+  map.row = FastDiv64(map.nx);
+  map.in_row = FastDiv(map.nx);
+  const dim3 grid = vec_grid(map.nvec, kMostGroups), b(256);
+  if (g.pitch == g.nx && !(by_row && g.nx % 4 == 0)) hipLaunchKernelGGL((read_kernel<true, Op>), grid, b, 0, s, op, map);
+  else hipLaunchKernelGGL((read_kernel<false, Op>), grid, b, 0, s, op, map);
   return hipGetLastError();
 }
 
@@ -947,14 +1084,6 @@ __global__ void zero_kernel(uint4 *p, size_t n16, uint8_t *tail, size_t ntail) {
   if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
 }
 
-// The columns that pad a field's rows, set to zero.
-template <typename T>
-__global__ void zero_padding_kernel(T *f, int nx, int pitch, size_t rows) {
-  for (size_t r = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; r < rows;
-       r += static_cast<size_t>(gridDim.x) * blockDim.x)
-    for (int x = nx; x < pitch; ++x) f[r * pitch + x] = 0;
-}
-
 unsigned grid_for(size_t n, unsigned block) {
   const size_t want = (n + block - 1) / block;
   const size_t cap = 256 * 64;  // enough workgroups to cover all CUs many times over
@@ -1001,12 +1130,12 @@ hipError_t launch_step(int storage, int variant, bool adjoint, const StepArgs &a
 }
 
 hipError_t launch_init_m(const float *vel, float *m, const GridRows &g, float dt, StepState *st, hipStream_t s) {
-  return launch_rows(InitM{vel, m, dt, st}, vel, g, true, false, s);
+  return launch_set(InitM{vel, m, dt, st}, g, true, s);
 }
 
 hipError_t launch_encode_m16(const float *vel, uint16_t *codes, const GridRows &g, float dt, float m_lo, float m_step,
                              hipStream_t s) {
-  return launch_rows(EncodeM16{vel, codes, dt, m_lo, m_step}, vel, g, false, false, s);
+  return launch_set(EncodeM16{vel, codes, dt, m_lo, m_step}, g, false, s);
 }
 
 hipError_t launch_encode_field(int storage, const float *x, void *dst, const GridRows &g, StepState *st,
@@ -1014,20 +1143,20 @@ hipError_t launch_encode_field(int storage, const float *x, void *dst, const Gri
   if (storage != kF16 && storage != kBF16) return hipErrorInvalidValue;
   const int vf = v_field ? 1 : 0;
   hipLaunchKernelGGL(scale_record_clear_kernel, dim3(1), dim3(64), 0, s, st, slots, vf);
-  hipError_t e = launch_rows(AbsMax{x, st, vf}, x, g, true, false, s);
+  hipError_t e = launch_set(AbsMax{x, st, vf}, g, true, s);
   if (e != hipSuccess) return e;
   if (storage == kF16) {
-    e = launch_rows(EncodeField<kF16>{x, static_cast<uint16_t *>(dst), st, vf}, x, g, false, false, s);
+    e = launch_set(EncodeField<kF16>{x, static_cast<uint16_t *>(dst), st, vf}, g, false, s);
     hipLaunchKernelGGL(scale_record_kernel<kF16>, dim3(1), dim3(64), 0, s, st, vf);
   } else {
-    e = launch_rows(EncodeField<kBF16>{x, static_cast<uint16_t *>(dst), st, vf}, x, g, false, false, s);
+    e = launch_set(EncodeField<kBF16>{x, static_cast<uint16_t *>(dst), st, vf}, g, false, s);
     hipLaunchKernelGGL(scale_record_kernel<kBF16>, dim3(1), dim3(64), 0, s, st, vf);
   }
   return e != hipSuccess ? e : hipGetLastError();
 }
 
 hipError_t launch_copy_in(const float *x, float *dst, const GridRows &g, hipStream_t s) {
-  return launch_rows(CopyIn{x, dst}, x, g, false, false, s);
+  return launch_set(CopyIn<float, 4>{x, dst}, g, false, s);
 }
 
 hipError_t launch_bump(StepState *st, int count, const uint32_t *slots, hipStream_t s) {
@@ -1061,11 +1190,11 @@ hipError_t launch_decode(int storage, const void *field, float *out, const GridR
   const int vf = v_field ? 1 : 0;
   switch (storage) {
     case kF32:
-      return launch_rows(Decode<kF32>{static_cast<const float *>(field), out, st, slot_off, vf}, out, g, false, false, s);
+      return launch_read(Decode<kF32>{static_cast<const float *>(field), out, st, slot_off, vf}, g, false, s);
     case kF16:
-      return launch_rows(Decode<kF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, out, g, false, false, s);
+      return launch_read(Decode<kF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, g, false, s);
     case kBF16:
-      return launch_rows(Decode<kBF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, out, g, false, false, s);
+      return launch_read(Decode<kBF16>{static_cast<const uint16_t *>(field), out, st, slot_off, vf}, g, false, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1074,8 +1203,9 @@ hipError_t launch_decode_prev(int storage, const void *fa, const void *fv, float
                               const float *gy, const float *gz, const GridRows &g, int ny, const StepState *st,
                               hipStream_t s) {
   const uint16_t *a = static_cast<const uint16_t *>(fa), *v = static_cast<const uint16_t *>(fv);
-  if (storage == kF16) return launch_rows(DecodePrev<kF16>{a, v, out, gx, gy, gz, ny, st}, out, g, false, true, s);
-  if (storage == kBF16) return launch_rows(DecodePrev<kBF16>{a, v, out, gx, gy, gz, ny, st}, out, g, false, true, s);
+  const FastDiv64 dx(g.nx), dy(ny);
+  if (storage == kF16) return launch_read(DecodePrev<kF16>{a, v, out, gx, gy, gz, dx, dy, st}, g, true, s);
+  if (storage == kBF16) return launch_read(DecodePrev<kBF16>{a, v, out, gx, gy, gz, dx, dy, st}, g, true, s);
   return hipErrorInvalidValue;
 }
 
@@ -1111,7 +1241,7 @@ hipError_t launch_check_finite(int storage, const void *field, size_t n, StepSta
 }
 
 hipError_t launch_grad_final(const float *img, const float *m, float dt, float *grad, const GridRows &g, hipStream_t s) {
-  return launch_rows(GradFinal{img, m, dt, grad}, grad, g, false, false, s);
+  return launch_read(GradFinal{img, m, dt, grad}, g, false, s);
 }
 
 namespace {
@@ -1157,14 +1287,15 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
   return hipGetLastError();
 }
 
-hipError_t launch_zero_padding(int storage, void *field, const GridRows &g, hipStream_t s) {
-  if (g.pitch == g.nx) return hipSuccess;
-  const dim3 grid(grid_for(g.rows, 256)), b(256);
-  if (storage == kF32)
-    hipLaunchKernelGGL(zero_padding_kernel<float>, grid, b, 0, s, static_cast<float *>(field), g.nx, g.pitch, g.rows);
-  else
-    hipLaunchKernelGGL(zero_padding_kernel<uint16_t>, grid, b, 0, s, static_cast<uint16_t *>(field), g.nx, g.pitch, g.rows);
-  return hipGetLastError();
+namespace {
+template <typename V> hipError_t copy_rows(V *snap, V *field, const GridRows &g, bool save, hipStream_t s) {
+  return save ? launch_read(CopyOut<V, 1>{field, snap}, g, false, s) : launch_set(CopyIn<V, 1>{snap, field}, g, false, s);
+}
+}  // namespace
+
+hipError_t launch_copy_rows(int storage, void *snap, void *field, const GridRows &g, bool save, hipStream_t s) {
+  if (storage == kF32) return copy_rows(static_cast<uint32_t *>(snap), static_cast<uint32_t *>(field), g, save, s);
+  return copy_rows(static_cast<uint16_t *>(snap), static_cast<uint16_t *>(field), g, save, s);
 }
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s) {

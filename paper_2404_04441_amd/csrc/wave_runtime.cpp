@@ -1264,13 +1264,11 @@ int wave_write_field(wave_t w, int32_t which, const float *in_dev) {
   if (w->p.storage == WAVE_F32) {
     if (which < 0 || which > 1) return WAVE_EINVAL;
     void *dst = w->field(which == 0 ? w->n : w->n + 3);
-    const int rc = hip_rc(launch_copy_in(in_dev, static_cast<float *>(dst), w->rows(), w->stream));
-    return rc ? rc : hip_rc(launch_zero_padding(w->p.storage, dst, w->rows(), w->stream));
+    return hip_rc(launch_copy_in(in_dev, static_cast<float *>(dst), w->rows(), w->stream));
   }
   if (which != 0 && which != 2) return WAVE_EINVAL;  // 16-bit storage keeps A^n and V^n
-  void *dst = which == 0 ? w->field(w->n) : w->fv;
-  const int rc = hip_rc(launch_encode_field(w->p.storage, in_dev, dst, w->rows(), w->st, w->slots, which == 2, w->stream));
-  return rc ? rc : hip_rc(launch_zero_padding(w->p.storage, dst, w->rows(), w->stream));
+  return hip_rc(launch_encode_field(w->p.storage, in_dev, which == 0 ? w->field(w->n) : w->fv, w->rows(),
+                                    w->st, w->slots, which == 2, w->stream));
 }
 
 // Snapshot layout: 256-B header | step state | A fields 0 and 1 | V (16-bit)
@@ -1297,13 +1295,10 @@ size_t state_bytes(const wave_ctx *w, size_t *field_bytes, size_t *slabs) {
 namespace {
 // The rows of a field to (from) a snapshot, which holds them without padding.
 hipError_t copy_rows(const wave_ctx *w, char *snap, void *field, bool save) {
-  const size_t es = w->p.storage == WAVE_F32 ? 4 : 2, row = es * w->nx, pitch = es * w->p.nx;
-  const size_t rows = static_cast<size_t>(w->p.ny) * w->p.nz;
-  if (row == pitch)
-    return save ? hipMemcpyAsync(snap, field, row * rows, hipMemcpyDeviceToDevice, w->stream)
-                : hipMemcpyAsync(field, snap, row * rows, hipMemcpyDeviceToDevice, w->stream);
-  return save ? hipMemcpy2DAsync(snap, row, field, pitch, row, rows, hipMemcpyDeviceToDevice, w->stream)
-              : hipMemcpy2DAsync(field, pitch, snap, row, row, rows, hipMemcpyDeviceToDevice, w->stream);
+  if (w->nx != w->p.nx) return launch_copy_rows(w->p.storage, snap, field, w->rows(), save, w->stream);
+  const size_t bytes = (w->p.storage == WAVE_F32 ? 4 : 2) * w->N;
+  return save ? hipMemcpyAsync(snap, field, bytes, hipMemcpyDeviceToDevice, w->stream)
+              : hipMemcpyAsync(field, snap, bytes, hipMemcpyDeviceToDevice, w->stream);
 }
 }  // namespace
 
@@ -1376,10 +1371,8 @@ int wave_load_state(wave_t w, const void *src_dev) {
     fields[1] = w->field(h.n + 3);
   }
   const int nfields = w->p.storage == WAVE_F32 ? 2 : 3;
-  for (int k = 0; k < nfields && !rc; ++k, off += align256(fb)) {
+  for (int k = 0; k < nfields && !rc; ++k, off += align256(fb))
     rc = hip_rc(copy_rows(w, const_cast<char *>(src) + off, fields[k], false));
-    if (!rc) rc = hip_rc(launch_zero_padding(w->p.storage, fields[k], w->rows(), w->stream));
-  }
   for (int a = 0; a < 3 && w->cpml && !rc; ++a) {
     rc = hip_rc(hipMemcpyAsync(w->ws + w->L.cpml_slab[a], src + off, slab_bytes(w, a), hipMemcpyDeviceToDevice,
                                w->stream));
