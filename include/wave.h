@@ -293,9 +293,10 @@ int wave_variant_count(void);
  * along z): by wavefronts of 64 lanes, ry rows and vec nodes along x per lane,
  * pd planes of loads in flight; tiles of 64*vec x by*ry nodes (variants up to
  * 19) or of the same number of nodes in another width (from 20 on).  The last
- * ones (from 29 on) are the shapes of several nodes per lane again, in their
- * order, for any nx: the workspace's rows are padded to whole vectors (info
- * reports vec = 1).  Variant 0 may choose them; wave_tiling then reports them.
+ * ones (from 29 on) are the shapes of families 0 to 2 again, those of several
+ * nodes per lane in their order and then the others, for any nx: the workspace's
+ * rows are padded to whole vectors (info reports vec = 1).  Variant 0 may choose
+ * them; wave_tiling then reports them.
  * Variant 0 means "automatic"; its info is the shape that choice falls back
  * to (also available explicitly as another variant).
  * Families 1 and 2 are the paper's 3D-blocking designs of the same section

@@ -36,12 +36,14 @@ struct Layout {
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 // The variants of the interface: the shapes of the kernel table and behind
-// them, for every 2.5D shape with more than one node per lane, its form with
-// padded rows (any nx; reported with vec = 1).
+// them, for every shape that the automatic choice may settle on, its form with
+// padded rows (any nx; reported with vec = 1), those with several nodes per
+// lane first.  Each has one, so that a choice made on padded rows can be named.
 std::vector<int> padded_shapes() {
   std::vector<int> v;
-  for (int k = 1; k < variant_count(); ++k)
-    if (variant_info(k).family == 0 && variant_info(k).vec > 1) v.push_back(k);
+  for (const bool wide : {true, false})
+    for (int k = 1; k < variant_count(); ++k)
+      if (variant_info(k).family <= 2 && (variant_info(k).vec > 1) == wide) v.push_back(k);
   return v;
 }
 const std::vector<int> kPadded = padded_shapes();
@@ -107,10 +109,10 @@ int validate(const wave_params *p) {
     if (p->storage != WAVE_F32 || p->nt_max < 1 || p->ckpt_interval < 0) return WAVE_EINVAL;
   }
   if (p->variant < 0 || p->variant >= interface_count()) return WAVE_EINVAL;
-  if (p->variant > 0 && !is_padded(p->variant)) {
-    const Variant v = variant_info(p->variant);
+  if (p->variant > 0) {
+    const Variant v = variant_info(base_shape(p->variant));
     // a tile shape with VEC > 1 x nodes per lane needs whole vectors per row
-    if (p->nx % v.vec) return WAVE_EINVAL;
+    if (!is_padded(p->variant) && p->nx % v.vec) return WAVE_EINVAL;
     // the study families (3D-blocked, semi-stencil) are float32 forward only
     if (v.family != 0 && (p->storage != WAVE_F32 || p->adjoint)) return WAVE_EINVAL;
   }
@@ -1427,8 +1429,7 @@ int wave_tiling(wave_t w, int32_t *out) {
     const Variant a = variant_info(0), b = variant_info(k);
     if (a.family == b.family && a.by == b.by && a.ry == b.ry && a.pd == b.pd && a.vec == b.vec) v = k;
   }
-  // on padded rows a shape that the caller's nx does not admit is its padded form
-  if (w->nx != w->p.nx && w->nx % variant_info(v).vec) v = padded_shape(v);
+  if (w->nx != w->p.nx) v = padded_shape(v);  // the variant that asks for padded rows again
   out[0] = v;
   out[1] = w->p.time_block == 2 ? w->pair.zchunk : w->fwd.zchunk;
   out[2] = w->fwd.keep ? 1 : 0;
