@@ -292,7 +292,8 @@ int wave_variant_count(void);
  * Family 0 is the 2.5D blocking of paper Sec. IV-A (tile x and y, stream
  * along z): by wavefronts of 64 lanes, ry rows and vec nodes along x per lane,
  * pd planes of loads in flight; tiles of 64*vec x by*ry nodes (variants up to
- * 19) or of the same number of nodes in another width (from 20 on).  The last
+ * 19) or of the same number of nodes in another width (from 20 on; see
+ * wave_variant_tile).  The last
  * ones (from 29 on) are the shapes of families 0 to 2 again, those of several
  * nodes per lane in their order and then the others, for any nx: the workspace's
  * rows are padded to whole vectors (info reports vec = 1).  Variant 0 may choose
@@ -309,6 +310,13 @@ int wave_variant_count(void);
  * kernel of time_block = 2 (by, ry give its 64 x by*ry first-step tile).  Errors: WAVE_EINVAL for a null
  * `info` or an out-of-range variant. */
 int wave_variant_info(int32_t variant, int32_t *info);
+
+/* The tile of kernel variant `variant` (0 .. wave_variant_count()-1), written
+ * to tile[0..1] (caller-owned host array of 2): nodes along x and y that one
+ * workgroup covers of a plane (the 2.5D blocking of paper Sec. IV-A; for the
+ * 3D-blocked families their block's, for family 4 its first step's).  Errors:
+ * WAVE_EINVAL for a null `tile` or an out-of-range variant. */
+int wave_variant_tile(int32_t variant, int32_t *tile);
 
 /* Static text for a status code. */
 const char *wave_status_string(int status);

@@ -23,7 +23,7 @@ EXPORTS = (
     "wave_reset", "wave_step", "wave_run",
     "wave_adjoint", "wave_read_field", "wave_write_field", "wave_time_index", "wave_state_bytes", "wave_save_state", "wave_load_state",
     "wave_sync_status", "wave_destroy", "wave_tiling",
-    "wave_variant_count", "wave_variant_info", "wave_status_string",
+    "wave_variant_count", "wave_variant_info", "wave_variant_tile", "wave_status_string",
 )
 
 
@@ -94,6 +94,7 @@ def lib():
         L.wave_destroy.argtypes = [vp]
         L.wave_variant_count.argtypes = []
         L.wave_variant_info.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+        L.wave_variant_tile.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
         L.wave_status_string.argtypes = [ctypes.c_int]
         L.wave_status_string.restype = ctypes.c_char_p
         for name in EXPORTS:

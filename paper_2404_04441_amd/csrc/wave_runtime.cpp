@@ -1448,6 +1448,15 @@ int wave_variant_info(int32_t variant, int32_t *info) {
   return WAVE_OK;
 }
 
+int wave_variant_tile(int32_t variant, int32_t *tile) {
+  if (!tile || variant < 0 || variant >= interface_count()) return WAVE_EINVAL;
+  const Variant v = variant_info(base_shape(variant));
+  const bool blocked = v.family == 1 || v.family == 2;  // blocks of 64 x by x ry nodes
+  tile[0] = blocked ? kTileX : v.lx * v.vec;
+  tile[1] = blocked ? v.by : 64 * v.by / v.lx * v.ry;
+  return WAVE_OK;
+}
+
 const char *wave_status_string(int status) {
   switch (status) {
     case WAVE_OK: return "ok";

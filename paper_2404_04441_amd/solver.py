@@ -223,3 +223,10 @@ def variant_info(variant: int) -> dict:
     info = (ctypes.c_int32 * 5)()
     L.check(L.lib().wave_variant_info(int(variant), info), "wave_variant_info")
     return dict(zip(("family", "by", "ry", "pd", "vec"), (int(v) for v in info)))
+
+
+def variant_tile(variant: int) -> tuple:
+    """Nodes along x and y that one workgroup of a kernel variant covers of a plane."""
+    tile = (ctypes.c_int32 * 2)()
+    L.check(L.lib().wave_variant_tile(int(variant), tile), "wave_variant_tile")
+    return int(tile[0]), int(tile[1])
