@@ -511,16 +511,24 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const char *U = static_cast<const char *>(a.cur);
   const char *P = static_cast<const char *>(a.prev);
   char *O = static_cast<char *>(a.out);
-  const rsrc_t rU_ = make_rsrc(U + base_b, span);
-  const rsrc_t rP_ = make_rsrc(P + base_b, span);
+  // A load of a plane that is not there takes the field's resource with no
+  // records.  Choosing between whole resources kept a null one beside each
+  // field's, four scalars a choice: in 256x8 bf16 tiles 40 spilled scalars
+  // instead of 28 and 76 instead of 64 scalar operations a plane.  512^3 from
+  // rest: bf16 275 -> 272.5 us a step, with 16-bit m 263 -> 259, f16 271.5 ->
+  // 269.5; f16 256x192x128 19.45 -> 19.15; the gradient of 256^3 17.3 -> 17.1 ms.
+  auto rU = [&](bool in) { return make_rsrc(U + base_b, in ? span : 0u); };
+  auto rP = [&](bool in) { return make_rsrc(P + base_b, in ? span : 0u); };
+  auto rM = [&](bool in) {
+    return M16 ? make_rsrc(reinterpret_cast<const char *>(a.m) + base * 2, in ? span : 0u)
+               : make_rsrc(a.m + base, in ? span_f : 0u);
+  };
   const rsrc_t rO = make_rsrc(O + base_b, span);
   const rsrc_t rVo = make_rsrc((S != kF32 ? static_cast<char *>(a.vout) : O) + base_b, span);
-  const rsrc_t rM_ = M16 ? make_rsrc(reinterpret_cast<const char *>(a.m) + base * 2, span)
-                         : make_rsrc(a.m + base, span_f);
   const rsrc_t rnull = make_rsrc(a.gz, 0u);
-  const rsrc_t rI_ = make_rsrc((IMG ? a.img : a.m) + base, IMG ? span_f : 0u);
-  const rsrc_t rL0_ = make_rsrc((IMG ? a.la0 : a.m) + base, IMG ? span_f : 0u);
-  const rsrc_t rL1_ = make_rsrc((IMG && a.la1 ? a.la1 : a.m) + base, IMG && a.la1 ? span_f : 0u);
+  auto rI = [&](bool in) { return make_rsrc((IMG ? a.img : a.m) + base, IMG && in ? span_f : 0u); };
+  auto rL0 = [&](bool in) { return make_rsrc((IMG ? a.la0 : a.m) + base, IMG && in ? span_f : 0u); };
+  auto rL1 = [&](bool in) { return make_rsrc((IMG && a.la1 ? a.la1 : a.m) + base, IMG && a.la1 && in ? span_f : 0u); };
   const rsrc_t rLo = make_rsrc((LAP ? a.lap : const_cast<float *>(a.m)) + base, LAP ? span_f : 0u);
   auto so = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes; };     // plane offset, A fields
   auto so_f = [&](int z) { return static_cast<uint32_t>(z - zlo) * pbytes_f; };  // plane offset, float fields
@@ -576,13 +584,12 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   const int W = CP ? a.cp.W : 0;
   const uint32_t W2 = 2u * static_cast<uint32_t>(W);
   const uint32_t uny = static_cast<uint32_t>(ny);
-  rsrc_t rPX = rnull, rZX = rnull;
+  const uint32_t bx = CP ? static_cast<uint32_t>(a.nz) * uny * W2 * 4u : 0u;
+  auto rPX = [&](bool in) { return make_rsrc(a.cp.psi[0], in ? bx : 0u); };
+  auto rZX = [&](bool in) { return make_rsrc(a.cp.zeta[0], in ? bx : 0u); };
   float cax[CP ? VEC : 1], cbx[CP ? VEC : 1];
   bool xown = false;  // some of this lane's columns lie in an x layer
   if constexpr (CP) {
-    const uint32_t bx = static_cast<uint32_t>(a.nz) * uny * W2 * 4u;
-    rPX = make_rsrc(a.cp.psi[0], bx);
-    rZX = make_rsrc(a.cp.zeta[0], bx);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       cax[i] = xin ? a.cp.ca[0][x + i] : 0.f;
@@ -617,35 +624,34 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
                               : rnull;
 
   // loads of planes past the chunk's outputs (the last PD iterations issue
-  // them) go through a resource without records: no memory traffic
+  // them) go through resources without records: no memory traffic
   auto load_stage = [&](StageT &st, int z) {
     const bool live = !kSkipTail || z < zend;
-    const rsrc_t rU = live ? rU_ : rnull, rP = live ? rP_ : rnull, rM = live ? rM_ : rnull;
+    const rsrc_t u = rU(live), p = rP(live), mm = rM(live);
     const uint32_t sl = so(z + R);
     const uint32_t sc = so(z), scf = so_f(z);
     st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
     st.rz = static_cast<int>(ld_words<4, 0>(rgz, 0u, rz_off + static_cast<uint32_t>(z) * 4u).w[0]);
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
-      st.lead[j] = ld_words<NA, 0>(rU, vrow[j], sl);
-      st.p[j] = ld_words<NA, NTP>(rP, vrow[j], sc);
-      st.m[j] = ld_words<StageT::NM, NTP>(rM, M16 ? vrow[j] : vrow_f[j], M16 ? sc : scf);
+      st.lead[j] = ld_words<NA, 0>(u, vrow[j], sl);
+      st.p[j] = ld_words<NA, NTP>(p, vrow[j], sc);
+      st.m[j] = ld_words<StageT::NM, NTP>(mm, M16 ? vrow[j] : vrow_f[j], M16 ? sc : scf);
     }
 #pragma unroll
-    for (int i = 0; i < NYH; ++i) st.yh[i] = ld_words<NA, 0>(rU, vyh[i], LEADH ? sl : sc);
-    st.xh = ld_words<S == kF32 ? 4 : 2, 0>(rU, vxh, LEADH ? sl : sc);
+    for (int i = 0; i < NYH; ++i) st.yh[i] = ld_words<NA, 0>(u, vyh[i], LEADH ? sl : sc);
+    st.xh = ld_words<S == kF32 ? 4 : 2, 0>(u, vxh, LEADH ? sl : sc);
     if constexpr (IMG) {
-      const rsrc_t rI = live ? rI_ : rnull, rL0 = live ? rL0_ : rnull, rL1 = live ? rL1_ : rnull;
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
-        st.img[j] = ld_words<NF, kNT>(rI, vrow_f[j], scf);
-        st.la0[j] = ld_words<NF, kNT>(rL0, vrow_f[j], scf);
-        st.la1[j] = ld_words<NF, kNT>(rL1, vrow_f[j], scf);
+        st.img[j] = ld_words<NF, kNT>(rI(live), vrow_f[j], scf);
+        st.la0[j] = ld_words<NF, kNT>(rL0(live), vrow_f[j], scf);
+        st.la1[j] = ld_words<NF, kNT>(rL1(live), vrow_f[j], scf);
       }
     }
     if constexpr (CP) {  // x slab plane z (none past nz); zero off the x layers
       const bool zin = z < a.nz;
-      const rsrc_t rp = zin ? rPX : rnull, rz = zin ? rZX : rnull;
+      const rsrc_t rp = rPX(zin), rz = rZX(zin);
       const uint32_t sp = zin ? static_cast<uint32_t>(z) * uny * W2 * 4u : 0u;
 #pragma unroll
       for (int j = 0; j < RY; ++j) {
@@ -673,18 +679,17 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   for (int k = 0; k < 2 * R; ++k) {
     const int zz = zb - R + k;
     const bool zok = zz >= 0;
-    const rsrc_t r = zok ? rU_ : rnull;
     const uint32_t s0 = zok ? so(zz) : 0u;
 #pragma unroll
-    for (int j = 0; j < RY; ++j) pq[k][j] = ld_words<NA, 0>(r, vrow[j], s0);
+    for (int j = 0; j < RY; ++j) pq[k][j] = ld_words<NA, 0>(rU(zok), vrow[j], s0);
   }
   if constexpr (LEADH) {
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       const uint32_t s0 = so(zb + k);
 #pragma unroll
-      for (int i = 0; i < NYH; ++i) pyh[k][i] = ld_words<NA, 0>(rU_, vyh[i], s0);
-      pxh[k] = ld_words<S == kF32 ? 4 : 2, 0>(rU_, vxh, s0);
+      for (int i = 0; i < NYH; ++i) pyh[k][i] = ld_words<NA, 0>(rU(true), vyh[i], s0);
+      pxh[k] = ld_words<S == kF32 ? 4 : 2, 0>(rU(true), vxh, s0);
     }
   }
   StageT stg[PD];
@@ -1078,7 +1083,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
             const uint32_t sp = static_cast<uint32_t>(z) * uny * W2 * 4u;
 #pragma unroll
             for (int i = 0; i < VEC; ++i)
-              st_words<4, 0>(Words<4>{{__float_as_uint(zn[i])}}, rZX, xoff(x + i, yj), sp);
+              st_words<4, 0>(Words<4>{{__float_as_uint(zn[i])}}, rZX(true), xoff(x + i, yj), sp);
           }
 #pragma unroll
           for (int i = 0; i < VEC; ++i) lap[i] += ext[i];
@@ -1138,7 +1143,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
           }
           rkeep[S != kF32 ? j : 0] = ra;
         }
-        if constexpr (IMG) st_words<NF, kNT>(row_put<kF32, VEC>(im[j]), rI_, vrow_f[j], sz0f);
+        if constexpr (IMG) st_words<NF, kNT>(row_put<kF32, VEC>(im[j]), rI(true), vrow_f[j], sz0f);
       }
       // receiver samples of A^{n+1} (forward), in the plane's own uniform branch
       if (!ADJ && rzi >= 0) {
