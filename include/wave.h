@@ -93,8 +93,9 @@ typedef struct {
                                 times candidate configurations for a few steps on fields of
                                 noise (zeroed afterwards): the 2.5D shapes and z-chunks, both cache policies
                                 (without CPML), and for float32 forward runs without
-                                CPML or adjoint also the 3D-blocked gmem and smem shapes.  It
-                                keeps the fastest (the fixed rule's choice unless another is more
+                                CPML or adjoint also the 3D-blocked gmem and smem shapes.  The
+                                fastest few are then timed in turn, on noise and from rest, and the
+                                smallest sum is kept (the fixed rule's choice unless another is more
                                 than 3% faster).  With adjoint != 0 it also times the adjoint
                                 step's shapes and z-chunks on their own and keeps the fastest the
                                 same way.  The choices are cached per (nx, ny, nz, storage, CPML,

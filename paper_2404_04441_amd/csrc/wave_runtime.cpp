@@ -577,9 +577,12 @@ int do_reset(wave_ctx *w) {
 
 // ---- shape tuning: time each candidate (2.5D shape, z-chunk) for a few
 // steps and keep the fastest.  All candidates compute identical bits, so the
-// choice only changes speed.  The fields hold noise meanwhile: on zeros the
-// vector units draw less power, the clock stays higher (256^3: 37.5 us a step
-// on zeros, 41.9 on data) and the order of the candidates is another one.
+// choice only changes speed.  The fields hold noise meanwhile, which the
+// steps propagate as they would any state: on zeros the vector units draw less
+// power, the clock stays higher (256^3: 37.5 us a step on zeros, 41.9 on data)
+// and the order of the candidates is another one.  A shot sees both, zeros for
+// most of its grid while it starts from rest, so the choice among the fastest is
+// made by the sum of the two times, taken in turn over enough steps.
 struct TuneEntry {
   int nx, ny, nz, storage, cache_hint, model_bits;
   bool cpml, adjoint;
@@ -634,6 +637,27 @@ bool fits(const wave_params &p, int variant, bool cpml, float *best) {
   return overhang(variant) <= 1.4f * *best;
 }
 
+using TimedTiling = std::pair<float, Tiling>;
+
+// The candidates for the last comparison: the default (the first one timed)
+// and the fastest others, at most four, within 8% of the best.  One sample of a
+// few steps of microseconds is off by that much.
+std::vector<Tiling> shortlist(std::vector<TimedTiling> timed) {
+  std::vector<Tiling> out{timed.front().second};
+  std::sort(timed.begin() + 1, timed.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+  const float best = timed.size() > 1 ? std::min(timed[0].first, timed[1].first) : timed[0].first;
+  for (size_t i = 1; i < timed.size() && out.size() < 5 && timed[i].first <= 1.08f * best; ++i)
+    out.push_back(timed[i].second);
+  return out;
+}
+
+// The index of the smallest score; the default (index 0) unless another is more
+// than 3% below it, so that near-ties do not move the choice.
+size_t settle(const std::vector<float> &score) {
+  const size_t best = static_cast<size_t>(std::min_element(score.begin(), score.end()) - score.begin());
+  return score[best] <= 0.97f * score[0] ? best : 0;
+}
+
 int tune_forward(wave_ctx *w) {
   const wave_params &p = w->p;
   {
@@ -659,22 +683,27 @@ int tune_forward(wave_ctx *w) {
   // steps per timing: 3, more where a step takes only microseconds (the
   // event pair's own granularity would decide between candidates)
   const int64_t nodes = static_cast<int64_t>(p.nx) * p.ny * p.nz;
-  const int nstep = nodes > (int64_t(1) << 24) ? 3 : (nodes > (int64_t(1) << 22) ? 5 : 8);
+  const int nstep = nodes > (int64_t(1) << 24) ? 3 : (nodes > (int64_t(1) << 22) ? 5 : (nodes > (int64_t(1) << 20) ? 8 : 16));
   float best_overhang = 0.f;
-  // milliseconds of nstep steps after 1 warm-up step, or a negative value on error
-  auto time_one = [&](const Tiling &t) {
+  // milliseconds a step over `count` steps after 1 warm-up step, or a negative
+  // value on error.  The host's step counter goes on with the device's: which
+  // level a buffer holds, and with it the level's scale, follows from it.
+  auto time_steps = [&](const Tiling &t, int count) {
     w->fwd = t;
     w->cpml_fused = w->cpml && variant_fuses_cpml(t.variant);
     int r = enqueue_steps(w, 1, nullptr, nullptr, false);
+    w->n += 1;
     if (!r) r = hip_rc(hipEventRecord(e0, w->stream));
-    if (!r) r = enqueue_steps(w, nstep, nullptr, nullptr, false);
+    if (!r) r = enqueue_steps(w, count, nullptr, nullptr, false);
+    w->n += count;
     if (!r) r = hip_rc(hipEventRecord(e1, w->stream));
     if (!r) r = hip_rc(hipEventSynchronize(e1));
     float ms = 0.f;
     if (!r) r = hip_rc(hipEventElapsedTime(&ms, e0, e1));
     if (r) rc = r;
-    return r ? -1.f : ms;
+    return r ? -1.f : ms / count;
   };
+  auto time_one = [&](const Tiling &t) { return time_steps(t, nstep); };
   // stage 1: the fixed rule's choice, then every shape at its automatic
   // z-chunk, 2.5D shapes with both cache policies where they apply (only the
   // cached one for cache_hint 1).  The 3D-blocked families compute the same
@@ -702,10 +731,10 @@ int tune_forward(wave_ctx *w) {
       cands.push_back(t);
     }
   }
-  std::vector<std::pair<float, Tiling>> timed;
+  std::vector<TimedTiling> timed;
   for (size_t i = 0; i < cands.size() && !rc; ++i) timed.emplace_back(time_one(cands[i]), cands[i]);
   // stage 2: the z-chunk lists of the four fastest 2.5D candidates of stage 1
-  std::vector<std::pair<float, Tiling>> top;
+  std::vector<TimedTiling> top;
   for (const auto &c : timed)
     if (variant_info(c.second.variant).family == 0) top.push_back(c);
   std::sort(top.begin(), top.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
@@ -721,35 +750,46 @@ int tune_forward(wave_ctx *w) {
       if (t.zchunk != c.second.zchunk) timed.emplace_back(time_one(t), t);
     }
   }
-  // the fixed rule's choice (timed first) stays unless another candidate is
-  // more than 3% faster, so near-ties (timing noise) do not move the choice
+  // last: the fixed rule's choice (timed first) and the fastest others in turn,
+  // on data and then from rest, about 0.2 ms of steps each time
+  const int rounds = nodes > (int64_t(1) << 24) ? 2 : 3;
+  auto sample = [&](float step_ms) { return std::max(3, std::min(64, static_cast<int>(0.2f / std::max(step_ms, 1e-3f)))); };
   Tiling best = fixed;
   if (!rc) {
-    const float base_ms = timed.front().first;
-    float best_ms = base_ms;
-    for (const auto &c : timed)
-      if (c.first < best_ms) {
-        best_ms = c.first;
-        best = c.second;
-      }
-    if (best_ms > 0.97f * base_ms) best = fixed;
+    const std::vector<Tiling> last = shortlist(timed);
+    const int count = sample(timed.front().first);
+    std::vector<float> score(last.size(), 0.f);
+    for (int rest = 0; rest < 2 && last.size() > 1 && !rc; ++rest) {
+      if (rest) rc = do_reset(w);
+      std::vector<float> ms(last.size(), 1e30f);
+      for (int round = 0; round < rounds && !rc; ++round)
+        for (size_t c = 0; c < last.size() && !rc; ++c) ms[c] = std::min(ms[c], time_steps(last[c], count));
+      for (size_t c = 0; c < last.size(); ++c) score[c] += ms[c];
+    }
+    if (!rc) best = last[settle(score)];
   }
   w->p.src[0] = src_x;
   w->fwd = best;
   w->cpml_fused = w->cpml && variant_fuses_cpml(w->fwd.variant);
   // Adjoint contexts: the adjoint step (every second one with two kept
   // Laplacians and the imaging accumulator on top of the forward step's
-  // streams) is timed on its own, with no residual, on whatever its buffers hold (wave_adjoint
-  // clears every buffer it reads before use): every 2.5D shape at its automatic z-chunk,
-  // then the z-chunk list (a shorter one) for the two fastest, the default kept unless
-  // another is more than 3% faster.  All compute the same bits.
+  // streams) is timed on its own, with no residual, on buffers of noise (wave_adjoint
+  // sets every buffer it reads before use): every 2.5D shape at its automatic z-chunk,
+  // then the z-chunk list for the two fastest, then the fastest of all in turn, as for
+  // the forward step.  All compute the same bits.
   if (!rc && p.adjoint) {
     const Layout &L = w->L;
     float *mu1 = reinterpret_cast<float *>(w->ws + L.mua);
     float *mu2 = reinterpret_cast<float *>(w->ws + L.mub);
     float *img = reinterpret_cast<float *>(w->ws + L.img);
     float *seg = reinterpret_cast<float *>(w->ws + L.seg);
-    auto time_adj = [&](const Tiling &t) {
+    float *const held[] = {mu1, mu2, img, seg, seg + w->Np};
+    for (uint32_t k = 0; k < 5 && !rc; ++k) {
+      rc = hip_rc(launch_fill_zero(held[k], 4 * w->Np, w->stream));
+      if (!rc) rc = hip_rc(launch_noise(kF32, held[k], w->N, 3u + k, w->stream));
+    }
+    // milliseconds a step over `pairs` pairs of a plain and an imaging step, after one pair
+    auto time_adj = [&](const Tiling &t, int pairs) {
       StepArgs b = base_args(w, t);
       b.sx = -1;
       b.cur = mu1;
@@ -759,7 +799,7 @@ int tune_forward(wave_ctx *w) {
       b.la1 = seg + w->Np;
       if (w->fused_rec) b.box = w->box;
       int r = 0;
-      for (int i = 0; i < 6 && !r; ++i) {  // plain and imaging steps in turn, two of each timed
+      for (int i = 0; i < 2 + 2 * pairs && !r; ++i) {
         if (i == 2) r = hip_rc(hipEventRecord(e0, w->stream));
         b.img = i & 1 ? img : nullptr;
         if (!r) r = hip_rc(launch_step(WAVE_F32, t.variant, true, b, w->stream));
@@ -769,10 +809,11 @@ int tune_forward(wave_ctx *w) {
       float ms = 0.f;
       if (!r) r = hip_rc(hipEventElapsedTime(&ms, e0, e1));
       if (r) rc = r;
-      return r ? -1.f : ms;
+      return r ? -1.f : ms / (2 * pairs);
     };
+    const int npair = nodes > (int64_t(1) << 22) ? 2 : 4;
     const Tiling dflt = w->adj;
-    std::vector<std::pair<float, Tiling>> ta{{time_adj(dflt), dflt}};
+    std::vector<TimedTiling> ta{{time_adj(dflt, npair), dflt}};
     for (int v = 0; v < variant_count() && !rc; ++v) {
       const Variant info = variant_info(v);
       if (info.family != 0 || p.nx % info.vec) continue;
@@ -783,10 +824,10 @@ int tune_forward(wave_ctx *w) {
       Tiling t = make_tiling(&q, v);
       for (const bool keep : {false, true}) {
         t.keep = keep;
-        if (!rc) ta.emplace_back(time_adj(t), t);
+        if (!rc) ta.emplace_back(time_adj(t, npair), t);
       }
     }
-    std::vector<std::pair<float, Tiling>> top(ta.begin(), ta.end());
+    std::vector<TimedTiling> top(ta.begin(), ta.end());
     std::sort(top.begin(), top.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     if (top.size() > 2) top.resize(2);
     for (const auto &c : top) {
@@ -797,18 +838,16 @@ int tune_forward(wave_ctx *w) {
         q.zchunk = zc;
         Tiling t = make_tiling(&q, q.variant);
         t.keep = c.second.keep;
-        if (t.zchunk != c.second.zchunk) ta.emplace_back(time_adj(t), t);
+        if (t.zchunk != c.second.zchunk) ta.emplace_back(time_adj(t, npair), t);
       }
     }
     if (!rc) {
-      const float base_ms = ta.front().first;
-      float best_ms = base_ms;
-      for (const auto &c : ta)
-        if (c.first > 0.f && c.first < best_ms) {
-          best_ms = c.first;
-          w->adj = c.second;
-        }
-      if (best_ms > 0.97f * base_ms) w->adj = dflt;
+      const std::vector<Tiling> last = shortlist(ta);
+      const int pairs = (sample(ta.front().first) + 1) / 2;
+      std::vector<float> ms(last.size(), last.size() > 1 ? 1e30f : 0.f);
+      for (int round = 0; round < rounds && last.size() > 1 && !rc; ++round)
+        for (size_t c = 0; c < last.size() && !rc; ++c) ms[c] = std::min(ms[c], time_adj(last[c], pairs));
+      if (!rc) w->adj = last[settle(ms)];
     }
   }
   if (e0) (void)hipEventDestroy(e0);
