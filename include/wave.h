@@ -246,6 +246,9 @@ int wave_read_field(wave_t w, int32_t which, float *out_dev);
  * values of which: WAVE_EINVAL.  The step counter is unchanged.  Non-finite
  * inputs are stored as given (the scale then falls back to 2^0 or its
  * clamp), and wave_sync_status reports them as for a run that diverged.
+ * With WAVE_F16, levels whose sizes differ by more than about 2^60 (and source
+ * samples that jump as far) make the next step a slow one, some 25 times a
+ * step's time, with the same rounding.
  * Enqueued on the context's stream; in_dev must stay valid until the stream
  * reaches it. */
 int wave_write_field(wave_t w, int32_t which, const float *in_dev);
