@@ -434,6 +434,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // wavefronts with nothing to write go there, so no write is predicated
   constexpr int LP = LH * LW + 64 * VEC;
   constexpr int DUMMY = LH * LW;
+  static_assert(LX <= 64 || NYH * ROWS == 2 * R, "the scratch row holds 64 vectors: wider rows of lanes may leave none idle");
   // LEADH: the x and y halo of A^n is loaded with the lead plane z+R, when
   // the neighbouring tiles load the same lines as their own lead (so those
   // loads meet in L2), instead of R planes later at the centre plane, by
