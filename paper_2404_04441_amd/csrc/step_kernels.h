@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // wavefronts with nothing to write go there, so no write is predicated
   constexpr int LP = LH * LW + 64 * VEC;
   constexpr int DUMMY = LH * LW;
-  static_assert(LX <= 64 || NYH * ROWS == 2 * R, "the scratch row holds 64 vectors: wider rows of lanes may leave none idle");
+  static_assert(LX <= 64 || (NYH * ROWS == 2 * R && LX <= 64 * VEC), "the scratch row holds 64 vectors: wider rows of lanes may leave none idle");
   // LEADH: the x and y halo of A^n is loaded with the lead plane z+R, when
   // the neighbouring tiles load the same lines as their own lead (so those
   // loads meet in L2), instead of R planes later at the centre plane, by
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   }
   // y-halo rows of this wavefront: halo row r = w + BY*i (r < R above the tile, else below)
   int yhlds[NYH];
-  uint32_t vyh[NYH], vyh_f[NYH];
+  uint32_t vyh[NYH];
 #pragma unroll
   for (int i = 0; i < NYH; ++i) {
     const int r = w + ROWS * i;
@@ -565,11 +565,10 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     yhlds[i] = yhin ? lr * LW + R + VEC * lane : DUMMY + VEC * lane;
     const uint32_t e = static_cast<uint32_t>(gyy) * static_cast<uint32_t>(nx) + static_cast<uint32_t>(x);
     vyh[i] = ok ? e * ES : kOOB;
-    vyh_f[i] = ok ? e * 4u : kOOB;
   }
   // x-halo: lane l < 8*RY covers row l/8 of this wavefront, column l%8
   int xhlds = DUMMY + lane, xhx = DUMMYX + lane, xh_x = -1, xh_y = 0;
-  uint32_t vxh = kOOB, vxh_f = kOOB;
+  uint32_t vxh = kOOB;
   if (lane < 8 * RY) {
     const int j = lane >> 3, c = lane & 7;
     const int gxx = c < R ? x0 - R + c : x0 + TX + (c - R);
@@ -583,7 +582,6 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     if (gxx >= 0 && gxx < nx && yj < ny) {
       const uint32_t e = static_cast<uint32_t>(yj) * static_cast<uint32_t>(nx) + static_cast<uint32_t>(gxx);
       vxh = e * ES;
-      vxh_f = e * 4u;
     }
   }
 

@@ -24,9 +24,10 @@ struct FastDiv {
 //   psi_a^n  = b psi_a^{n-1}  + a D1_a p^n
 //   zeta_a^n = b zeta_a^{n-1} + a (D2_a p^n + D1_a psi_a^n)
 //   p^{n+1}  = (plain leapfrog step) + m sum_a (D1_a psi_a^n + zeta_a^n).
-// Both kernels run one thread per node of the boundary shell: the planes of
-// the z layers, then the rows of the y layers in the remaining planes, then
-// the columns of the x layers in the remaining rows (each node once).
+// The psi update runs before the step, along y and z by rows of the boundary
+// shell and along x over its slabs.  The correction runs after it: by rows for the
+// y and z terms where the step applies the x part itself, else a thread per node of
+// the shell for all three.
 
 // Node t of the boundary shell for layers of E nodes: the planes of the z
 // layers, then in the remaining planes the rows of the y layers, then in the
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(256) cpml_psi_kernel(CpmlArgs c, ShellWork P, 
 
 // The y and z terms of one row: out += m * sum_{a = y, z} (D1_a psi_a +
 // zeta_a), zeta_a updated, VEC consecutive x nodes per lane (nx % VEC == 0).
-// Per node the same operations as cpml_fix_kernel with a0 = 1.
+// Per node the operations of cpml_fix_kernel without its x part.
 template <int VEC>
 __device__ __forceinline__ void fix_row(const CpmlArgs &c, const float *cur, const float *m, float *out, int y, int z,
                                         uint32_t xo) {
@@ -500,23 +501,19 @@ __global__ void __launch_bounds__(256) cpml_fix_yz_kernel(CpmlArgs c, ShellWork 
                  at.part == 0 ? static_cast<int>(S.z_at(k)) : z, xo);
 }
 
-// One thread per node within W + R of a face, adding the terms of axes
-// a0 .. 2: a0 = 0 after the plain step (all nodes of the shell), a0 = 1 after
-// the step with the x part fused in (then only the z-layer planes and the
-// y-layer rows of the shell, count = its first two parts, need a term).
+// After the plain step: one thread per node within W + R of a face adds the
+// terms of all three axes.
 __global__ void __launch_bounds__(256) cpml_fix_kernel(CpmlArgs c, const float *__restrict__ cur,
-                                                       const float *__restrict__ m, float *out, int a0,
-                                                       unsigned count) {
+                                                       const float *__restrict__ m, float *out) {
   const Shell S(c.W + R, c.nx, c.ny, c.nz);
   const unsigned t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= count) return;
+  if (t >= S.count()) return;
   int x, y, z;
   S.node(t, x, y, z);
   const unsigned o = (static_cast<unsigned>(z) * c.ny + y) * c.nx + x;
   float extra = 0.f;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    if (a < a0) continue;
     const AxisAt A = axis_at(c, a, x, y, z);
     if (A.i >= c.W + R && A.i < A.n - c.W - R) continue;  // psi_a and zeta_a vanish this far in
     float dpsi = 0.f;
@@ -1283,7 +1280,7 @@ hipError_t launch_cpml_fix(const CpmlArgs &c, const float *cur, const float *m, 
   }
   const unsigned n = S.count();
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(cpml_fix_kernel, dim3((n + 255) / 256), dim3(256), 0, s, c, cur, m, out, 0, n);
+  hipLaunchKernelGGL(cpml_fix_kernel, dim3((n + 255) / 256), dim3(256), 0, s, c, cur, m, out);
   return hipGetLastError();
 }
 
