@@ -381,7 +381,7 @@ static_assert(kPadZ >= (kQ - 1) + kMaxPD + R, "z padding must cover the last tri
 // in place on the x layers.  Off the layers psi_x and zeta_x read as zero,
 // so this needs no branch.  psi_x and zeta_x come through the prefetch
 // pipeline; psi_x is staged in LDS like A^n (its x neighbours are other
-// lanes' values).  The y and z parts follow in cpml_fix_kernel over the rows
+// lanes' values).  The y and z parts follow in cpml_fix_yz_kernel over the rows
 // and planes within W + R of a y or z face: in the streaming kernel their
 // neighbours would be loads the z loop waits on in every such row and plane.
 // KEEP: the fields read or written once (float32: A^{n-1}, m, A^{n+1};
@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   static_assert(!KEEP || (!SEMI && !CP), "the cached policy is for the plain steps");
   constexpr int NTP = KEEP ? 0 : kNT;  // cache policy of the fields read or written once
   // f16 storage with 16-bit m sums the Laplacian from its centre weight (Eq. 1
-  // as written) instead of as centred differences: 25 instead of 48 vector
+  // as written) instead of as centred differences: 25 instead of 42.5 vector
   // operations per node, for the one form whose rate the instruction issue
   // limits.  Its float32 rounding, relative to the terms rather than to their
   // differences, stays far below the f16 rounding of the stored fields.
@@ -1665,9 +1665,10 @@ constexpr Variant kVariants[] = {WAVE_VARIANTS(WAVE_VARIANT_INFO)};
 #undef WAVE_VARIANT_INFO
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Shapes with the x part of the CPML boundary fused into the step: those
-// whose fused kernel fits the register file without spilling (at most two
-// rows per wavefront and four nodes per thread).
+// Shapes with the x part of the CPML boundary fused into the step: at most two
+// rows per wavefront and four nodes per thread, which fit the register file.
+// Those of 9 to 12 wavefronts (26, 27, 28), with 168 registers to a thread, spill
+// 8 to 16 of them; tuning times them with the others all the same.
 template <int RY, int VEC>
 constexpr bool fuses_cpml() {
   return RY <= 2 && RY * VEC <= 4;

@@ -143,14 +143,14 @@ struct GridRows {
 
 struct Variant {
   int by;   // wavefronts per workgroup
-  int ry;   // consecutive rows per wavefront (tile height = by * ry)
+  int ry;   // consecutive rows per row of lanes
   int pd;   // z-planes of loads in flight ahead of the plane being computed
-  int vec;  // consecutive x nodes per lane (tile width = 64 * vec); needs nx % vec == 0
+  int vec;  // consecutive x nodes per lane; needs nx % vec == 0
   int family;  // 0: 2.5D streaming; 1: 3D blocks from global memory; 2: 3D blocks via LDS;
                // 3: 2.5D streaming with a semi-stencil z sum; 4: two time steps per
                // pass (families 1 and 2: blocks of 64 x by x ry nodes; families 1-4:
                // float32 forward only)
-  int lx;   // 2.5D: lanes per tile row (tile lx * vec x 64 * by / lx * ry nodes)
+  int lx;   // lanes per tile row (families 0, 3 and 4: tile lx * vec x 64 * by / lx * ry nodes)
 };
 
 int variant_count();
