@@ -620,9 +620,11 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   };
   // per-plane tables, nz + kPadZ entries: the padding planes read sponge
   // factor 0 and receiver index -1
-  // (one resource over both: rz lies behind gz in the workspace)
+  // (one resource over both, from plane zb on: rz lies behind gz in the
+  // workspace, and table entries counted from plane 0 would pass 2^32 bytes in
+  // grids of 2^29 planes)
   const uint32_t rz_off = static_cast<uint32_t>(reinterpret_cast<const char *>(a.rz) - reinterpret_cast<const char *>(a.gz));
-  const rsrc_t rgz = make_rsrc(a.gz, rz_off + static_cast<uint32_t>(a.nz + kPadZ) * 4u);
+  const rsrc_t rgz = make_rsrc(a.gz + zb, rz_off + static_cast<uint32_t>(zhi - zb) * 4u);
   // residual row of this launch (adjoint); the resource covers exactly that
   // row.  Without receivers it has no records (its loads return zero).
   const bool has_res = ADJ && a.resid != nullptr && a.nrec > 0;
@@ -637,8 +639,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
     const rsrc_t u = rU(live), p = rP(live), mm = rM(live);
     const uint32_t sl = so(z + R);
     const uint32_t sc = so(z), scf = so_f(z);
-    st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z) * 4u).w[0]);
-    st.rz = static_cast<int>(ld_words<4, 0>(rgz, 0u, rz_off + static_cast<uint32_t>(z) * 4u).w[0]);
+    st.gz = __uint_as_float(ld_words<4, 0>(rgz, 0u, static_cast<uint32_t>(z - zb) * 4u).w[0]);
+    st.rz = static_cast<int>(ld_words<4, 0>(rgz, 0u, rz_off + static_cast<uint32_t>(z - zb) * 4u).w[0]);
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
       st.lead[j] = ld_words<NA, 0>(u, vrow[j], sl);

@@ -47,3 +47,25 @@ def test_cpml_of_134_million_layer_rows():
         del s
     assert out[0][1].abs().max() > 0
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_more_planes_than_32_bit_table_offsets_hold():
+    """1 x 1 x (2^29 + 1000) nodes, source and receivers in the last planes:
+    what a grid of 1000 planes gives at its end, where nothing from the other
+    end arrives (4 planes a step)."""
+    from paper_2404_04441_amd import Solver
+
+    nt = 6
+    wav = torch.from_numpy(ricker(nt, DT, 60.0, t0=2 * DT)).cuda()
+    out = []
+    for nz in (1000, (1 << 29) + 1000):
+        print(f"case: 1 x 1 x {nz}", flush=True)
+        rec = np.array([(0, 0, nz - 30 + k) for k in range(0, 30, 3)])
+        s = Solver(torch.full((nz, 1, 1), 3000.0, device="cuda"), H, DT, src=(0, 0, nz - 9), rec=rec, tune=False)
+        tr = s.run(nt, wav)
+        assert s.sync_status() == 0
+        out.append((tr, s.read_field(0)[-60:].clone()))
+        s.close()
+        del s
+    assert out[0][1].abs().max() > 0
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
