@@ -639,9 +639,14 @@ __global__ void __launch_bounds__(256) set_kernel(Op op, RowMap map) {
       u = (r0 + k) * map.nx + col;
       n = min(4u, map.nx - col);
     }
+    typename Op::T v[4];
+    if (FLAT && (t0 + 64u) * 4u <= map.total) {  // the whole wavefront: no checks per lane
+      op.in(u, v, 4u);
+      op.set(f, v, 4u, 4u);
+      continue;
+    }
     // the nodes past a row's end are the next row's, but for the array's last
     const unsigned have = static_cast<unsigned>(min(map.total - u, size_t(4)));
-    typename Op::T v[4];
     op.in(u, v, have);
     if constexpr (FLAT) op.set(f, v, have, have);
     else op.set(f, v, n, 4u);
@@ -650,8 +655,9 @@ __global__ void __launch_bounds__(256) set_kernel(Op op, RowMap map) {
 }
 
 // Passes that read a field.  Op::at(f, v): four stored nodes of the field from
-// index f; Op::out(u, v, row, col, n): n of them to index u of the caller's array,
-// the first one node col of row `row` (FLAT: row 0, col = u).
+// index f; Op::out(u, v, r0, k, col, n): n of them to index u of the caller's
+// array, the first one node col of row r0 + k, r0 the same for the wavefront
+// (FLAT: row 0, col = u).
 template <bool FLAT, class Op>
 __global__ void __launch_bounds__(256) read_kernel(Op op, RowMap map) {
   const unsigned lane = threadIdx.x & 63u;
@@ -660,24 +666,26 @@ __global__ void __launch_bounds__(256) read_kernel(Op op, RowMap map) {
     if (t0 + lane >= map.nvec) break;
     const size_t u = (t0 + lane) * 4u;
     typename Op::Raw v;
-    size_t row = 0, col = u;
+    uint64_t r0 = 0;
+    unsigned k = 0;
+    size_t col = u;
     if constexpr (FLAT) {
       op.at(u, v);
     } else {
       const size_t u0 = t0 * 4u;
-      const uint64_t r0 = map.row(u0);
-      const unsigned i = static_cast<unsigned>(u0 - r0 * map.row.d) + 4u * lane, k = map.in_row(i);
-      row = r0 + k;
+      r0 = map.row(u0);
+      const unsigned i = static_cast<unsigned>(u0 - r0 * map.row.d) + 4u * lane;
+      k = map.in_row(i);
       col = i - k * map.in_row.d;
-      op.at(row * map.pitch + col, v);
+      op.at((r0 + k) * map.pitch + col, v);
       const unsigned n = static_cast<unsigned>(map.nx - col);
       if (n < 4u) {
         typename Op::Raw w;
-        op.at((row + 1) * map.pitch - n, w);
+        op.at((r0 + k + 1) * map.pitch - n, w);
         v.from(w, n);
       }
     }
-    op.out(u, v, row, col, static_cast<unsigned>(min(map.total - u, size_t(4))));
+    op.out(u, v, r0, k, col, static_cast<unsigned>(min(map.total - u, size_t(4))));
   }
 }
 
@@ -842,12 +850,14 @@ __global__ void scale_record_kernel(StepState *st, int v_field) {
 
 // Values as they are into a field, from an array that starts at any multiple
 // of ALIGN bytes (float32 between two fields too, of which a checkpoint starts at
-// any element).
-template <typename V, int ALIGN> struct CopyIn {
+// any element).  NT: past the cache, for arrays that with the field overflow
+// the 256 MB last-level cache (256x512x512 100 -> 87 us; 16x1024x1024, within it, 34 -> 31 us
+// without).
+template <typename V, int ALIGN, bool NT = false> struct CopyIn {
   using T = V;
   const V *x;
   V *dst;
-  __device__ void in(size_t u, V (&v)[4], unsigned n) { get4<ALIGN, false>(x + u, v, n); }
+  __device__ void in(size_t u, V (&v)[4], unsigned n) { get4<ALIGN, NT>(x + u, v, n); }
   __device__ void set(size_t f, const V (&v)[4], unsigned n, unsigned k) {
     V o[4];
 #pragma unroll
@@ -863,7 +873,7 @@ template <typename V, int ALIGN> struct CopyOut {
   const V *src;
   V *dst;
   __device__ void at(size_t f, Raw &r) { get4<sizeof(V), false>(src + f, r.v[0]); }
-  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) { put4<ALIGN, true>(dst + u, r.v[0], n); }
+  __device__ void out(size_t u, const Raw &r, uint64_t, unsigned, size_t, unsigned n) { put4<ALIGN, true>(dst + u, r.v[0], n); }
 };
 
 template <int S> struct Decode {
@@ -874,7 +884,7 @@ template <int S> struct Decode {
   const StepState *st;
   int slot_off, v_field;
   __device__ void at(size_t f, Raw &r) { get4<sizeof(raw), false>(src + f, r.v[0]); }
-  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) {
+  __device__ void out(size_t u, const Raw &r, uint64_t, unsigned, size_t, unsigned n) {
     float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = Codec<S>::dec(r.v[0][e]);
@@ -896,23 +906,25 @@ template <int S> struct DecodePrev {
   float *dst;
   const float *gx, *gy, *gz;
   FastDiv64 nx, ny;
+  FastDiv ny32;
   const StepState *st;
   __device__ void at(size_t f, Raw &r) {
     get4<sizeof(raw), false>(fa + f, r.v[0]);
     get4<sizeof(raw), false>(fv + f, r.v[1]);
   }
-  __device__ float gyz(size_t row) const {  // the step kernel's association; gz goes on past the grid
-    const uint64_t z = ny(row);
-    return gy[row - z * ny.d] * gz[z];
+  __device__ float gyz(uint64_t r0, unsigned k) const {  // the step kernel's association; gz goes on past the grid
+    const uint64_t z = ny(r0);
+    const unsigned y = static_cast<unsigned>(r0 - z * ny.d) + k, over = ny32(y);
+    return gy[y - over * ny32.d] * gz[z + over];
   }
-  __device__ void out(size_t u, const Raw &r, size_t row, size_t col, unsigned n) {
+  __device__ void out(size_t u, const Raw &r, uint64_t r0, unsigned k, size_t col, unsigned n) {
     const int slot = st->n & 3;
     const float ia = exp2i(-st->exps[slot]), iv = exp2i(-st->exps_v[slot]);
     if (col >= nx.d) {  // counted through the rows
-      row = nx(col);
-      col -= row * nx.d;
+      r0 = nx(col);
+      col -= r0 * nx.d;
     }
-    float v[4], g[4], gr = gyz(row);
+    float v[4], g[4], gr = gyz(r0, k);
     if (col + 4u <= nx.d) {
       get4<4, false>(gx + col, g);
 #pragma unroll
@@ -922,7 +934,7 @@ template <int S> struct DecodePrev {
       for (int e = 0; e < 4; ++e) {
         if (col == nx.d) {
           col = 0;
-          gr = gyz(++row);
+          gr = gyz(r0, ++k);
         }
         g[e] = gx[col++] * gr;
       }
@@ -943,7 +955,7 @@ struct GradFinal {
     get4<4, false>(img + f, r.v[0]);
     get4<4, false>(m + f, r.v[1]);
   }
-  __device__ void out(size_t u, const Raw &r, size_t, size_t, unsigned n) {
+  __device__ void out(size_t u, const Raw &r, uint64_t, unsigned, size_t, unsigned n) {
     float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = 2.f * r.v[0][e] * dt / sqrtf(r.v[1][e]);
@@ -1153,6 +1165,7 @@ hipError_t launch_encode_field(int storage, const float *x, void *dst, const Gri
 }
 
 hipError_t launch_copy_in(const float *x, float *dst, const GridRows &g, hipStream_t s) {
+  if (8 * g.rows * g.nx > (size_t(256) << 20)) return launch_set(CopyIn<float, 4, true>{x, dst}, g, false, s);
   return launch_set(CopyIn<float, 4>{x, dst}, g, false, s);
 }
 
@@ -1201,8 +1214,8 @@ hipError_t launch_decode_prev(int storage, const void *fa, const void *fv, float
                               hipStream_t s) {
   const uint16_t *a = static_cast<const uint16_t *>(fa), *v = static_cast<const uint16_t *>(fv);
   const FastDiv64 dx(g.nx), dy(ny);
-  if (storage == kF16) return launch_read(DecodePrev<kF16>{a, v, out, gx, gy, gz, dx, dy, st}, g, true, s);
-  if (storage == kBF16) return launch_read(DecodePrev<kBF16>{a, v, out, gx, gy, gz, dx, dy, st}, g, true, s);
+  if (storage == kF16) return launch_read(DecodePrev<kF16>{a, v, out, gx, gy, gz, dx, dy, FastDiv(ny), st}, g, true, s);
+  if (storage == kBF16) return launch_read(DecodePrev<kBF16>{a, v, out, gx, gy, gz, dx, dy, FastDiv(ny), st}, g, true, s);
   return hipErrorInvalidValue;
 }
 
