@@ -96,7 +96,7 @@ typedef struct {
                                 CPML or adjoint also the 3D-blocked gmem and smem shapes.  The
                                 fastest few are then timed in turn, on noise and from rest, and the
                                 smallest sum is kept (the fixed rule's choice unless another is more
-                                than 3% faster).  With adjoint != 0 it also times the adjoint
+                                than 1% faster).  With adjoint != 0 it also times the adjoint
                                 step's shapes and z-chunks on their own and keeps the fastest the
                                 same way.  The choices are cached per (nx, ny, nz, storage, CPML,
                                 adjoint, cache_hint, model_bits) for the life of the process.
