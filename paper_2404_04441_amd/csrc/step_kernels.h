@@ -399,7 +399,7 @@ static_assert(kPadZ >= (kQ - 1) + kMaxPD + R, "z padding must cover the last tri
 // from the recomputation (it is computed there in any case) the adjoint
 // step has one stencil, one queue and one ring instead of two, and the image is
 // read and written every second step: 60 instead of 64 bytes per node and step
-// of the whole gradient, and an adjoint step of 256^3 went from 87 us to 42
+// of the whole gradient, and an adjoint step of 256^3 went from 88 us to 39
 // and 73 us in turn.
 template <int S, int BY, int RY, int PD, int VEC, int LX, bool SEMI, int MODE, bool CP, bool KEEP, bool M16 = false>
 __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
@@ -750,8 +750,8 @@ __global__ void __launch_bounds__(64 * BY) step_kernel(StepArgs a) {
   // bf16 is the exception: its exponent range is float32's, so that the far
   // tails of a wave are float32 subnormals in true units and rounded there;
   // it decodes to true units (kTrue: two multiplications more per node).  At
-  // 1024^3 with 16-bit m 2260 us a step before both, 2050 us now; f16 at 512^3
-  // 294 and 290 us, both on fields of waves.
+  // 1024^3 with 16-bit m 2260 us a step before both, 2037 us now; f16 at 512^3
+  // 302 and 286 us, both on fields of waves.
   // Where the exponents lie so far apart that a factor could overflow (fields
   // set to arbitrary scales by wave_write_field), the chunk is advanced in
   // true units, node by node (step_far).

@@ -550,9 +550,9 @@ __global__ void __launch_bounds__(256) cpml_fix_kernel(CpmlArgs c, const float *
 // without row padding count as one row.  Bound by memory: one access per lane
 // and array in many short workgroups, the form that streams fastest here.
 // Against one node per lane and access in a strided loop, 1024^3 bf16: reading a
-// field 1937 -> 1080 us, its maximum 1165 -> 773 us, encoding it 1509 -> 1105 us.
+// field 1940 -> 1030 us, its maximum 1200 -> 800 us, encoding it 1500 -> 1105 us.
 // The set-up of m at 256^3, which queued two atomics per workgroup on one line:
-// 378 -> 34 us.  Rows of a vector each, a wavefront per row and single accesses
+// 378 -> 40 us.  Rows of a vector each, a wavefront per row and single accesses
 // in padded rows, took 2 to 14 times as long where rows are short or padded: A^{n-1}
 // of 4x2048x2048 f16 783 -> 40 us, reading 33x896x896 f32 87 -> 41 us, writing it
 // 133 -> 44 us, and a snapshot of 301x512x512 f16, then copied by
