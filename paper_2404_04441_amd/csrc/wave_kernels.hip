@@ -144,7 +144,7 @@ template <int VEC> __device__ __forceinline__ void st_row(const float *v, rsrc_t
 // Every XCD takes an eighth of each part (z-layer rows, y-layer rows, nodes of
 // the x slabs), so that they end together.  Measured at 512^3, W = 20: the psi
 // update (before: a row kernel of 95 us and a column kernel of 37 us) 83 us,
-// 0.44 GB; the correction reads 0.45 instead of 0.80 GB; at 401x333x301, where a lane held one node, a whole step went from
+// 0.44 GB; the correction reads 0.45 instead of 0.80 GB (0.50 with four rows a wavefront); at 401x333x301, where a lane held one node, a whole step went from
 // 398 to 362 us.  Bundles of 4, 32 and 64 rows differ by 1%.
 constexpr unsigned kBundle = 32;
 

@@ -651,6 +651,19 @@ std::vector<Tiling> shortlist(std::vector<TimedTiling> timed) {
   return out;
 }
 
+// The `count` fastest 2.5D shapes among the candidates timed, each under the
+// cache policy it was faster with: two policies of one shape would keep another
+// out, whose best z-chunk is then never timed.
+std::vector<TimedTiling> fastest_shapes(std::vector<TimedTiling> timed, size_t count) {
+  std::sort(timed.begin(), timed.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+  std::vector<TimedTiling> out;
+  for (const auto &c : timed) {
+    const bool taken = std::any_of(out.begin(), out.end(), [&](const auto &o) { return o.second.variant == c.second.variant; });
+    if (variant_info(c.second.variant).family == 0 && !taken && out.size() < count) out.push_back(c);
+  }
+  return out;
+}
+
 // The index of the smallest score; the default (index 0) unless another is more
 // than 1% below it, so that near-ties do not move the choice (times taken in
 // turn repeat to that; at 896^3 another z-chunk is 1.5% faster).
@@ -734,12 +747,8 @@ int tune_forward(wave_ctx *w) {
   }
   std::vector<TimedTiling> timed;
   for (size_t i = 0; i < cands.size() && !rc; ++i) timed.emplace_back(time_one(cands[i]), cands[i]);
-  // stage 2: the z-chunk lists of the four fastest 2.5D candidates of stage 1
-  std::vector<TimedTiling> top;
-  for (const auto &c : timed)
-    if (variant_info(c.second.variant).family == 0) top.push_back(c);
-  std::sort(top.begin(), top.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-  if (top.size() > 4) top.resize(4);
+  // stage 2: the z-chunk lists of the four fastest 2.5D shapes of stage 1
+  const std::vector<TimedTiling> top = fastest_shapes(timed, 4);
   for (const auto &c : top) {
     wave_params q = p;
     q.variant = c.second.variant;
@@ -828,9 +837,7 @@ int tune_forward(wave_ctx *w) {
         if (!rc) ta.emplace_back(time_adj(t, npair), t);
       }
     }
-    std::vector<TimedTiling> top(ta.begin(), ta.end());
-    std::sort(top.begin(), top.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-    if (top.size() > 2) top.resize(2);
+    const std::vector<TimedTiling> top = fastest_shapes(ta, 2);
     for (const auto &c : top) {
       wave_params q = p;
       q.variant = c.second.variant;
